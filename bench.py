@@ -252,8 +252,8 @@ def kernel_avg_us(launch, reps):
 # their joint hash, so a counter figure is reported only for the kernels it
 # was measured on.
 KERNEL_SOURCES = {
-    "backbone": ["backbone.hip", "scan.h", "affine.h", "sincos.h", "a2c_internal.h"],
-    "fullatom": ["fullatom.hip", "scan.h", "affine.h", "sincos.h", "a2c_internal.h"],
+    "backbone": ["backbone.hip", "scan.h", "spine.h", "affine.h", "sincos.h", "a2c_internal.h"],
+    "fullatom": ["fullatom.hip", "scan.h", "spine.h", "affine.h", "sincos.h", "a2c_internal.h"],
 }
 
 

@@ -207,8 +207,8 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  * A2C_FULLATOM) and waves of 64 lanes per workgroup (1..16).  A chunk is
  * 64 * waves * res_per_lane consecutive residues.
  *   - The forwards of both models (a2c_forward, A2C_SCAN), the backbone
- *     adjoint from coordinates (a2c_backward with d_coords) and every
- *     full-atom adjoint (a2c_backward, a2c_mse_step) run on windows:
+ *     adjoint from coordinates (a2c_backward with d_coords), every full-atom
+ *     adjoint and the fused step (a2c_mse_step) run on windows:
  *     workgroup t takes residues [s_t, s_t+1) of the packed batch, at most
  *     one chunk C.  Where every chain fits in one chunk, the windows hold
  *     whole chains, packed in order; otherwise they are fixed,
@@ -221,17 +221,20 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  *     adjoints take fixed windows last to first, in each class of workgroup
  *     index mod 8 separately, and whole-chain ones in order; the full-atom
  *     ones that recompute the frames first run a spine-only pass over the
- *     same windows, which waits on nothing); a launch therefore progresses
- *     whenever the device holds 8 of its workgroups at once.  Consequently
- *     two such calls on one plan must not run at the same time (on
- *     different streams).
+ *     same windows, which waits on nothing; the backbone fused step takes
+ *     fixed windows in order and also waits on those its last chain runs
+ *     into, unless a chain spans more than 32 windows, when it runs that
+ *     spine pass as well); a launch therefore progresses whenever the device
+ *     holds 32 of its workgroups at once.  Consequently two such calls on one
+ *     plan must not run at the same time (on different streams).
  *   - The backbone adjoint that recomputes the frames (a2c_backward without
- *     d_coords) and the backbone a2c_mse_step pack chains of at most one
- *     chunk whole, in order, into tiles of at most one chunk; a longer chain
- *     gets a tile of its own, which one workgroup walks chunk by chunk (at
- *     most 64 chunks), carrying the frame (forward) and the wrench (adjoint)
- *     from chunk to chunk.  One workgroup per tile, longest tiles dispatched
- *     first.
+ *     d_coords) hands nothing between workgroups.  Where every chain fits in
+ *     one chunk, it and the backbone fused step run on windows of whole
+ *     chains; otherwise the adjoint packs chains of at most one chunk whole,
+ *     in order, into tiles of at most one chunk, and a longer chain gets a
+ *     tile of its own, which one workgroup walks chunk by chunk (at most 64
+ *     chunks), carrying the frame (forward) and the wrench (adjoint) from
+ *     chunk to chunk.
  * Re-packs and re-uploads the tables (synchronises `stream`).
  * The tables of the schedule it replaces stay allocated until
  * a2c_plan_destroy, so a graph captured before the change replays the
@@ -338,18 +341,18 @@ a2c_status a2c_coords_to_angles(a2c_plan *plan, const float *d_coords, float *d_
 /* Fused training step for the squared-distance loss
  *   L = sum over atoms a of |r_a - t_a|^2
  * (r the map of d_angles, t = d_target [3][A]): one kernel, one workgroup
- * per tile, recomputes the frames, forms the loss gradient 2 (r - t) in
+ * per window, recomputes the frames, forms the loss gradient 2 (r - t) in
  * registers and runs the adjoint above, so neither the coordinates nor
  * their gradient make a round trip through memory.  Same result as
  * a2c_forward, then dL/dr = 2 (r - t), then a2c_backward, up to float32
  * rounding.
  *   d_coords      [3][A] receives r, or NULL (not written);
- *   d_loss        float[1] receives L, or NULL (not computed).  Each tile
+ *   d_loss        float[1] receives L, or NULL (not computed).  Each window
  *                 adds its atoms in a fixed order into a share kept in the
- *                 plan; the tile that finishes last sums the shares in tile
- *                 order, so L is deterministic for a given schedule.
+ *                 plan; the workgroup dispatched last sums the shares in
+ *                 window order, so L is deterministic for a given schedule.
  *   d_grad_angles [K][R] receives dL/dalpha.
- * Enqueues one kernel on `stream` (a fill kernel for an empty plan); no
+ * Enqueues kernels only on `stream` (a fill kernel for an empty plan); no
  * allocation (capturable).  Calls that share a plan must not overlap. */
 a2c_status a2c_mse_step(a2c_plan *plan, const float *d_angles, const float *d_target,
                         float *d_coords, float *d_loss, float *d_grad_angles, void *stream);

@@ -67,15 +67,24 @@ struct FATable {
     int32_t max_side;
 };
 
+// Windows ahead of its own that a window of a recomputing adjoint may wait
+// on: a device (or a partition of one) that holds 32 workgroups at once makes
+// progress.  Batches with a chain over more windows take a spine pass.
+constexpr int kMaxAhead = 31;
+
 // One scan schedule: K residues per lane, W waves per workgroup, and the
-// layouts built for them: tiles (chains of at most one chunk of 64 W K
-// residues packed whole into tiles of at most one chunk; a longer chain
-// alone) and/or windows of at most one chunk C with a look-back table
-// (forwards and the full-atom adjoint: windows only; backbone adjoint: both,
-// windows for the adjoint from coordinates, tiles for the recomputing
-// adjoint and the fused step).  Windows hold whole chains where every chain
-// fits in one, and are fixed, [t C, t C + C), otherwise.  n_tiles counts the
-// layout the schedule reports: windows where there are no tiles.
+// layouts built for them, in chunks of C = 64 W K residues.
+//   - windows of at most C residues with look tables (every kernel but the
+//     backbone adjoint that recomputes the frames).  They hold whole chains
+//     where every chain fits in one and that packs well, and are fixed,
+//     [t C, t C + C), otherwise;
+//   - own windows (that adjoint, and the backbone fused step where the
+//     windows hold whole chains): whole chains wherever every chain fits in
+//     one;
+//   - tiles (that adjoint where a chain is longer than a chunk): chains of at
+//     most one chunk packed whole, a longer chain alone.
+// n_tiles counts the layout the schedule reports: windows, or for the
+// backbone adjoint own windows or tiles.
 struct Sched {
     int32_t K = 4, W = 4, n_tiles = 0;
     int32_t n_win = 0;                   // windows (0: none)
@@ -86,19 +95,18 @@ struct Sched {
                                          // aggregate window t composes; adjoint, the
                                          // last window whose wrench it adds (t: none)
     uint64_t *d_status = nullptr;        // n_win x kLbWords tagged words
-    // full-atom adjoint: a spine pass publishes each window's aggregate in
-    // its own tagged words; each window of the adjoint composes those of the
-    // windows its first chain spans (from d_look_fwd[t] to t - 1)
+    // recomputing adjoints on fixed windows: each window's spine aggregate in
+    // its own tagged words; a window composes those of the windows its first
+    // chain spans (from d_look_fwd[t] to t - 1)
     int32_t *d_look_fwd = nullptr;       // n_win, first window to compose
     uint64_t *d_status_fwd = nullptr;    // n_win x kLbWords tagged words
+    bool spined = false;                 // a chain spans more than kMaxAhead + 1 windows
     int32_t fa_stage_atoms = 0;          // per-wave staging (floats per plane)
     bool fa_unstaged = false;            // stage too large for the LDS: direct I/O
-    bool multi_chunk = false;            // some tile spans several chunks
+    int32_t n_own = 0;                   // own windows
+    int32_t *d_own_wstart = nullptr;     // n_own + 1 boundaries
+    uint64_t *d_own_status = nullptr;    // n_own x kLbWords tagged words (loss shares)
     int32_t *d_tile_res = nullptr;       // n_tiles (first, end) residue pairs, longest first
-    // fused training step: each tile's share of the loss, and the count of
-    // tiles done (the last one sums the shares; it re-arms the count to 0)
-    float *d_loss_part = nullptr;        // n_tiles
-    uint32_t *d_loss_count = nullptr;    // 1
 };
 
 }  // namespace a2c

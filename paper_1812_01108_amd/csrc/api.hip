@@ -39,24 +39,45 @@ a2c_status upload(void **dst, const void *src, size_t bytes, hipStream_t s)
     return A2C_OK;
 }
 
+// The device tables a schedule owns.
+std::vector<void *> sched_tables(const Sched &S)
+{
+    return {S.d_tile_res, S.d_wstart,     S.d_look,      S.d_status, S.d_look_fwd, S.d_status_fwd,
+            S.d_own_wstart, S.d_own_status};
+}
+
+void forget_tables(Sched &S)
+{
+    S.d_tile_res = S.d_wstart = S.d_look = S.d_look_fwd = S.d_own_wstart = nullptr;
+    S.d_status = S.d_status_fwd = S.d_own_status = nullptr;
+}
+
 void free_sched(Sched &S)
 {
-    (void)hipFree(S.d_tile_res);
-    (void)hipFree(S.d_loss_part);
-    (void)hipFree(S.d_loss_count);
-    (void)hipFree(S.d_wstart);
-    (void)hipFree(S.d_look);
-    (void)hipFree(S.d_status);
-    (void)hipFree(S.d_look_fwd);
-    (void)hipFree(S.d_status_fwd);
-    S.d_tile_res = nullptr;
-    S.d_loss_part = nullptr;
-    S.d_loss_count = nullptr;
-    S.d_wstart = nullptr;
-    S.d_look = nullptr;
-    S.d_status = nullptr;
-    S.d_look_fwd = nullptr;
-    S.d_status_fwd = nullptr;
+    for (void *q : sched_tables(S)) (void)hipFree(q);
+    forget_tables(S);
+}
+
+// Boundaries of windows of at most `cap` residues that hold whole chains,
+// packed greedily in order (none for an empty batch or where a chain is
+// longer than cap).  Zero-length chains take no space.
+std::vector<int64_t> whole_chain_starts(const a2c_plan *p, int64_t cap)
+{
+    std::vector<int64_t> st;
+    if (p->R == 0 || p->max_len > cap) return st;
+    st.push_back(0);
+    int64_t cur = 0;  // residues in the open window
+    for (size_t c = 0; c + 1 < p->res_off.size(); ++c) {
+        const int64_t L = p->res_off[c + 1] - p->res_off[c];
+        if (L == 0) continue;
+        if (cur + L > cap) {
+            st.push_back(p->res_off[c]);
+            cur = 0;
+        }
+        cur += L;
+    }
+    st.push_back(p->R);
+    return st;
 }
 
 // Window boundaries for windows of at most `cap` residues (n_win + 1
@@ -69,30 +90,16 @@ void free_sched(Sched &S)
 // wherever the chains fall.  Zero-length chains take no space.
 std::vector<int64_t> window_starts(const a2c_plan *p, int64_t cap, bool &whole_chains)
 {
-    std::vector<int64_t> st;
+    std::vector<int64_t> st = whole_chain_starts(p, cap);
     whole_chains = false;
     if (p->R == 0) return st;
     const int64_t n_fixed = (p->R + cap - 1) / cap;
-    if (p->max_len <= cap) {
-        st.push_back(0);
-        int64_t cur = 0;  // residues in the open window
-        for (size_t c = 0; c + 1 < p->res_off.size(); ++c) {
-            const int64_t L = p->res_off[c + 1] - p->res_off[c];
-            if (L == 0) continue;
-            if (cur + L > cap) {
-                st.push_back(p->res_off[c]);
-                cur = 0;
-            }
-            cur += L;
-        }
-        st.push_back(p->R);
-        const int64_t n_whole = (int64_t)st.size() - 1;
-        if (n_whole <= n_fixed + n_fixed / 8 || n_whole <= p->n_cu) {
-            whole_chains = true;
-            return st;
-        }
-        st.clear();
+    const int64_t n_whole = (int64_t)st.size() - 1;
+    if (!st.empty() && (n_whole <= n_fixed + n_fixed / 8 || n_whole <= p->n_cu)) {
+        whole_chains = true;
+        return st;
     }
+    st.clear();
     for (int64_t b = 0; b < p->R; b += cap) st.push_back(b);
     st.push_back(p->R);
     return st;
@@ -104,15 +111,26 @@ int32_t window_of(const std::vector<int64_t> &starts, int64_t r)
     return (int32_t)(std::upper_bound(starts.begin(), starts.end() - 1, r) - starts.begin()) - 1;
 }
 
+// kLbWords tagged words for each of n windows, at tag 0.
+a2c_status new_words(uint64_t *&d_status, int64_t n, hipStream_t s)
+{
+    const size_t words = (size_t)std::max<int64_t>(1, n) * kLbWords * sizeof(uint64_t);
+    hipError_t e = hipMalloc((void **)&d_status, words);
+    if (e == hipSuccess) e = hipMemsetAsync(d_status, 0, words, s);
+    return e == hipSuccess ? A2C_OK : hip_fail(e, "look-back words");
+}
+
 // Look-back table and tagged words of the windows given by starts.  Forward
 // (look_back): for each window t the first window whose aggregate its
 // carry-in needs, i.e. the window holding the head of the chain its first
 // residue belongs to (t itself when a chain starts there).  Adjoint: the last
 // window whose wrench it adds, i.e. the window holding the end of the chain
-// of its last residue (t itself when a chain ends there).  The tagged words
+// of its last residue (t itself when a chain ends there).  long_span is set
+// where a window looks more than kMaxAhead windows away.  The tagged words
 // start at tag 0.
 a2c_status build_windows(const a2c_plan *p, const std::vector<int64_t> &starts, bool look_back,
-                         int32_t *&d_look, uint64_t *&d_status, int32_t &n_win, hipStream_t s)
+                         int32_t *&d_look, uint64_t *&d_status, int32_t &n_win, bool &long_span,
+                         hipStream_t s)
 {
     const int64_t n = starts.empty() ? 0 : (int64_t)starts.size() - 1;
     std::vector<int32_t> look((size_t)n);
@@ -122,15 +140,12 @@ a2c_status build_windows(const a2c_plan *p, const std::vector<int64_t> &starts, 
         while (p->res_off[c + 1] <= r) ++c;
         look[(size_t)t] =
             window_of(starts, look_back ? p->res_off[c] : (int64_t)p->res_off[c + 1] - 1);
+        if (std::abs((int64_t)look[(size_t)t] - t) > kMaxAhead) long_span = true;
     }
     n_win = (int32_t)n;
     a2c_status st = upload((void **)&d_look, look.data(), look.size() * sizeof(int32_t), s);
     if (st != A2C_OK) return st;
-    const size_t words = (size_t)std::max<int64_t>(1, n) * kLbWords * sizeof(uint64_t);
-    hipError_t e = hipMalloc((void **)&d_status, words);
-    if (e == hipSuccess) e = hipMemsetAsync(d_status, 0, words, s);
-    if (e != hipSuccess) return hip_fail(e, "look-back words");
-    return A2C_OK;
+    return new_words(d_status, n, s);
 }
 
 // The window boundaries as int32 on the device.
@@ -176,125 +191,72 @@ enum SchedRole { kRoleForward, kRoleAdjoint };
 a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipStream_t s,
                        SchedRole role)
 {
-    const bool flat = role == kRoleForward || p->model == A2C_FULLATOM;  // windows only
-    const bool windows = flat || p->model == A2C_BACKBONE;
     const int64_t cap = (int64_t)kWave * W * K;  // residues per chunk
     if (p->max_len > cap * kMaxChunks)
         return fail(A2C_ERR_UNSUPPORTED, "a chain of " + std::to_string(p->max_len) +
                                              " residues needs more than " +
                                              std::to_string(kMaxChunks) + " chunks of " +
                                              std::to_string(cap) + " residues");
-    bool whole_chains = false;
-    const std::vector<int64_t> starts =
-        windows ? window_starts(p, cap, whole_chains) : std::vector<int64_t>();
-    if (flat) {
-        Sched S;
-        S.K = K;
-        S.W = W;
-        S.whole_chains = whole_chains;
-        if (p->model == A2C_FULLATOM) {
-            // per-wave LDS stage of three planes (the adjoint from
-            // coordinates stages six where they fit): the most atoms of one
-            // wave's run of 64 K residues
-            int64_t most = 1;
-            for (size_t t = 0; t + 1 < starts.size(); ++t)
-                for (int64_t rb = starts[t]; rb < starts[t + 1]; rb += (int64_t)kWave * K) {
-                    const int64_t re = std::min<int64_t>(rb + (int64_t)kWave * K, starts[t + 1]);
-                    most = std::max<int64_t>(most, p->res_atom_off[re] - p->res_atom_off[rb]);
-                }
-            if ((size_t)W * 3 * most * sizeof(float) > (size_t)kMaxDynamicLds)
-                S.fa_unstaged = true;  // atoms straight to global memory
-            else
-                S.fa_stage_atoms = (int32_t)most;
-        }
-        const bool fwd = role == kRoleForward;
-        a2c_status st = upload_starts(starts, S.d_wstart, s);
-        if (st == A2C_OK) st = build_windows(p, starts, fwd, S.d_look, S.d_status, S.n_win, s);
-        S.n_tiles = S.n_win;
-        if (st == A2C_OK && !fwd) {
-            // the full-atom adjoint: the spine pass's words and the windows
-            // whose aggregates each window composes (the fused step's loss
-            // shares travel in the adjoint's own tagged words)
-            int32_t n2 = 0;
-            st = build_windows(p, starts, true, S.d_look_fwd, S.d_status_fwd, n2, s);
-        }
-        if (st == A2C_OK) {
-            const hipError_t e = hipStreamSynchronize(s);
-            if (e != hipSuccess) st = hip_fail(e, "hipStreamSynchronize");
-        }
-        if (st != A2C_OK) {
-            free_sched(S);
-            return st;
-        }
-        out = S;
-        return A2C_OK;
-    }
-    std::vector<int32_t> tiles = pack_tiles(p->res_off, cap);
-    int32_t stage_atoms = 0;
-    if (p->model == A2C_FULLATOM) {
-        // largest atom run of one wave in one chunk: the per-wave staging size
-        const int64_t per_wave = (int64_t)kWave * K;
-        for (size_t t = 0; t + 1 < tiles.size(); ++t)
-            for (int64_t cs = tiles[t]; cs < tiles[t + 1]; cs += cap) {
-                const int64_t ce = std::min<int64_t>(cs + cap, tiles[t + 1]);
-                for (int64_t rb = cs; rb < ce; rb += per_wave) {
-                    const int64_t re = std::min<int64_t>(rb + per_wave, ce);
-                    stage_atoms = std::max<int32_t>(
-                        stage_atoms, p->res_atom_off[re] - p->res_atom_off[rb]);
-                }
-            }
-        stage_atoms = std::max<int32_t>(stage_atoms, 1);
-    }
-    // full-atom atom I/O goes through a per-wave LDS stage of three planes
-    // (forward, recompute adjoint; the coordinate-mode adjoint stages six and
-    // uses the recompute form where they do not fit); where three planes do
-    // not fit either, the kernels read and write the atoms in global memory
-    // directly
-    bool unstaged = false;
-    if (p->model == A2C_FULLATOM &&
-        (size_t)W * 3 * stage_atoms * sizeof(float) > (size_t)kMaxDynamicLds) {
-        unstaged = true;
-        stage_atoms = 0;
-    }
     Sched S;
-    S.whole_chains = whole_chains;
-    S.fa_stage_atoms = stage_atoms;
-    S.fa_unstaged = unstaged;
-    S.multi_chunk = false;
-    for (size_t t = 0; t + 1 < tiles.size(); ++t)
-        if (tiles[t + 1] - tiles[t] > cap) S.multi_chunk = true;
     S.K = K;
     S.W = W;
-    S.n_tiles = tiles.empty() ? 0 : (int32_t)tiles.size() - 1;
-    // (first, end) residue pairs, longest tile first: tiles are independent,
-    // and dispatching the long ones (multi-chunk chains, full tiles) first
-    // keeps them out of the tail of the launch
-    std::vector<int32_t> order(S.n_tiles);
-    for (int32_t t = 0; t < S.n_tiles; ++t) order[t] = t;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        return tiles[a + 1] - tiles[a] > tiles[b + 1] - tiles[b];
-    });
-    std::vector<int32_t> pairs(2 * (size_t)S.n_tiles);
-    for (int32_t t = 0; t < S.n_tiles; ++t) {
-        pairs[2 * t] = tiles[order[t]];
-        pairs[2 * t + 1] = tiles[order[t] + 1];
+    const std::vector<int64_t> starts = window_starts(p, cap, S.whole_chains);
+    if (p->model == A2C_FULLATOM) {
+        // per-wave LDS stage of three planes (the adjoint from coordinates
+        // stages six where they fit): the most atoms of one wave's run of
+        // 64 K residues
+        int64_t most = 1;
+        for (size_t t = 0; t + 1 < starts.size(); ++t)
+            for (int64_t rb = starts[t]; rb < starts[t + 1]; rb += (int64_t)kWave * K) {
+                const int64_t re = std::min<int64_t>(rb + (int64_t)kWave * K, starts[t + 1]);
+                most = std::max<int64_t>(most, p->res_atom_off[re] - p->res_atom_off[rb]);
+            }
+        if ((size_t)W * 3 * most * sizeof(float) > (size_t)kMaxDynamicLds)
+            S.fa_unstaged = true;  // atoms straight to global memory
+        else
+            S.fa_stage_atoms = (int32_t)most;
     }
-    a2c_status st = upload((void **)&S.d_tile_res, pairs.data(), pairs.size() * sizeof(int32_t), s);
-    if (st == A2C_OK && windows) st = upload_starts(starts, S.d_wstart, s);
-    if (st == A2C_OK && windows) st = build_windows(p, starts, false, S.d_look, S.d_status, S.n_win, s);
-    // the fused step's per-tile loss shares and its count of finished tiles
-    // (zero: the last tile of every launch sets it back to zero)
-    if (st == A2C_OK) {
-        hipError_t e = hipMalloc((void **)&S.d_loss_part,
-                                 std::max<size_t>(1, S.n_tiles) * sizeof(float));
-        if (e == hipSuccess) e = hipMalloc((void **)&S.d_loss_count, sizeof(uint32_t));
-        if (e == hipSuccess) e = hipMemsetAsync(S.d_loss_count, 0, sizeof(uint32_t), s);
-        if (e != hipSuccess) st = hip_fail(e, "loss scratch");
+    const bool fwd = role == kRoleForward;
+    bool ignored = false;
+    a2c_status st = upload_starts(starts, S.d_wstart, s);
+    if (st == A2C_OK)
+        st = build_windows(p, starts, fwd, S.d_look, S.d_status, S.n_win, ignored, s);
+    S.n_tiles = S.n_win;
+    if (st == A2C_OK && !fwd) {
+        // the recomputing adjoints: the spine aggregates' words and the
+        // windows whose aggregates each window composes (the fused step's
+        // loss shares travel in the adjoint's own tagged words)
+        int32_t n2 = 0;
+        st = build_windows(p, starts, true, S.d_look_fwd, S.d_status_fwd, n2, S.spined, s);
     }
-    if (st == A2C_OK) {
-        const hipError_t e = hipStreamSynchronize(s);
-        if (e != hipSuccess) st = hip_fail(e, "hipStreamSynchronize");
+    if (st == A2C_OK && !fwd && p->model == A2C_BACKBONE && p->R > 0) {
+        const std::vector<int64_t> own = whole_chain_starts(p, cap);
+        if (!own.empty()) {
+            S.n_tiles = S.n_own = (int32_t)own.size() - 1;
+            st = upload_starts(own, S.d_own_wstart, s);
+            if (st == A2C_OK) st = new_words(S.d_own_status, S.n_own, s);
+        } else {
+            // (first, end) residue pairs, longest tile first: tiles are
+            // independent, and dispatching the long ones first keeps them out
+            // of the tail of the launch
+            const std::vector<int32_t> tiles = pack_tiles(p->res_off, cap);
+            S.n_tiles = (int32_t)tiles.size() - 1;
+            std::vector<int32_t> order(S.n_tiles);
+            for (int32_t t = 0; t < S.n_tiles; ++t) order[t] = t;
+            std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+                return tiles[a + 1] - tiles[a] > tiles[b + 1] - tiles[b];
+            });
+            std::vector<int32_t> pairs(2 * (size_t)S.n_tiles);
+            for (int32_t t = 0; t < S.n_tiles; ++t) {
+                pairs[2 * t] = tiles[order[t]];
+                pairs[2 * t + 1] = tiles[order[t] + 1];
+            }
+            st = upload((void **)&S.d_tile_res, pairs.data(), pairs.size() * sizeof(int32_t), s);
+        }
     }
+    // the host tables above are read by the copies until here
+    const hipError_t e = hipStreamSynchronize(s);
+    if (st == A2C_OK && e != hipSuccess) st = hip_fail(e, "hipStreamSynchronize");
     if (st != A2C_OK) {
         free_sched(S);
         return st;
@@ -307,18 +269,9 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
 // destroyed: a graph captured before the change still launches with them.
 void retire_sched(a2c_plan *p, Sched &S)
 {
-    for (void *q : {(void *)S.d_tile_res, (void *)S.d_loss_part, (void *)S.d_loss_count,
-                    (void *)S.d_wstart, (void *)S.d_look, (void *)S.d_status,
-                    (void *)S.d_look_fwd, (void *)S.d_status_fwd})
+    for (void *q : sched_tables(S))
         if (q) p->retired.push_back(q);
-    S.d_tile_res = nullptr;
-    S.d_loss_part = nullptr;
-    S.d_loss_count = nullptr;
-    S.d_wstart = nullptr;
-    S.d_look = nullptr;
-    S.d_status = nullptr;
-    S.d_look_fwd = nullptr;
-    S.d_status_fwd = nullptr;
+    forget_tables(S);
 }
 
 // Replace one of the plan's schedules; on failure it stays as it was.  The

@@ -1,7 +1,7 @@
 // Backbone model ("Backbone model" section of the paper) on gfx950.
 //
-// Scan form.  Whole chains are packed into tiles; one workgroup of W waves
-// owns one tile and each lane owns K consecutive residues (3K transforms).
+// Scan form.  The packed batch is cut into windows; one workgroup of W waves
+// owns one window and each lane owns K consecutive residues (3K transforms).
 //   1. lane-serial walk from the identity over its 3K transforms, keeping the
 //      local translation of every atom and the lane aggregate (reset at chain
 //      heads);
@@ -22,6 +22,7 @@
 // and a backward where each thread owns one angle and sums
 // g_k . (M_{i-1} dR_i M_i^-1 r_k) over all downstream atoms.
 #include "scan.h"
+#include "spine.h"
 
 namespace a2c {
 
@@ -358,39 +359,30 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
     lanes_to_run<3 * K>(buf, z, out + 2 * A, 3 * nres, full);
 }
 
-// Backward that recomputes the frames from the angles (no stored state).
-// Tiles of several chunks first run the forward scan alone to record each
-// chunk's carry-in frame, then visit the chunks last to first.
-//   GM = kGradLoad: the upstream gradient is read from g;
-//   GM = kGradMse:  g points at a target t and the upstream gradient is that
-//                   of the squared distance, 2 (r - t), formed in registers
-//                   from the recomputed positions (the fused training step);
-//                   xyz_out (may be NULL) receives the positions, loss_out
-//                   (may be NULL) the batch's sum of |r - t|^2 (from the
-//                   tiles' shares in loss_part, counted in loss_count).
-template <int K, bool MULTI, int LB, int GM>
-__global__ __launch_bounds__(LB) void bb_backward_recompute_kernel(
+// Backward that recomputes the frames from the angles for batches with a chain
+// longer than a chunk.  Calls on one plan may overlap here, so nothing is
+// handed between workgroups: whole-chain tiles, a long chain walked chunk by
+// chunk by one workgroup, which first runs the forward scan alone to record
+// each chunk's carry-in frame and then visits the chunks last to first.
+template <int K, int LB>
+__global__ __launch_bounds__(LB) void bb_backward_chunked_kernel(
     const float *__restrict__ ang, const float *__restrict__ g, float *__restrict__ gang,
-    float *__restrict__ xyz_out, float *__restrict__ loss_out, float *__restrict__ loss_part,
-    uint32_t *__restrict__ loss_count, const int32_t *__restrict__ tile_res,
-    const uint32_t *__restrict__ head_bits, int64_t R, BBParams P0)
+    const int32_t *__restrict__ tile_res, const uint32_t *__restrict__ head_bits, int64_t R,
+    BBParams P0)
 {
     extern __shared__ float stage_mem[];
     __shared__ FwdShared shf[2];
     __shared__ BwdShared shb[2];
     __shared__ float fwd_carry[kMaxChunks][12];
-    __shared__ float loss_tot[GM == kGradMse ? kMaxWaves : 1];
-    float loss = 0.f;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *buf = stage_mem + wave * kWave * Stride<3 * K>::value;
     const int64_t ts = tile_res[2 * blockIdx.x], te = tile_res[2 * blockIdx.x + 1];
     const int64_t A = 3 * R;
-    // MULTI = false: every tile is one chunk (straight-line code)
-    const int nch = MULTI ? chunks_of<K>(ts, te) : 1;
+    const int nch = chunks_of<K>(ts, te);
     if (nch > 1) {
         Aff carry = aff_identity();
         for (int c = 0; c < nch; ++c) {
-            const BBParams P = MULTI ? opaque_params(P0) : P0;
+            const BBParams P = opaque_params(P0);
             if (threadIdx.x == 0) aff_store(fwd_carry[c], carry);
             const Chunk k = chunk_of<K>(ts, te, c);
             const int64_t rbase = k.cs + (int64_t)wave * kWave * K;
@@ -403,13 +395,13 @@ __global__ __launch_bounds__(LB) void bb_backward_recompute_kernel(
             if (active) load_angles<K>(buf, ang, R, rbase, nres, phi, psi, om);
             float x[3 * K], y[3 * K], z[3 * K];
             float px, py, pz;
-            bb_lane_positions<K, MULTI>(phi, psi, om, P, k.nact, shf[c & 1], carry, x, y, z, px, py, pz,
-                                 cnt, hm);
+            bb_lane_positions<K, true>(phi, psi, om, P, k.nact, shf[c & 1], carry, x, y, z, px, py,
+                                       pz, cnt, hm);
         }
     }
     Wrench rcarry = wrench_zero();
     for (int c = nch - 1; c >= 0; --c) {
-        const BBParams P = MULTI ? opaque_params(P0) : P0;
+        const BBParams P = opaque_params(P0);
         const Chunk k = chunk_of<K>(ts, te, c);
         const int64_t rbase = k.cs + (int64_t)wave * kWave * K;
         const bool active = wave < k.nact;
@@ -441,33 +433,288 @@ __global__ __launch_bounds__(LB) void bb_backward_recompute_kernel(
         float x[3 * K], y[3 * K], z[3 * K];
         float px, py, pz;
         // buffers alternate with the pass above: its last chunk used shf[(nch-1) & 1]
-        bb_lane_positions<K, MULTI>(phi, psi, om, P, k.nact, shf[(c + 1) & 1], fcarry, x, y, z, px, py,
-                             pz, cnt, hm);
+        bb_lane_positions<K, true>(phi, psi, om, P, k.nact, shf[(c + 1) & 1], fcarry, x, y, z, px,
+                                   py, pz, cnt, hm);
+        float gr[3][K];
+        bb_lane_adjoint<K, true>(P, k.nact, shb[c & 1], rcarry, x, y, z, gx, gy, gz, px, py, pz, cnt,
+                                 hm, lm, gr);
+        if (active) store_angle_grads<K>(buf, gr, gang, R, rbase, nres);
+    }
+}
+
+// One lane's walk from the identity over its K residues (3K transforms),
+// restarting at chain heads: the local position of every atom, and the lane's
+// aggregate after one polar step (which removes the coherent scale drift of
+// the repeated fixed rotations).  first_head: the first residue that starts a
+// chain (K: none); residues before it need the frame entering the lane.
+// Residues past a window's end are walked too: nothing after them reads the
+// frame.
+template <int K>
+__device__ __forceinline__ Aff bb_walk(const float (&phi)[K], const float (&psi)[K],
+                                       const float (&om)[K], uint32_t hm, const BBParams &P,
+                                       float (&x)[3 * K], float (&y)[3 * K], float (&z)[3 * K],
+                                       int &first_head)
+{
+    Aff m = aff_identity();
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+        ok = ok && sincos_fast_ok(om[j]) && sincos_fast_ok(phi[j]) && sincos_fast_ok(psi[j]);
+    const bool fast = __all(ok);
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        float so, co, sp, cp, ss, cs;
+        if (fast) {
+            sincos_fast(om[j], so, co);
+            sincos_fast(phi[j], sp, cp);
+            sincos_fast(psi[j], ss, cs);
+        } else {
+            sincos_accurate(om[j], so, co);
+            sincos_accurate(phi[j], sp, cp);
+            sincos_accurate(psi[j], ss, cs);
+        }
+        const bool h = (hm >> j) & 1u;
+        if (j == 0) {
+            m = aff_first_transform(P.ct[0], P.st[0], P.d[0], co, so);
+            first_head = h ? 0 : first_head;
+        } else if (__builtin_amdgcn_ballot_w64(h) != 0ull) {
+            const Aff f = aff_first_transform(P.ct[0], P.st[0], P.d[0], co, so);
+            aff_apply_transform(m, P.ct[0], P.st[0], P.d[0], co, so);
+            m = aff_select(h, f, m);
+            first_head = (h && first_head == K) ? j : first_head;
+        } else {
+            aff_apply_transform(m, P.ct[0], P.st[0], P.d[0], co, so);
+        }
+        x[3 * j] = m.t0; y[3 * j] = m.t1; z[3 * j] = m.t2;
+        aff_apply_transform(m, P.ct[1], P.st[1], P.d[1], cp, sp);
+        x[3 * j + 1] = m.t0; y[3 * j + 1] = m.t1; z[3 * j + 1] = m.t2;
+        aff_apply_transform(m, P.ct[2], P.st[2], P.d[2], cs, ss);
+        x[3 * j + 2] = m.t0; y[3 * j + 2] = m.t1; z[3 * j + 2] = m.t2;
+    }
+    aff_orthonormalise(m);
+    return m;
+}
+
+// Wrench of a lane's atoms up to and including its first chain end (bit j of
+// lm: residue j ends a chain); f: a chain ends in the lane.
+template <int K>
+__device__ __forceinline__ Wrench bb_lane_wrench(
+    const float (&x)[3 * K], const float (&y)[3 * K], const float (&z)[3 * K],
+    const float (&gx)[3 * K], const float (&gy)[3 * K], const float (&gz)[3 * K], uint32_t lm,
+    bool &f)
+{
+    Wrench agg = wrench_zero();
+    f = false;
+    if (__builtin_amdgcn_ballot_w64(lm != 0u) == 0ull) {  // no chain ends in the wave
+#pragma unroll
+        for (int i = 0; i < 3 * K; ++i) wrench_add_point(agg, x[i], y[i], z[i], gx[i], gy[i], gz[i]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                const int i = 3 * j + s;
+                if (!f) wrench_add_point(agg, x[i], y[i], z[i], gx[i], gy[i], gz[i]);
+            }
+            if ((lm >> j) & 1u) f = true;
+        }
+    }
+    return agg;
+}
+
+// Angle gradients of a lane, last atom first, from the wrench S of everything
+// after it in its chain: dL/dalpha = u . (S_m - r x S_g) (u from consecutive
+// positions; px, py, pz: the atom before the lane's first), then the atom
+// joins S.  gr[s][j]: slot s (0 omega, 1 phi, 2 psi) of residue j.
+template <int K>
+__device__ __forceinline__ void bb_lane_torques(
+    Wrench S, const float (&x)[3 * K], const float (&y)[3 * K], const float (&z)[3 * K],
+    const float (&gx)[3 * K], const float (&gy)[3 * K], const float (&gz)[3 * K], float px,
+    float py, float pz, uint32_t hm, uint32_t lm, const BBParams &P, float (&gr)[3][K])
+{
+#pragma unroll
+    for (int j = K - 1; j >= 0; --j) {
+        if ((lm >> j) & 1u) S = wrench_zero();
+        const bool head = (hm >> j) & 1u;
+#pragma unroll
+        for (int s = 2; s >= 0; --s) {
+            const int i = 3 * j + s;
+            float qx, qy, qz;  // atom before i
+            if (s > 0) { qx = x[i - 1]; qy = y[i - 1]; qz = z[i - 1]; }
+            else if (head) { qx = 0.f; qy = 0.f; qz = 0.f; }
+            else if (j > 0) { qx = x[i - 1]; qy = y[i - 1]; qz = z[i - 1]; }
+            else { qx = px; qy = py; qz = pz; }
+            const float ux = (x[i] - qx) * P.inv_d[s];
+            const float uy = (y[i] - qy) * P.inv_d[s];
+            const float uz = (z[i] - qz) * P.inv_d[s];
+            gr[s][j] = wrench_torque(S, x[i], y[i], z[i], ux, uy, uz);
+            wrench_add_point(S, x[i], y[i], z[i], gx[i], gy[i], gz[i]);
+        }
+    }
+}
+
+// The three gradient planes of a wave's run (non-temporal stores when nt).
+template <int K>
+__device__ __forceinline__ void bb_store_torques(float *buf, const float (&gr)[3][K],
+                                                 float *__restrict__ gang, int64_t R, int64_t rbase,
+                                                 int nres, bool full, bool nt)
+{
+    if (nt) {
+        lanes_to_run<K, true>(buf, gr[1], gang + rbase, nres, full);          // phi  (slot CA)
+        lanes_to_run<K, true>(buf, gr[2], gang + R + rbase, nres, full);      // psi  (slot C)
+        lanes_to_run<K, true>(buf, gr[0], gang + 2 * R + rbase, nres, full);  // omega (slot N)
+    } else {
+        lanes_to_run<K>(buf, gr[1], gang + rbase, nres, full);
+        lanes_to_run<K>(buf, gr[2], gang + R + rbase, nres, full);
+        lanes_to_run<K>(buf, gr[0], gang + 2 * R + rbase, nres, full);
+    }
+}
+
+// Adjoint that recomputes the frames from the angles, over windows of the
+// packed batch, and the fused training step.  The forward's walk and prefix
+// scan give every atom's position, then the adjoint's reverse scan runs on
+// them, all in registers: 12 + 36 bytes in and 12 out per residue (+ 36 where
+// the fused step writes the positions).
+// Bound by VALU issue (some 2300 instructions per wave of 256 residues at
+// K = 4) with the memory close behind; hence the forward's straight-line walk
+// and constant-offset LDS transposes, against per-residue predicates and
+// per-element index divisions before.  On 6000 chains of 20..1000 residues
+// the adjoint went from 65.4 to 55.5 us at (4, 4) (51.7 at (4, 8)).  The
+// fused step went from 247 to 77.9 us there: its loss shares now travel in
+// tagged words, where every workgroup's fence before its atomic count flushed
+// the L2.  On 48 chains of 1500..6000 residues, one workgroup walking each
+// chain chunk by chunk took 83.7 us at (4, 16) and linked windows take 22.5
+// (15.1 at (2, 8)).
+//   GM = kGradLoad: g is the upstream gradient;
+//   GM = kGradMse:  g is a target t and the upstream gradient 2 (r - t);
+//                   xyz_out (may be NULL) receives the positions, loss_out
+//                   (may be NULL) the batch's sum of |r - t|^2.
+//   LINK = false:   windows of whole chains; none needs another's state.
+//   LINK = true:    fixed windows (the fused step alone, whose calls may not
+//                   overlap).  Window t publishes its spine aggregate, takes
+//                   the frames of the earlier windows its first chain spans,
+//                   then publishes its wrench and adds those of the later
+//                   windows its last chain runs into.  A wrench waits only on
+//                   aggregates, and those on nothing, so a launch progresses
+//                   as long as the device holds the at most kMaxAhead + 1
+//                   workgroups a chain spans at once; for longer chains
+//                   (spined) a spine pass has published the aggregates and
+//                   the windows go last to first.
+template <int K, int LB, int GM, bool LINK>
+__global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
+    const float *__restrict__ ang, const float *__restrict__ g, float *__restrict__ gang,
+    float *__restrict__ xyz_out, float *__restrict__ loss_out,
+    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart,
+    const int32_t *__restrict__ look_first, uint64_t *__restrict__ status_fwd,
+    const int32_t *__restrict__ look_last, uint64_t *__restrict__ status, int64_t R, BBParams P,
+    int32_t spined, int32_t nt)
+{
+    extern __shared__ float stage_mem[];
+    __shared__ FwdShared shf;
+    __shared__ BwdShared shb;
+    __shared__ float fcarry_sh[12];
+    __shared__ float rcarry_sh[6];
+    __shared__ float loss_tot[GM == kGradMse ? kMaxWaves : 1];
+    constexpr int RUN = kWave * K;  // residues per wave
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t t =
+        LINK && spined ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const int64_t ts = wstart[t], te = wstart[t + 1];
+    const int nact = (int)((te - ts + RUN - 1) / RUN);
+    const int64_t rbase = ts + (int64_t)wave * RUN;
+    const int nres = (int)max((int64_t)0, min((int64_t)RUN, te - rbase));
+    const bool active = nres > 0, full = nres == RUN;
+    const int64_t rs = rbase + lane * K;
+    float *buf = stage_mem + wave * kWave * Stride<3 * K>::value;
+    const int64_t A = 3 * R;
+    // own words of the previous launch (the tags) and the look ranges, read
+    // ahead of the inputs so that their latency overlaps
+    uint64_t prev_f = 0, prev_b = 0, prev_l = 0;
+    int64_t first = t, last = t;
+    if (wave == 0) {
+        if constexpr (LINK) {
+            prev_f = lb_load(status_fwd + t * kLbWords);
+            prev_b = lb_load(status + t * kLbWords);
+            first = look_first[t];
+            last = look_last[t];
+        }
+        if (GM == kGradMse && loss_out) prev_l = lb_load(status + t * kLbWords + kLbLossWord);
+    }
+    const uint32_t hm = head_mask<K>(head_bits, rs < te ? rs : te);
+    const uint32_t lm = head_mask<K>(head_bits, rs < te ? rs + 1 : te + 1);
+    float x[3 * K], y[3 * K], z[3 * K], gx[3 * K], gy[3 * K], gz[3 * K];
+    Aff m = aff_identity();
+    int first_head = K;
+    if (active) {
+        float phi[K], psi[K], om[K];
+        float v0[K], v1[K], v2[K], w0[3 * K], w1[3 * K], w2[3 * K];
+        const float *gb = g + 3 * rbase;
+        run_load<K>(ang + rbase, nres, full, v0);
+        run_load<K>(ang + R + rbase, nres, full, v1);
+        run_load<K>(ang + 2 * R + rbase, nres, full, v2);
+        run_load<3 * K>(gb, 3 * nres, full, w0);
+        run_load<3 * K>(gb + A, 3 * nres, full, w1);
+        run_load<3 * K>(gb + 2 * A, 3 * nres, full, w2);
+        run_to_lanes<K>(buf, v0, phi);
+        run_to_lanes<K>(buf, v1, psi);
+        run_to_lanes<K>(buf, v2, om);
+        m = bb_walk<K>(phi, psi, om, hm, P, x, y, z, first_head);
+        run_to_lanes<3 * K>(buf, w0, gx);
+        run_to_lanes<3 * K>(buf, w1, gy);
+        run_to_lanes<3 * K>(buf, w2, gz);
+    }
+    const uint64_t heads = __builtin_amdgcn_ballot_w64(first_head < K);
+    const Aff X = block_prefix_windows<LINK>(m, heads, nact, active, shf, fcarry_sh, status_fwd, t,
+                                             first, prev_f, spined != 0);
+    float px = 0.f, py = 0.f, pz = 0.f;  // the atom before the lane's first
+    float loss = 0.f;
+    Wrench agg = wrench_zero();
+    bool f = false;
+    if (active) {
+        if (!(hm & 1u)) { px = X.t0; py = X.t1; pz = X.t2; }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (j < first_head) {
+#pragma unroll
+                for (int s = 0; s < 3; ++s) {
+                    float ax, ay, az;
+                    aff_point(X, x[3 * j + s], y[3 * j + s], z[3 * j + s], ax, ay, az);
+                    x[3 * j + s] = ax; y[3 * j + s] = ay; z[3 * j + s] = az;
+                }
+            }
+        }
         if (GM == kGradMse) {
             // gx.. hold the target: the loss gradient 2 (r - t) of valid atoms
+            const int left = nres - lane * K;  // the lane's residues inside the window
 #pragma unroll
             for (int i = 0; i < 3 * K; ++i) {
                 const float dx = x[i] - gx[i], dy = y[i] - gy[i], dz = z[i] - gz[i];
-                const bool v = i < 3 * cnt;
+                const bool v = full || i / 3 < left;
                 loss += v ? dx * dx + dy * dy + dz * dz : 0.f;
                 gx[i] = v ? 2.f * dx : 0.f;
                 gy[i] = v ? 2.f * dy : 0.f;
                 gz[i] = v ? 2.f * dz : 0.f;
             }
-            if (xyz_out && active) {
+            if (xyz_out) {
                 float *out = xyz_out + 3 * rbase;
-                stage_store<3 * K>(buf, x, out, 3 * nres);
-                stage_store<3 * K>(buf, y, out + A, 3 * nres);
-                stage_store<3 * K>(buf, z, out + 2 * A, 3 * nres);
+                lanes_to_run<3 * K>(buf, x, out, 3 * nres, full);
+                lanes_to_run<3 * K>(buf, y, out + A, 3 * nres, full);
+                lanes_to_run<3 * K>(buf, z, out + 2 * A, 3 * nres, full);
             }
         }
+        agg = bb_lane_wrench<K>(x, y, z, gx, gy, gz, lm, f);
+    }
+    const uint64_t ends = __builtin_amdgcn_ballot_w64(f);
+    const Wrench S = block_suffix_windows<LINK>(agg, ends, nact, active, shb, rcarry_sh, status, t,
+                                                last, prev_b);
+    if (active) {
         float gr[3][K];
-        bb_lane_adjoint<K, MULTI>(P, k.nact, shb[c & 1], rcarry, x, y, z, gx, gy, gz, px, py, pz, cnt,
-                           hm, lm, gr);
-        if (active) store_angle_grads<K>(buf, gr, gang, R, rbase, nres);
+        bb_lane_torques<K>(S, x, y, z, gx, gy, gz, px, py, pz, hm, lm, P, gr);
+        bb_store_torques<K>(buf, gr, gang, R, rbase, nres, full, nt != 0);
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) loss_commit(loss, loss_part, loss_count, loss_out, loss_tot);
+        if (loss_out) lb_loss_commit(loss, status, t, gridDim.x, prev_l, loss_out, loss_tot);
     }
 }
 
@@ -556,54 +803,13 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     // wrench of the lane's atoms up to and including its first chain end
     Wrench agg = wrench_zero();
     bool f = false;
-    if (active) {
-        if (__builtin_amdgcn_ballot_w64(lm != 0u) == 0ull) {  // no chain ends in the wave
-#pragma unroll
-            for (int i = 0; i < 3 * K; ++i) wrench_add_point(agg, x[i], y[i], z[i], gx[i], gy[i], gz[i]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < K; ++j) {
-#pragma unroll
-                for (int s = 0; s < 3; ++s) {
-                    const int i = 3 * j + s;
-                    if (!f) wrench_add_point(agg, x[i], y[i], z[i], gx[i], gy[i], gz[i]);
-                }
-                if ((lm >> j) & 1u) f = true;
-            }
-        }
-    }
+    if (active) agg = bb_lane_wrench<K>(x, y, z, gx, gy, gz, lm, f);
     const uint64_t ends = __builtin_amdgcn_ballot_w64(f);
-    Wrench S = block_suffix_windows(agg, ends, nact, active, sh, carry_sh, status, t, last, prev);
+    const Wrench S = block_suffix_windows(agg, ends, nact, active, sh, carry_sh, status, t, last, prev);
     if (!active) return;
     float gr[3][K];
-#pragma unroll
-    for (int j = K - 1; j >= 0; --j) {
-        if ((lm >> j) & 1u) S = wrench_zero();
-        const bool head = (hm >> j) & 1u;
-#pragma unroll
-        for (int s = 2; s >= 0; --s) {
-            const int i = 3 * j + s;
-            float qx, qy, qz;  // atom before i
-            if (s > 0) { qx = x[i - 1]; qy = y[i - 1]; qz = z[i - 1]; }
-            else if (head) { qx = 0.f; qy = 0.f; qz = 0.f; }
-            else if (j > 0) { qx = x[i - 1]; qy = y[i - 1]; qz = z[i - 1]; }
-            else { qx = px; qy = py; qz = pz; }
-            const float ux = (x[i] - qx) * P.inv_d[s];
-            const float uy = (y[i] - qy) * P.inv_d[s];
-            const float uz = (z[i] - qz) * P.inv_d[s];
-            gr[s][j] = wrench_torque(S, x[i], y[i], z[i], ux, uy, uz);
-            wrench_add_point(S, x[i], y[i], z[i], gx[i], gy[i], gz[i]);
-        }
-    }
-    if (nt) {
-        lanes_to_run<K, true>(buf, gr[1], gang + rbase, nres, full);          // phi  (slot CA)
-        lanes_to_run<K, true>(buf, gr[2], gang + R + rbase, nres, full);      // psi  (slot C)
-        lanes_to_run<K, true>(buf, gr[0], gang + 2 * R + rbase, nres, full);  // omega (slot N)
-    } else {
-        lanes_to_run<K>(buf, gr[1], gang + rbase, nres, full);
-        lanes_to_run<K>(buf, gr[2], gang + R + rbase, nres, full);
-        lanes_to_run<K>(buf, gr[0], gang + 2 * R + rbase, nres, full);
-    }
+    bb_lane_torques<K>(S, x, y, z, gx, gy, gz, px, py, pz, hm, lm, P, gr);
+    bb_store_torques<K>(buf, gr, gang, R, rbase, nres, full, nt != 0);
 }
 
 // ---------------------------------------------------------------- plain form
@@ -733,31 +939,51 @@ hipError_t fwd_k(const a2c_plan &p, const float *ang, float *xyz, hipStream_t s,
     return quat ? fwd_kq<K, true>(p, ang, xyz, s) : fwd_kq<K, false>(p, ang, xyz, s);
 }
 
-template <int K, bool MULTI, int LB>
-hipError_t bwd_kml(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
-                   float *gang, hipStream_t s)
+template <int K, int LB>
+hipError_t bwd_kl(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
+                  float *gang, hipStream_t s)
 {
-    const dim3 grid(p.bs.n_tiles), block(p.bs.W * kWave);
-    const size_t lds = stage_bytes<K>(p.bs.W);
+    const Sched &S = p.bs;
+    const dim3 block(S.W * kWave);
+    const size_t lds = stage_bytes<K>(S.W);
     if (xyz)
-        hipLaunchKernelGGL((bb_backward_coords_flat_kernel<K, LB>), dim3(p.bs.n_win), block, lds, s,
-                           xyz, g, gang, p.d_head_bits, p.bs.d_wstart, p.bs.d_look, p.bs.d_status,
-                           p.R, p.bb, p.bs.whole_chains ? 0 : 1, p.nt_grad ? 1 : 0);
+        hipLaunchKernelGGL((bb_backward_coords_flat_kernel<K, LB>), dim3(S.n_win), block, lds, s,
+                           xyz, g, gang, p.d_head_bits, S.d_wstart, S.d_look, S.d_status, p.R, p.bb,
+                           S.whole_chains ? 0 : 1, p.nt_grad ? 1 : 0);
+    else if (S.n_own)
+        hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradLoad, false>),
+                           dim3(S.n_own), block, lds, s, ang, g, gang, nullptr, nullptr,
+                           p.d_head_bits, S.d_own_wstart, nullptr, nullptr, nullptr, nullptr, p.R,
+                           p.bb, 0, p.nt_grad ? 1 : 0);
     else
-        hipLaunchKernelGGL((bb_backward_recompute_kernel<K, MULTI, LB, kGradLoad>), grid, block,
-                           lds, s, ang, g, gang, nullptr, nullptr, nullptr, nullptr,
-                           p.bs.d_tile_res, p.d_head_bits, p.R, p.bb);
+        hipLaunchKernelGGL((bb_backward_chunked_kernel<K, LB>), dim3(S.n_tiles), block, lds, s, ang,
+                           g, gang, S.d_tile_res, p.d_head_bits, p.R, p.bb);
     return hipGetLastError();
 }
 
-template <int K, bool MULTI, int LB>
-hipError_t mse_kml(const a2c_plan &p, const float *ang, const float *tgt, float *xyz,
-                   float *loss, float *gang, hipStream_t s)
+template <int K, int LB>
+hipError_t mse_kl(const a2c_plan &p, const float *ang, const float *tgt, float *xyz, float *loss,
+                  float *gang, hipStream_t s)
 {
-    hipLaunchKernelGGL((bb_backward_recompute_kernel<K, MULTI, LB, kGradMse>), dim3(p.bs.n_tiles),
-                       dim3(p.bs.W * kWave), stage_bytes<K>(p.bs.W), s, ang, tgt, gang, xyz, loss,
-                       p.bs.d_loss_part, p.bs.d_loss_count, p.bs.d_tile_res, p.d_head_bits, p.R,
-                       p.bb);
+    const Sched &S = p.bs;
+    const dim3 block(S.W * kWave);
+    const size_t lds = stage_bytes<K>(S.W);
+    // Whole-chain windows wherever every chain fits in one, however they pack:
+    // 6000 chains of 20..1000 residues took 77.9 us on 4057 of them at (4, 4)
+    // and 82.3 us on 2996 linked ones (74.8 and 81.6 us at (4, 8)), 1500 of
+    // them 24.9 and 27.1 us at (4, 8).
+    if (S.n_own)
+        hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradMse, false>), dim3(S.n_own),
+                           block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_own_wstart,
+                           nullptr, nullptr, nullptr, S.d_own_status, p.R, p.bb, 0,
+                           p.nt_grad ? 1 : 0);
+    else {
+        if (S.spined) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
+        hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradMse, true>), dim3(S.n_win),
+                           block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_wstart,
+                           S.d_look_fwd, S.d_status_fwd, S.d_look, S.d_status, p.R, p.bb,
+                           S.spined ? 1 : 0, p.nt_grad ? 1 : 0);
+    }
     return hipGetLastError();
 }
 
@@ -765,24 +991,16 @@ template <int K>
 hipError_t mse_k(const a2c_plan &p, const float *ang, const float *tgt, float *xyz,
                  float *loss, float *gang, hipStream_t s)
 {
-    const bool small = p.bs.W * kWave <= kLbSmall;
-    if (p.bs.multi_chunk)
-        return small ? mse_kml<K, true, kLbSmall>(p, ang, tgt, xyz, loss, gang, s)
-                     : mse_kml<K, true, kLbLarge>(p, ang, tgt, xyz, loss, gang, s);
-    return small ? mse_kml<K, false, kLbSmall>(p, ang, tgt, xyz, loss, gang, s)
-                 : mse_kml<K, false, kLbLarge>(p, ang, tgt, xyz, loss, gang, s);
+    return p.bs.W * kWave <= kLbSmall ? mse_kl<K, kLbSmall>(p, ang, tgt, xyz, loss, gang, s)
+                                      : mse_kl<K, kLbLarge>(p, ang, tgt, xyz, loss, gang, s);
 }
 
 template <int K>
 hipError_t bwd_k(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
                  float *gang, hipStream_t s)
 {
-    const bool small = p.bs.W * kWave <= kLbSmall;
-    if (p.bs.multi_chunk)
-        return small ? bwd_kml<K, true, kLbSmall>(p, ang, xyz, g, gang, s)
-                     : bwd_kml<K, true, kLbLarge>(p, ang, xyz, g, gang, s);
-    return small ? bwd_kml<K, false, kLbSmall>(p, ang, xyz, g, gang, s)
-                 : bwd_kml<K, false, kLbLarge>(p, ang, xyz, g, gang, s);
+    return p.bs.W * kWave <= kLbSmall ? bwd_kl<K, kLbSmall>(p, ang, xyz, g, gang, s)
+                                      : bwd_kl<K, kLbLarge>(p, ang, xyz, g, gang, s);
 }
 
 }  // namespace

@@ -21,6 +21,7 @@
 #include <string>
 
 #include "scan.h"
+#include "spine.h"
 
 namespace a2c {
 
@@ -395,87 +396,6 @@ __device__ __forceinline__ void frame_wrench_xyz(const FATable &tab, const FATyp
     }
 }
 
-struct ResidueIn {
-    float co, so, cp, sp, cs, ss;  // cos/sin of omega, phi, psi
-};
-
-// Spine angles (phi, psi, omega) of a lane's K residues, 0 past the chunk.
-template <int K>
-struct SpineAngles {
-    float phi[K], psi[K], om[K];
-};
-
-template <int K>
-__device__ __forceinline__ SpineAngles<K> load_spine_angles(const float *__restrict__ ang,
-                                                            int64_t R, int64_t rs, int cnt)
-{
-    SpineAngles<K> a;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        a.phi[j] = j < cnt ? ang[rs + j] : 0.f;
-        a.psi[j] = j < cnt ? ang[R + rs + j] : 0.f;
-        a.om[j] = j < cnt ? ang[2 * R + rs + j] : 0.f;
-    }
-    return a;
-}
-
-// Lane-serial spine aggregate of K residues (reset at chain heads), with one
-// polar step; keeps the spine cos/sin per residue for the re-walk.
-template <int K>
-__device__ __forceinline__ Aff fa_lane_aggregate(const SpineAngles<K> &a, int cnt, uint32_t hm,
-                                                 const BBParams &P, ResidueIn (&in)[K],
-                                                 int &first_head)
-{
-    Aff m = aff_identity();
-    first_head = K;
-    const float(&phi)[K] = a.phi;
-    const float(&psi)[K] = a.psi;
-    const float(&om)[K] = a.om;
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < K; ++j)
-        ok = ok && sincos_fast_ok(om[j]) && sincos_fast_ok(phi[j]) && sincos_fast_ok(psi[j]);
-    if (__all(ok)) {
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            sincos_fast(phi[j], in[j].sp, in[j].cp);
-            sincos_fast(psi[j], in[j].ss, in[j].cs);
-            sincos_fast(om[j], in[j].so, in[j].co);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            sincos_accurate(phi[j], in[j].sp, in[j].cp);
-            sincos_accurate(psi[j], in[j].ss, in[j].cs);
-            sincos_accurate(om[j], in[j].so, in[j].co);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        if (j < cnt) {
-            if ((hm >> j) & 1u) {
-                m = aff_identity();
-                if (first_head == K) first_head = j;
-            }
-            aff_apply_transform(m, P.ct[0], P.st[0], P.d[0], in[j].co, in[j].so);
-            aff_apply_transform(m, P.ct[1], P.st[1], P.d[1], in[j].cp, in[j].sp);
-            aff_apply_transform(m, P.ct[2], P.st[2], P.d[2], in[j].cs, in[j].ss);
-        }
-    }
-    aff_orthonormalise(m);
-    return m;
-}
-
-template <int K>
-__device__ __forceinline__ Aff fa_lane_aggregate(const float *__restrict__ ang, int64_t R,
-                                                 int64_t rs, int cnt, uint32_t hm,
-                                                 const BBParams &P, ResidueIn (&in)[K],
-                                                 int &first_head)
-{
-    return fa_lane_aggregate<K>(load_spine_angles<K>(ang, R, rs, cnt), cnt, hm, P, in,
-                                first_head);
-}
-
 __device__ __forceinline__ void side_step(Aff &sf, const FAType &ft, int f, float chi)
 {
     float c = 1.f, s = 0.f;
@@ -732,61 +652,6 @@ __device__ __forceinline__ void fa_store_grads(float *__restrict__ gang, int64_t
     S_out = S;
 }
 
-// Spine aggregates for the recomputing full-atom adjoints.  Those take fixed
-// windows last to first (for the wrench look-back), so they cannot wait on
-// earlier windows' frames themselves: this spine-only pass over the same
-// windows publishes each window's aggregate (the product of its spine
-// transforms from its last chain head, or its start, to its end) as tagged
-// words and waits on nothing; the adjoint then composes the aggregates of
-// the windows its first chain spans, all complete by then (lb_carry_in).
-template <int K, int LB>
-__global__ __launch_bounds__(LB) void fa_spine_aggregate_kernel(
-    const float *__restrict__ ang, const uint32_t *__restrict__ head_bits,
-    const int32_t *__restrict__ wstart, uint64_t *__restrict__ status, int64_t R, BBParams P)
-{
-    __shared__ FwdShared sh;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t = blockIdx.x;
-    FAChunk k;
-    k.cs = wstart[t];
-    k.ce = wstart[t + 1];
-    k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
-    const bool active = wave < k.nact;
-    const int64_t rs = k.cs + (int64_t)threadIdx.x * K;
-    const int cnt = (int)max((int64_t)0, min((int64_t)K, k.ce - rs));
-    const uint32_t hm = lane_head_mask<K>(head_bits, rs, k.ce, cnt);
-    uint64_t prev = 0;
-    if (wave == 0) prev = lb_load(status + t * kLbWords);
-    ResidueIn in[K];
-    int first_head = K;
-    Aff m = aff_identity();
-    if (active) m = fa_lane_aggregate<K>(load_spine_angles<K>(ang, R, rs, cnt), cnt, hm, P, in,
-                                         first_head);
-    const uint64_t heads = __builtin_amdgcn_ballot_w64(first_head < K);
-    if (active) {
-        aff_wave_scan<false>(m, heads, kWave, lane);
-        if (lane == kWave - 1) {
-            aff_store(sh.tot[wave], m);
-            sh.tot_flag[wave] = heads != 0ull ? 1 : 0;
-        }
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    Aff tw = aff_identity();
-    bool tf = false;
-    if (lane < k.nact) {
-        tw = aff_load(sh.tot[lane]);
-        tf = sh.tot_flag[lane] != 0;
-    }
-    const uint64_t th = __builtin_amdgcn_ballot_w64(tf);
-    aff_wave_scan<true>(tw, th, k.nact, lane);
-    if (lane == k.nact - 1) aff_store(sh.pre[0], tw);
-    wave_lds_sync();
-    const uint32_t tag = (uint32_t)(__builtin_amdgcn_readfirstlane((uint32_t)(prev >> 32))) + 1u;
-    if (lane < kLbWords) lb_store(status + t * kLbWords + lane, tag, sh.pre[0][lane]);
-}
-
 // Backward over windows of the packed batch, last window first (rev:
 // reverse_window, so that window t runs on the XCD where the spine pass's
 // window t read the same angles; in order where the windows hold whole
@@ -795,7 +660,7 @@ __global__ __launch_bounds__(LB) void fa_spine_aggregate_kernel(
 // reverse scan over residues (window look-back for the wrench of later
 // windows), and u . (S_m - o x S_g) gives phi, psi, omega.
 // RECOMPUTE: frames from the angles, the frame entering the window composed
-// from the aggregates fa_spine_aggregate_kernel published (status_fwd,
+// from the aggregates spine_aggregate_kernel published (status_fwd,
 // windows look_fwd[t] .. t - 1); otherwise positions and axes from the
 // forward's coordinates.
 // GM = kGradMse (with RECOMPUTE): g points at a target t and the upstream
@@ -1039,32 +904,13 @@ hipError_t fa_fwd_k(const a2c_plan &p, const float *ang, float *xyz, hipStream_t
     return p.fs.fa_unstaged ? fa_fwd_ks<K, false>(p, ang, xyz, s) : fa_fwd_ks<K, true>(p, ang, xyz, s);
 }
 
-// The spine pass covers the adjoint's windows (C = 64 W K residues) with
-// more residues per lane where C allows (8 or 4 per lane, fewer waves): it
-// only walks the spine, so the per-residue walk is cheap and the scan is
-// shared by more residues.
-template <int K>
-void fa_spine_launch(const a2c_plan &p, const float *ang, hipStream_t s)
-{
-    const int64_t C = (int64_t)kWave * K * p.bs.W;
-    const dim3 grid(p.bs.n_win);
-    if (C % (kWave * 8) == 0)
-        hipLaunchKernelGGL((fa_spine_aggregate_kernel<8, 1024>), grid, dim3(C / 8), 0, s, ang,
-                           p.d_head_bits, p.bs.d_wstart, p.bs.d_status_fwd, p.R, p.bb);
-    else if (C % (kWave * 4) == 0)
-        hipLaunchKernelGGL((fa_spine_aggregate_kernel<4, 1024>), grid, dim3(C / 4), 0, s, ang,
-                           p.d_head_bits, p.bs.d_wstart, p.bs.d_status_fwd, p.R, p.bb);
-    else
-        hipLaunchKernelGGL((fa_spine_aggregate_kernel<K, 1024>), grid, dim3(C / K), 0, s, ang,
-                           p.d_head_bits, p.bs.d_wstart, p.bs.d_status_fwd, p.R, p.bb);
-}
-
 template <int K, bool RECOMPUTE, int LB, int GM, bool STG>
 void fa_bwd_launch(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
                    float *gang, hipStream_t s, float *xyz_out, float *loss_out)
 {
     // whole-chain windows start at a chain head: none needs the spine pass
-    if (RECOMPUTE && !p.bs.whole_chains) fa_spine_launch<K>(p, ang, s);
+    if (RECOMPUTE && !p.bs.whole_chains)
+        launch_spine_pass(ang, p.d_head_bits, p.bs, p.R, p.bb, s);
     const size_t lds =
         STG ? (size_t)p.bs.W * (RECOMPUTE ? 3 : 6) * p.bs.fa_stage_atoms * sizeof(float) : 0;
     hipLaunchKernelGGL((fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, STG>), dim3(p.bs.n_win),

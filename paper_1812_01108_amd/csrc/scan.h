@@ -156,37 +156,6 @@ __device__ __forceinline__ float block_sum(float v, float (&wave_tot)[kMaxWaves]
     return t;
 }
 
-// The fused step's loss: every tile stores its share (the block sum of v),
-// counts itself done with one atomic, and the tile that counts last sums all
-// shares in tile order (each thread a fixed strided subset, then block_sum)
-// into *out and sets the count back to 0 for the next launch.  No tile waits
-// for another; the total does not depend on which tile finishes last.
-// Every thread of the block calls this (block-uniform arguments).
-__device__ __forceinline__ void loss_commit(float v, float *__restrict__ parts,
-                                            uint32_t *__restrict__ count, float *__restrict__ out,
-                                            float (&wave_tot)[kMaxWaves])
-{
-    __shared__ int last;
-    const float t = block_sum(v, wave_tot);
-    if (threadIdx.x == 0) {
-        parts[blockIdx.x] = t;
-        __threadfence();   // the share is visible before the count says so
-        last = atomicAdd(count, 1u) == gridDim.x - 1 ? 1 : 0;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    float s = 0.f;
-    for (unsigned i = threadIdx.x; i < gridDim.x; i += blockDim.x)
-        s += __hip_atomic_load(parts + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();   // wave_tot is reused
-    const float total = block_sum(s, wave_tot);
-    if (threadIdx.x == 0) {
-        *out = total;
-        __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
 __device__ __forceinline__ float uni(float v)
 {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
@@ -800,10 +769,15 @@ __device__ __forceinline__ Aff lb_carry_in(const uint64_t *status, int64_t first
 // wave's lanes holding a chain head; prev, first (read by wave 0 early): the
 // window's own first tagged word and the first window of its look-back.
 // Every thread of the block calls it; inactive waves get the identity.
+// LINK = false (windows of whole chains): no window needs another's frame, so
+// nothing is published or read (status, first, prev and carry_sh unused).
+// published: an earlier launch has published the aggregates (the spine pass).
+template <bool LINK = true>
 __device__ __forceinline__ Aff block_prefix_windows(Aff m, uint64_t heads, int nact, bool active,
                                                     FwdShared &sh, float (&carry_sh)[12],
                                                     uint64_t *__restrict__ status, int64_t t,
-                                                    int64_t first, uint64_t prev)
+                                                    int64_t first, uint64_t prev,
+                                                    bool published = false)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -828,20 +802,31 @@ __device__ __forceinline__ Aff block_prefix_windows(Aff m, uint64_t heads, int n
             aff_store(sh.pre[lane], tw);
             sh.pre_flag[lane] = (th & lanes_upto(lane)) != 0ull ? 1 : 0;
         }
-        wave_lds_sync();
-        // publish this window's aggregate, then read the earlier windows' ones
-        const uint32_t tag = (uint32_t)(__builtin_amdgcn_readfirstlane((uint32_t)(prev >> 32))) + 1u;
-        if (lane < kLbWords) lb_store(status + t * kLbWords + lane, tag, sh.pre[nact - 1][lane]);
-        const int64_t f = (int64_t)__builtin_amdgcn_readfirstlane((int)first);
-        const Aff carry = lb_carry_in(status, f, t, tag);
-        if (lane == 0) aff_store(carry_sh, carry);
+        if constexpr (LINK) {
+            wave_lds_sync();
+            // publish this window's aggregate, then read the earlier windows' ones
+            const uint32_t tag =
+                (uint32_t)(__builtin_amdgcn_readfirstlane((uint32_t)(prev >> 32))) +
+                (published ? 0u : 1u);
+            if (!published && lane < kLbWords)
+                lb_store(status + t * kLbWords + lane, tag, sh.pre[nact - 1][lane]);
+            const int64_t f = (int64_t)__builtin_amdgcn_readfirstlane((int)first);
+            const Aff carry = lb_carry_in(status, f, t, tag);
+            if (lane == 0) aff_store(carry_sh, carry);
+        }
     }
     __syncthreads();
     if (!active) return aff_identity();
     // frame entering the wave, then entering each lane
-    const Aff carry = aff_load(carry_sh);
-    Aff cw = carry;
-    if (wave > 0) cw = aff_seg_after(carry, aff_load(sh.pre[wave - 1]), sh.pre_flag[wave - 1] != 0);
+    Aff cw = aff_identity();
+    if constexpr (LINK) {
+        const Aff carry = aff_load(carry_sh);
+        cw = carry;
+        if (wave > 0)
+            cw = aff_seg_after(carry, aff_load(sh.pre[wave - 1]), sh.pre_flag[wave - 1] != 0);
+    } else if (wave > 0) {
+        cw = aff_load(sh.pre[wave - 1]);  // a chain starts at the window's first residue
+    }
     Aff e = aff_dpp_z<kDppWaveShr1>(m);
     if (lane == 0) e = aff_identity();
     const bool fe = (heads & lanes_below(lane)) != 0ull;
@@ -915,6 +900,8 @@ __device__ __forceinline__ Wrench lb_carry_after(const uint64_t *status, int64_t
 // windows its last chain runs into (lb_carry_after).  prev, last (read by
 // wave 0 early): the window's own first tagged word and the last window of
 // its look-ahead.  Every thread of the block calls it; inactive waves get 0.
+// LINK = false (windows of whole chains): nothing is published or read.
+template <bool LINK = true>
 __device__ __forceinline__ Wrench block_suffix_windows(Wrench agg, uint64_t ends, int nact,
                                                        bool active, BwdShared &sh,
                                                        float (&carry_sh)[6],
@@ -944,22 +931,26 @@ __device__ __forceinline__ Wrench block_suffix_windows(Wrench agg, uint64_t ends
             wrench_store(sh.suf[lane], tw);
             sh.suf_flag[lane] = (th & (~0ull << lane)) != 0ull ? 1 : 0;
         }
-        wave_lds_sync();
-        // publish this window's wrench, then read the later windows' ones
-        const uint32_t tag = (uint32_t)(__builtin_amdgcn_readfirstlane((uint32_t)(prev >> 32))) + 1u;
-        if (lane < kLbWrenchWords) lb_store(status + t * kLbWords + lane, tag, sh.suf[0][lane]);
-        const int64_t l = (int64_t)__builtin_amdgcn_readfirstlane((int)last);
-        const Wrench carry = lb_carry_after(status, t, l, tag);
-        if (lane == 0) wrench_store(carry_sh, carry);
+        if constexpr (LINK) {
+            wave_lds_sync();
+            // publish this window's wrench, then read the later windows' ones
+            const uint32_t tag =
+                (uint32_t)(__builtin_amdgcn_readfirstlane((uint32_t)(prev >> 32))) + 1u;
+            if (lane < kLbWrenchWords) lb_store(status + t * kLbWords + lane, tag, sh.suf[0][lane]);
+            const int64_t l = (int64_t)__builtin_amdgcn_readfirstlane((int)last);
+            const Wrench carry = lb_carry_after(status, t, l, tag);
+            if (lane == 0) wrench_store(carry_sh, carry);
+        }
     }
     __syncthreads();
     if (!active) return wrench_zero();
     // everything after the wave up to the end of its last chain
-    const Wrench carry = wrench_load(carry_sh);
-    Wrench cw = carry;
+    Wrench cw = wrench_zero();
+    if constexpr (LINK) cw = wrench_load(carry_sh);
     if (wave + 1 < nact) {
+        const Wrench carry = cw;
         cw = wrench_load(sh.suf[wave + 1]);
-        if (sh.suf_flag[wave + 1] == 0) wrench_add(cw, carry);
+        if (LINK && sh.suf_flag[wave + 1] == 0) wrench_add(cw, carry);
     }
     // everything after lane l inside the wave: the inclusive value of lane
     // l + 1, complete when a chain ends in lanes after l

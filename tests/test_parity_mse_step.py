@@ -125,6 +125,35 @@ def test_separate_adjoint_schedule(model):
     _run(plan, model, off, seq, ang, t, f"{model} fwd (1,4) adj (2,8)")
 
 
+@pytest.mark.parametrize("model,K,W,lengths", [
+    # fixed windows of 64: the long chain touches 32 windows (the most a
+    # window waits ahead within), then 33 (a spine pass goes first)
+    ("backbone", 1, 1, [5, 64 * 31 - 4, 3]),
+    ("backbone", 1, 1, [63, 64 * 31 + 2, 70]),
+    ("fullatom", 1, 1, [5, 64 * 31 - 4, 3]),
+    ("fullatom", 1, 1, [63, 64 * 31 + 2, 70]),
+    # linked windows of several waves, chains ending on and around their edges
+    ("backbone", 2, 2, [256, 255, 257, 1500, 1, 0, 511]),
+    ("backbone", 4, 3, [768, 2303, 1, 769, 40]),
+    ("fullatom", 2, 2, [256, 255, 257, 1500, 1, 0, 511]),
+    # windows of whole chains that pack badly
+    ("backbone", 1, 2, [65, 64, 128, 1, 127, 2] * 60),
+])
+def test_windows_across_chains(model, K, W, lengths):
+    a2c = _a2c()
+    off, seq, ang, t = _case(model, lengths, 331 + K + W)
+    plan = (a2c.Plan("backbone", offsets=off) if model == "backbone"
+            else a2c.Plan("fullatom", offsets=off, seq=seq))
+    plan.set_schedule(K, W)
+    # coordinates: the bound of 1e-3 A at 1000 residues grows with the
+    # chain's length to the power 3/2 (rounding errors of the frames add up as
+    # a random walk, and turn ever longer arms)
+    tol = COORD_TOL_A * max(1.0, (max(lengths) / 1000.0) ** 1.5)
+    for _ in range(3):   # the tags move on from call to call
+        _run(plan, model, off, seq, ang, t, f"{model} K={K} W={W} {len(lengths)} chains",
+             coord_tol=tol)
+
+
 def test_training_workload_full_size():
     """The ragged 512-chain full-atom workload (chains to 2000 residues)."""
     a2c = _a2c()
