@@ -219,12 +219,11 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  *     device memory before it reads any (window look-back), and waits only
  *     on workgroups started before it or at most 7 places after it (the
  *     adjoints take fixed windows last to first, in each class of workgroup
- *     index mod 8 separately, and whole-chain ones in order; the full-atom
- *     ones that recompute the frames first run a spine-only pass over the
- *     same windows, which waits on nothing; the backbone fused step takes
- *     fixed windows in order and also waits on those its last chain runs
- *     into, unless a chain spans more than 32 windows, when it runs that
- *     spine pass as well); a launch therefore progresses whenever the device
+ *     index mod 8 separately, and whole-chain ones in order; those that
+ *     recompute the frames take them in order and also wait on the windows
+ *     their last chain runs into, unless a chain spans more than 32 windows:
+ *     then a spine-only pass over the same windows, which waits on nothing,
+ *     goes first); a launch therefore progresses whenever the device
  *     holds 32 of its workgroups at once.  Consequently two such calls on one
  *     plan must not run at the same time (on different streams).
  *   - The backbone adjoint that recomputes the frames (a2c_backward without

@@ -63,8 +63,24 @@ struct FAType {
 
 struct FATable {
     FAType t[A2C_NUM_RESIDUE_TYPES];
-    int32_t max_count[7];           // max atoms per frame over the types
-    int32_t max_side;
+};
+
+// The same as the kernels read it, 272 bytes per type: an odd number of
+// 16-byte pieces, so that lanes reading the same field of different types
+// spread over the LDS banks.
+struct alignas(16) FADevType {
+    float4 fr[4];                   // side frame f: cos, sin theta, d, 1 where it has a chi
+    float4 inv_d;                   // 1 / d of the side frames
+    float pre_c, pre_s;             // fixed rotation of side frame 0
+    uint32_t origin;                // byte f: residue slot of side frame f's origin atom
+    uint32_t counts;                // nibble i < 7: extra atoms at position i of the walk (N,
+                                    // CA, side frames 0..3, C); nibble 7: side frames
+    FAAtom ex[A2C_MAX_RESIDUE_ATOMS - 3];  // extra atoms (not at a frame's origin), walk order
+};
+static_assert(sizeof(FADevType) == 272, "odd number of 16-byte pieces");
+
+struct FADevTable {
+    FADevType t[A2C_NUM_RESIDUE_TYPES];
 };
 
 // Windows ahead of its own that a window of a recomputing adjoint may wait
@@ -138,9 +154,10 @@ struct a2c_plan {
     int32_t *d_res_off = nullptr;        // chain residue offsets (plain form)
     int32_t *d_res_atom_off = nullptr;   // R + 1 (full-atom)
     uint8_t *d_seq = nullptr;            // R (full-atom)
-    a2c::FATable *d_fa = nullptr;        // full-atom constants
+    a2c::FADevTable *d_fa = nullptr;     // full-atom constants
     a2c::BBParams bb{};
     a2c::FATable fa_host{};
+    a2c::FADevTable fa_dev{};
     // LRMSD segments (the sums): runs of at most kLrSegAtoms atoms of one
     // chain; pieces (the gradient): runs of at most kLrPieceAtoms
     int32_t lr_n_seg = 0;

@@ -572,7 +572,7 @@ a2c_status a2c_plan_create(a2c_plan **out, int32_t model_id, int32_t n_chains,
         st = upload((void **)&p->d_res_atom_off, p->res_atom_off.data(),
                     p->res_atom_off.size() * sizeof(int32_t), s);
         if (st == A2C_OK) st = upload((void **)&p->d_seq, p->seq.data(), p->seq.size(), s);
-        if (st == A2C_OK) st = upload((void **)&p->d_fa, &p->fa_host, sizeof(FATable), s);
+        if (st == A2C_OK) st = upload((void **)&p->d_fa, &p->fa_dev, sizeof(FADevTable), s);
         if (st == A2C_OK) {
             int8_t chi[A2C_NUM_RESIDUE_TYPES][4][4];
             build_chi_slots(p->fa_host, chi);

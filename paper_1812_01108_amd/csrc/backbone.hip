@@ -34,7 +34,7 @@ __device__ __forceinline__ int slot_plane(int s) { return s == 0 ? 2 : (s == 1 ?
 // Absolute atom positions of one lane's residues (x[3j+s], ...), given its
 // angles, and the position of the atom just before the lane (the origin when
 // the lane starts a chain).  Every thread of the block calls this.
-template <int K, bool MULTI>
+template <int K>
 __device__ __forceinline__ void bb_lane_positions(
     const float (&phi)[K], const float (&psi)[K], const float (&om)[K],
     const BBParams &P, int nact, FwdShared &sh, Aff &carry, float (&x)[3 * K],
@@ -94,7 +94,7 @@ __device__ __forceinline__ void bb_lane_positions(
         // lane aggregate (every 3K transforms) removes that drift
         aff_orthonormalise(m);
     }
-    const Aff X = block_exclusive_prefix<MULTI>(m, first_head < K, nact, sh, carry);
+    const Aff X = block_exclusive_prefix(m, first_head < K, nact, sh, carry);
     px = py = pz = 0.f;
     if (!wave_active) return;
     // previous atom position (origin when the lane's first residue is a head)
@@ -116,7 +116,7 @@ __device__ __forceinline__ void bb_lane_positions(
 // omega, 1 phi, 2 psi) from absolute positions, upstream gradients and the
 // atom before the lane: a reverse segmented scan of wrenches over the tile.
 // Every thread of the block calls this.
-template <int K, bool MULTI>
+template <int K>
 __device__ __forceinline__ void bb_lane_adjoint(
     const BBParams &P, int nact, BwdShared &sh, Wrench &carry,
     const float (&x)[3 * K], const float (&y)[3 * K], const float (&z)[3 * K],
@@ -143,7 +143,7 @@ __device__ __forceinline__ void bb_lane_adjoint(
             }
         }
     }
-    Wrench S = block_exclusive_suffix<MULTI>(agg, f, nact, sh, carry);
+    Wrench S = block_exclusive_suffix(agg, f, nact, sh, carry);
     if (!wave_active) return;
 #pragma unroll
     for (int j = K - 1; j >= 0; --j) {
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(LB) void bb_backward_chunked_kernel(
             if (active) load_angles<K>(buf, ang, R, rbase, nres, phi, psi, om);
             float x[3 * K], y[3 * K], z[3 * K];
             float px, py, pz;
-            bb_lane_positions<K, true>(phi, psi, om, P, k.nact, shf[c & 1], carry, x, y, z, px, py,
+            bb_lane_positions<K>(phi, psi, om, P, k.nact, shf[c & 1], carry, x, y, z, px, py,
                                        pz, cnt, hm);
         }
     }
@@ -433,10 +433,10 @@ __global__ __launch_bounds__(LB) void bb_backward_chunked_kernel(
         float x[3 * K], y[3 * K], z[3 * K];
         float px, py, pz;
         // buffers alternate with the pass above: its last chunk used shf[(nch-1) & 1]
-        bb_lane_positions<K, true>(phi, psi, om, P, k.nact, shf[(c + 1) & 1], fcarry, x, y, z, px,
+        bb_lane_positions<K>(phi, psi, om, P, k.nact, shf[(c + 1) & 1], fcarry, x, y, z, px,
                                    py, pz, cnt, hm);
         float gr[3][K];
-        bb_lane_adjoint<K, true>(P, k.nact, shb[c & 1], rcarry, x, y, z, gx, gy, gz, px, py, pz, cnt,
+        bb_lane_adjoint<K>(P, k.nact, shb[c & 1], rcarry, x, y, z, gx, gy, gz, px, py, pz, cnt,
                                  hm, lm, gr);
         if (active) store_angle_grads<K>(buf, gr, gang, R, rbase, nres);
     }

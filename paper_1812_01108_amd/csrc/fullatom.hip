@@ -5,9 +5,10 @@
 // chain off the CA frame through a fixed rotation R' and a chain of up to
 // four side frames M_f = M_parent R(chi_f, theta_f, d_f), and places every
 // atom as r = M_frame r°.  One lane owns K consecutive residues:
-//   forward : lane aggregate of the 3K spine transforms -> block prefix scan
-//             -> the lane re-walks its residues from its prefix frame,
-//             building spine and side frames and emitting atoms;
+//   forward : lane aggregate of the 3K spine transforms -> window prefix scan
+//             on a quarter of the waves -> the lane re-walks its residues from
+//             its prefix frame, building spine and side frames and emitting
+//             atoms;
 //   adjoint : the same walk yields frame origins and axes; per residue the
 //             side-frame subtree wrenches give the chi gradients (side frames
 //             form a chain, so a suffix over frames), the residue's N, CA
@@ -16,6 +17,7 @@
 //             omega -- Eq. FAMBackward summed over subtrees in O(N).
 // In the adjoint the atom positions either come from the forward's output
 // (axes from bond vectors) or are recomputed from the angles.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -150,11 +152,38 @@ a2c_status convert_residue_table(const a2c_residue_table *table, const double sp
                         ++n;
                     }
             ft.fcount[k] = n - ft.fbegin[k];
-            T.max_count[k] = std::max(T.max_count[k], ft.fcount[k]);
         }
-        T.max_side = std::max(T.max_side, ft.n_side);
     }
     return A2C_OK;
+}
+
+// The kernels' form of the converted table: per type the side frames'
+// constants, the slots of their origin atoms, and the other ("extra") atoms
+// in the order the walk meets them (N, CA, the side frames in order, C).
+static void build_device_table(const FATable &T, FADevTable &D)
+{
+    static const int walk[7] = {0, 1, 3, 4, 5, 6, 2};  // frame at each position of the walk
+    std::memset(&D, 0, sizeof(D));
+    for (int t = 0; t < A2C_NUM_RESIDUE_TYPES; ++t) {
+        const FAType &ft = T.t[t];
+        FADevType &d = D.t[t];
+        d.pre_c = ft.pre_c;
+        d.pre_s = ft.pre_s;
+        d.counts = (uint32_t)ft.n_side << 28;
+        float *inv = &d.inv_d.x;
+        for (int f = 0; f < ft.n_side; ++f) {
+            d.fr[f] = float4{ft.ct[f], ft.st[f], ft.d[f], ft.side_chi[f] ? 1.f : 0.f};
+            inv[f] = ft.inv_d[f];
+            d.origin |= (uint32_t)ft.origin_slot[3 + f] << (8 * f);
+        }
+        int n = 0;
+        for (int i = 0; i < 7; ++i) {
+            const int k = walk[i];
+            // a frame's list starts with its origin atom
+            for (int a = 1; a < ft.fcount[k]; ++a) d.ex[n++] = ft.atom[ft.fbegin[k] + a];
+            if (ft.fcount[k] > 1) d.counts |= (uint32_t)(ft.fcount[k] - 1) << (4 * i);
+        }
+    }
 }
 
 a2c_status build_fullatom_tables(a2c_plan *p, const a2c_residue_table *table)
@@ -163,6 +192,7 @@ a2c_status build_fullatom_tables(a2c_plan *p, const a2c_residue_table *table)
     const double spine_d[3] = {p->bb.d[0], p->bb.d[1], p->bb.d[2]};
     const a2c_status st = convert_residue_table(table, spine_d, T);
     if (st != A2C_OK) return st;
+    build_device_table(T, p->fa_dev);
     // atom offsets
     p->res_atom_off.assign((size_t)p->R + 1, 0);
     for (int64_t r = 0; r < p->R; ++r)
@@ -207,23 +237,39 @@ namespace a2c {
 
 namespace {
 
-// The constant table into LDS: 16-byte pieces, every load of a thread issued
-// before its first store (one memory latency also for a one-wave group).
-__device__ __forceinline__ void load_table(FATable &tab, const FATable *__restrict__ g)
+// The constant table into LDS in 16-byte pieces: loads first (issued ahead of
+// the window's inputs, so that the copy waits for nothing else), then the
+// stores, which a barrier of the caller closes.  Rounds past the end are
+// skipped as a whole; inside the last one indices are clamped (those threads
+// rewrite the last piece with the value it already gets).
+constexpr int kTabPieces = sizeof(FADevTable) / 16;
+constexpr int kTabRounds = (kTabPieces + kWave - 1) / kWave;
+
+typedef int Piece __attribute__((ext_vector_type(4)));
+
+struct TableCopy {
+    Piece v[kTabRounds];
+};
+
+__device__ __forceinline__ TableCopy table_load(const FADevTable *__restrict__ g)
 {
-    static_assert(sizeof(FATable) % 16 == 0, "FATable copies in 16-byte pieces");
-    constexpr int n = sizeof(FATable) / 16;
-    constexpr int per = (n + kWave - 1) / kWave;
-    const int4 *src = reinterpret_cast<const int4 *>(g);
-    int4 *dst = reinterpret_cast<int4 *>(&tab);
-    int4 v[per];
-    // indices past the end are clamped: those threads rewrite the last piece
-    // with the value it already gets (no branches, so the loads batch)
+    static_assert(sizeof(FADevTable) % 16 == 0, "the table copies in 16-byte pieces");
+    TableCopy c;
+    const Piece *src = reinterpret_cast<const Piece *>(g);
 #pragma unroll
-    for (int u = 0; u < per; ++u) v[u] = src[min((int)(threadIdx.x + u * blockDim.x), n - 1)];
+    for (int u = 0; u < kTabRounds; ++u)
+        if (u * (int)blockDim.x < kTabPieces)
+            c.v[u] = src[min((int)(threadIdx.x + u * blockDim.x), kTabPieces - 1)];
+    return c;
+}
+
+__device__ __forceinline__ void table_store(FADevTable &tab, const TableCopy &c)
+{
+    Piece *dst = reinterpret_cast<Piece *>(&tab);
 #pragma unroll
-    for (int u = 0; u < per; ++u) dst[min((int)(threadIdx.x + u * blockDim.x), n - 1)] = v[u];
-    __syncthreads();
+    for (int u = 0; u < kTabRounds; ++u)
+        if (u * (int)blockDim.x < kTabPieces)
+            dst[min((int)(threadIdx.x + u * blockDim.x), kTabPieces - 1)] = c.v[u];
 }
 
 // M <- M Rx(b): the fixed pre-rotation of side frame 0
@@ -235,203 +281,111 @@ __device__ __forceinline__ void aff_rot_x(Aff &m, float c, float s)
     m.r02 = b0; m.r12 = b1; m.r22 = b2;
 }
 
-// A wave's atom run [A0, A0 + n): plane p of atom e (relative to A0) lives
-// at st[p * ns + e] -- in the per-wave LDS stage (ns = the stage's floats per
-// plane), or, for schedules whose stage does not fit the LDS, in global
-// memory itself (st = array + A0, ns = A): the same indexing serves both.
-struct Stage {
-    float *st;
-    int64_t ns;
+// A wave's atom run [A0, A0 + n): atom e (relative to A0).  In the per-wave
+// LDS stage (LDS = true) its x, y, z lie side by side (one 12-byte access per
+// atom, and the coalesced side of the copies reads with an odd stride of
+// three); for schedules whose stage does not fit the LDS the run is global
+// memory itself, in planes ns apart.
+struct F3 {
+    float x, y, z;
 };
 
-// Coalesced copy between a global run (3 planes, plane stride A) and the
-// wave's staging buffer, eight rows of 64 atoms at a time: all loads of a
-// batch are issued before the first store (indices past the run are clamped
-// to its last atom), so a batch costs one memory latency, not eight.
-constexpr int kStageBatch = 8;
-
-__device__ __forceinline__ void run_to_lds(const Stage &sg, int plane0, const float *__restrict__ src,
-                                           int64_t A, int64_t A0, int n)
-{
-    const int lane = lane_id();
-    const float *s0 = src + A0, *s1 = src + A + A0, *s2 = src + 2 * A + A0;
-    float *d0 = sg.st + plane0 * sg.ns, *d1 = d0 + sg.ns, *d2 = d1 + sg.ns;
-    for (int base = 0; base < n; base += kStageBatch * kWave) {
-        float v0[kStageBatch], v1[kStageBatch], v2[kStageBatch];
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int e = min(base + lane + u * kWave, n - 1);
-            v0[u] = s0[e];
-            v1[u] = s1[e];
-            v2[u] = s2[e];
-        }
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int e = base + lane + u * kWave;
-            if (e < n) {
-                d0[e] = v0[u];
-                d1[e] = v1[u];
-                d2[e] = v2[u];
-            }
-        }
+template <bool LDS>
+struct Atoms {
+    float *st;
+    int64_t ns;
+    __device__ __forceinline__ F3 get(int e) const
+    {
+        if constexpr (LDS) return *reinterpret_cast<const F3 *>(st + 3 * e);
+        else return F3{st[e], st[ns + e], st[2 * ns + e]};
     }
+    __device__ __forceinline__ void put(int e, float x, float y, float z) const
+    {
+        if constexpr (LDS) *reinterpret_cast<F3 *>(st + 3 * e) = F3{x, y, z};
+        else { st[e] = x; st[ns + e] = y; st[2 * ns + e] = z; }
+    }
+};
+
+// Coalesced copies between a global run (3 planes, plane stride A) and the
+// wave's stage, kRows rows of 64 atoms at a time: a batch's loads are all
+// issued before its first store.  Rows past the run are skipped as a whole
+// (n is wave-uniform); inside the last row indices are clamped.
+constexpr int kRows = 10;
+
+struct RunRows {
+    float v0[kRows], v1[kRows], v2[kRows];
+};
+
+__device__ __forceinline__ RunRows rows_load(const float *__restrict__ src, int64_t A, int64_t A0,
+                                             int base, int n)
+{
+    const int lane = threadIdx.x & 63;
+    const float *s0 = src + A0, *s1 = src + A + A0, *s2 = src + 2 * A + A0;
+    RunRows r;
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+        if (base + u * kWave < n) {
+            const int e = min(base + lane + u * kWave, n - 1);
+            r.v0[u] = s0[e];
+            r.v1[u] = s1[e];
+            r.v2[u] = s2[e];
+        }
+    return r;
 }
 
-__device__ __forceinline__ void lds_to_run(const Stage &sg, float *__restrict__ dst, int64_t A,
+__device__ __forceinline__ void rows_to_lds(const RunRows &r, float *st, int base, int n)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+        if (base + u * kWave < n) {
+            const int e = min(base + lane + u * kWave, n - 1);
+            st[3 * e] = r.v0[u];
+            st[3 * e + 1] = r.v1[u];
+            st[3 * e + 2] = r.v2[u];
+        }
+}
+
+// the rows after the first batch
+__device__ __forceinline__ void run_to_lds_rest(float *st, const float *__restrict__ src, int64_t A,
+                                                int64_t A0, int n)
+{
+    for (int base = kRows * kWave; base < n; base += kRows * kWave)
+        rows_to_lds(rows_load(src, A, A0, base, n), st, base, n);
+}
+
+__device__ __forceinline__ void lds_to_run(const float *st, float *__restrict__ dst, int64_t A,
                                            int64_t A0, int n)
 {
-    const int lane = lane_id();
+    const int lane = threadIdx.x & 63;
     float *o0 = dst + A0, *o1 = dst + A + A0, *o2 = dst + 2 * A + A0;
-    const float *s0 = sg.st, *s1 = s0 + sg.ns, *s2 = s1 + sg.ns;
-    for (int base = 0; base < n; base += kStageBatch * kWave) {
-        float v0[kStageBatch], v1[kStageBatch], v2[kStageBatch];
+    for (int base = 0; base < n; base += kRows * kWave) {
+        RunRows r;
 #pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int e = min(base + lane + u * kWave, n - 1);
-            v0[u] = s0[e];
-            v1[u] = s1[e];
-            v2[u] = s2[e];
-        }
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int e = base + lane + u * kWave;
-            if (e < n) {
-                o0[e] = v0[u];
-                o1[e] = v1[u];
-                o2[e] = v2[u];
+        for (int u = 0; u < kRows; ++u)
+            if (base + u * kWave < n) {
+                const int e = min(base + lane + u * kWave, n - 1);
+                r.v0[u] = st[3 * e];
+                r.v1[u] = st[3 * e + 1];
+                r.v2[u] = st[3 * e + 2];
             }
-        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u)
+            if (base + u * kWave < n) {
+                const int e = min(base + lane + u * kWave, n - 1);
+                o0[e] = r.v0[u];
+                o1[e] = r.v1[u];
+                o2[e] = r.v2[u];
+            }
     }
 }
 
-// Emit the atoms of frame k of type t placed by F into the staging buffer.
-// The frame's first atom is its origin: F's translation, no product.  Frame
-// k exists for the type (every existing frame holds its origin atom).
-__device__ __forceinline__ void emit_frame(const FATable &tab, const FAType &ft, int k,
-                                           const Aff &F, const Stage &sg, int aloc)
-{
-    {
-        const int e = aloc + ft.atom[ft.fbegin[k]].slot;
-        sg.st[e] = F.t0;
-        sg.st[sg.ns + e] = F.t1;
-        sg.st[2 * sg.ns + e] = F.t2;
-    }
-    for (int i = 1; i < tab.max_count[k]; ++i) {
-        if (i < ft.fcount[k]) {
-            const FAAtom at = ft.atom[ft.fbegin[k] + i];
-            float x, y, z;
-            aff_point(F, at.x, at.y, at.z, x, y, z);
-            const int e = aloc + at.slot;
-            sg.st[e] = x;
-            sg.st[sg.ns + e] = y;
-            sg.st[2 * sg.ns + e] = z;
-        }
-    }
-}
-
-// Wrench of the atoms of frame k placed by F, upstream gradients staged in
-// planes 0..2 (the origin atom first, at F's translation).
-__device__ __forceinline__ void frame_wrench(const FATable &tab, const FAType &ft, int k,
-                                             const Aff &F, const Stage &sg, int aloc, Wrench &w)
-{
-    {
-        const int e = aloc + ft.atom[ft.fbegin[k]].slot;
-        wrench_add_point(w, F.t0, F.t1, F.t2, sg.st[e], sg.st[sg.ns + e], sg.st[2 * sg.ns + e]);
-    }
-    for (int i = 1; i < tab.max_count[k]; ++i) {
-        if (i < ft.fcount[k]) {
-            const FAAtom at = ft.atom[ft.fbegin[k] + i];
-            float x, y, z;
-            aff_point(F, at.x, at.y, at.z, x, y, z);
-            const int e = aloc + at.slot;
-            wrench_add_point(w, x, y, z, sg.st[e], sg.st[sg.ns + e], sg.st[2 * sg.ns + e]);
-        }
-    }
-}
-
-// The fused training step: the stage holds the target t of each atom; the
-// wrench of frame k's atoms takes the loss gradient 2 (r - t), the loss
-// accumulates |r - t|^2, and the staged target is replaced by r (so the
-// stage ends up holding the coordinates).
-__device__ __forceinline__ void atom_mse(float x, float y, float z, int e, const Stage &sg,
-                                         const Stage &so, bool write, Wrench &w, float &loss)
-{
-    const float dx = x - sg.st[e], dy = y - sg.st[sg.ns + e], dz = z - sg.st[2 * sg.ns + e];
-    loss += dx * dx + dy * dy + dz * dz;
-    wrench_add_point(w, x, y, z, 2.f * dx, 2.f * dy, 2.f * dz);
-    if (write) {
-        so.st[e] = x;
-        so.st[so.ns + e] = y;
-        so.st[2 * so.ns + e] = z;
-    }
-}
-
-__device__ __forceinline__ void frame_wrench_mse(const FATable &tab, const FAType &ft, int k,
-                                                 const Aff &F, const Stage &sg, const Stage &so,
-                                                 bool write, int aloc, Wrench &w, float &loss)
-{
-    atom_mse(F.t0, F.t1, F.t2, aloc + ft.atom[ft.fbegin[k]].slot, sg, so, write, w, loss);
-    for (int i = 1; i < tab.max_count[k]; ++i) {
-        if (i < ft.fcount[k]) {
-            const FAAtom at = ft.atom[ft.fbegin[k] + i];
-            float x, y, z;
-            aff_point(F, at.x, at.y, at.z, x, y, z);
-            atom_mse(x, y, z, aloc + at.slot, sg, so, write, w, loss);
-        }
-    }
-}
-
-// Wrench of the atoms of frame k with positions from sx and upstream
-// gradients from sg.
-__device__ __forceinline__ void frame_wrench_xyz(const FATable &tab, const FAType &ft, int k,
-                                                 const Stage &sg, const Stage &sx, int aloc,
-                                                 Wrench &w)
-{
-    for (int i = 0; i < tab.max_count[k]; ++i) {
-        if (i < ft.fcount[k]) {
-            const int e = aloc + ft.atom[ft.fbegin[k] + i].slot;
-            wrench_add_point(w, sx.st[e], sx.st[sx.ns + e], sx.st[2 * sx.ns + e],
-                             sg.st[e], sg.st[sg.ns + e], sg.st[2 * sg.ns + e]);
-        }
-    }
-}
-
-__device__ __forceinline__ void side_step(Aff &sf, const FAType &ft, int f, float chi)
-{
-    float c = 1.f, s = 0.f;
-    if (ft.side_chi[f]) {
-        if (__all(sincos_fast_ok(chi))) sincos_fast(chi, s, c);
-        else sincos_accurate(chi, s, c);
-    }
-    aff_apply_transform(sf, ft.ct[f], ft.st[f], ft.d[f], c, s);
-}
-
-// Chunk c of a tile: residues [cs, ce) handled by the waves wave < nact.
-struct FAChunk {
+struct ChunkRange {
     int64_t cs, ce;
     int nact;
 };
 
-template <int K>
-__device__ __forceinline__ FAChunk fa_chunk(int64_t ts, int64_t te, int c)
-{
-    const int nw = blockDim.x >> 6;
-    const int64_t ch = (int64_t)kWave * K * nw;
-    FAChunk k;
-    k.cs = ts + (int64_t)c * ch;
-    k.ce = min(k.cs + ch, te);
-    k.nact = (int)min((int64_t)nw, (k.ce - k.cs + kWave * K - 1) / (kWave * K));
-    return k;
-}
-
-template <int K>
-__device__ __forceinline__ int fa_chunks(int64_t ts, int64_t te)
-{
-    const int64_t ch = (int64_t)kWave * K * (blockDim.x >> 6);
-    return (int)((te - ts + ch - 1) / ch);
-}
-
-// Per-lane bookkeeping of one chunk.
+// Per-lane bookkeeping of one window.
 template <int K>
 struct LaneRun {
     int64_t rs, rbase, A0;
@@ -441,7 +395,7 @@ struct LaneRun {
 };
 
 template <int K>
-__device__ __forceinline__ LaneRun<K> lane_run(const FAChunk &k,
+__device__ __forceinline__ LaneRun<K> lane_run(const ChunkRange &k,
                                                const uint32_t *__restrict__ head_bits,
                                                const int32_t *__restrict__ res_aoff)
 {
@@ -463,31 +417,35 @@ __device__ __forceinline__ LaneRun<K> lane_run(const FAChunk &k,
     return L;
 }
 
-// Per-residue inputs of a lane, read right after the chunk's bookkeeping so
-// that their latency overlaps the block scan instead of stalling the walk:
-// residue type, first atom and (CHI) the four chi planes (read for every
-// residue; a residue without chi f ignores plane f).
-template <int K, bool CHI>
+// Per-residue inputs of a lane, read right after the window's bookkeeping so
+// that their latency overlaps the spine scan instead of stalling the walk:
+// residue type, first atom and (ANG) the seven angles (chi planes are read
+// for every residue; a residue without chi f ignores plane f).
+template <int K, bool ANG>
 struct LaneRes {
     int type[K];
     int aoff[K];
-    float chi[CHI ? K : 1][4];
+    float phi[ANG ? K : 1], psi[ANG ? K : 1], om[ANG ? K : 1];
+    float chi[ANG ? K : 1][4];
 };
 
-template <int K, bool CHI>
-__device__ __forceinline__ LaneRes<K, CHI> load_lane_res(const LaneRun<K> &L,
+template <int K, bool ANG>
+__device__ __forceinline__ LaneRes<K, ANG> load_lane_res(const LaneRun<K> &L,
                                                          const uint8_t *__restrict__ seq,
                                                          const int32_t *__restrict__ res_aoff,
                                                          const float *__restrict__ ang, int64_t R)
 {
-    LaneRes<K, CHI> lr;
+    LaneRes<K, ANG> lr;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const bool v = j < L.cnt;
         const int64_t r = v ? L.rs + j : 0;
         lr.type[j] = v ? seq[r] : 0;
         lr.aoff[j] = v ? res_aoff[r] : 0;
-        if (CHI) {
+        if (ANG) {
+            lr.phi[j] = v ? ang[r] : 0.f;
+            lr.psi[j] = v ? ang[R + r] : 0.f;
+            lr.om[j] = v ? ang[2 * R + r] : 0.f;
 #pragma unroll
             for (int f = 0; f < 4; ++f) lr.chi[j][f] = v ? ang[(3 + f) * R + r] : 0.f;
         }
@@ -495,91 +453,325 @@ __device__ __forceinline__ LaneRes<K, CHI> load_lane_res(const LaneRun<K> &L,
     return lr;
 }
 
-// All atoms of one residue from the frame before it (cur, advanced to the
-// residue's C frame): spine transforms omega, phi, psi, and the side chain
-// branching off the CA frame, each frame's atoms written to the stage.
-__device__ __forceinline__ void fa_emit_residue(const FATable &tab, const FAType &ft, Aff &cur,
-                                                const ResidueIn &in, const float (&chi)[4],
-                                                const BBParams &P, const Stage &sg, int aloc)
+// ------------------------------------------------------- entering frames
+// The spine scan of a window.  Every lane forms the product of its K residues'
+// spine transforms (its unit) and leaves it in LDS; the window's first waves
+// then take four units per lane (256 per wave), scan them, hand frames across
+// the window's edges and leave the frame entering every unit in its place.
+// The wave scan costs some 370 VALU instructions however many residues a lane
+// holds, so it runs on a quarter of the waves, and a window of four waves
+// needs no scan across waves; everything per residue stays spread over all
+// lanes.
+//
+// 256 units take one block of 3 x 4 x 65 16-byte pieces: piece part of unit
+// 4 l + j sits at (4 part + j) 65 + l, so that neither the spine lanes (l
+// consecutive) nor the unit lanes (j fastest) meet bank conflicts.
+constexpr int kGroup = 4;                        // units per spine lane
+constexpr int kSpineUnits = kWave * kGroup;      // units per spine wave
+constexpr int kFrameBlock = 3 * kGroup * 65 * 4; // floats
+
+inline size_t frame_bytes(int waves)
 {
-    aff_apply_transform(cur, P.ct[0], P.st[0], P.d[0], in.co, in.so);
-    emit_frame(tab, ft, 0, cur, sg, aloc);
-    aff_apply_transform(cur, P.ct[1], P.st[1], P.d[1], in.cp, in.sp);
-    emit_frame(tab, ft, 1, cur, sg, aloc);
-    if (ft.n_side > 0) {
-        Aff sf = cur;
-        aff_rot_x(sf, ft.pre_c, ft.pre_s);
+    return (size_t)((waves + kGroup - 1) / kGroup) * kFrameBlock * sizeof(float);
+}
+
+__device__ __forceinline__ void frame_put(float *frames, int block, int i, const Aff &m)
+{
+    float4 *q = reinterpret_cast<float4 *>(frames + block * kFrameBlock);
+    q[i] = float4{m.r00, m.r10, m.r20, m.r01};
+    q[i + kGroup * 65] = float4{m.r11, m.r21, m.r02, m.r12};
+    q[i + 2 * kGroup * 65] = float4{m.r22, m.t0, m.t1, m.t2};
+}
+
+__device__ __forceinline__ Aff frame_get(const float *frames, int block, int i)
+{
+    const float4 *q = reinterpret_cast<const float4 *>(frames + block * kFrameBlock);
+    const float4 u = q[i], v = q[i + kGroup * 65], w = q[i + 2 * kGroup * 65];
+    Aff m;
+    m.r00 = u.x; m.r10 = u.y; m.r20 = u.z; m.r01 = u.w;
+    m.r11 = v.x; m.r21 = v.y; m.r02 = v.z; m.r12 = v.w;
+    m.r22 = w.x; m.t0 = w.y; m.t1 = w.z; m.t2 = w.w;
+    return m;
+}
+
+// The frame entering each lane's unit.  unit: the product of the lane's spine
+// transforms since its last chain head (the identity for an empty lane);
+// head: a chain starts in the lane; n_units: lanes holding residues.  Every
+// thread of the block calls it; flags (kMaxWaves words) and frames
+// (frame_bytes) are LDS.  The frames are free again after the caller's next
+// barrier.
+__device__ __forceinline__ Aff entering_frame(const Aff &unit, bool head, int n_units,
+                                              float *frames, uint64_t (&flags)[kMaxWaves],
+                                              FwdShared &sh, float (&carry_sh)[12],
+                                              uint64_t *__restrict__ status, int64_t t,
+                                              int64_t first, uint64_t prev, bool published)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int block = wave / kGroup;
+    const int at = (lane & 3) * 65 + (wave % kGroup) * (kWave / kGroup) + (lane >> 2);
+    const uint64_t heads_u = __builtin_amdgcn_ballot_w64(head);
+    if (wave * kWave < n_units) {
+        frame_put(frames, block, at, unit);
+        if (lane == 0) flags[wave] = heads_u;
+    }
+    __syncthreads();
+    const int ns = (n_units + kSpineUnits - 1) / kSpineUnits;  // spine waves
+    const bool spine = wave < ns;
+    Aff m = aff_identity();
+    uint32_t hm = 0;  // chain heads in the lane's four units
+    if (spine) {
+        // the other waves of the workgroup wait for this part
+        __builtin_amdgcn_s_setprio(3);
+        const int w = kGroup * wave + (lane >> 4);  // the wave holding the lane's units
+        const int u0 = wave * kSpineUnits + kGroup * lane;
+        if (u0 < n_units) {
+            hm = (uint32_t)(flags[w] >> (4 * (lane & 15))) & 15u;
+            const bool any = __builtin_amdgcn_ballot_w64(hm != 0u) != 0ull;
+            m = frame_get(frames, wave, lane);
 #pragma unroll
-        for (int f = 0; f < A2C_MAX_SIDE_FRAMES; ++f) {
-            if (f < tab.max_side && f < ft.n_side) {
-                side_step(sf, ft, f, chi[f]);
-                emit_frame(tab, ft, 3 + f, sf, sg, aloc);
+            for (int j = 1; j < kGroup; ++j) {
+                // units past the last one hold nothing (their waves may not
+                // have run): they leave the aggregate alone
+                if (u0 + j < n_units) {
+                    const Aff b = frame_get(frames, wave, j * 65 + lane);
+                    const Aff c = aff_compose(m, b);
+                    if (any) m = aff_select((hm >> j) & 1u, b, c);
+                    else m = c;
+                }
             }
         }
+        // the fixed rotations repeat every residue, so their float32 rounding
+        // drifts the scale of long products coherently; one polar step per
+        // lane aggregate removes that drift
+        aff_orthonormalise(m);
+    }
+    const uint64_t heads = __builtin_amdgcn_ballot_w64(hm != 0u);
+    Aff cur = block_prefix_windows(m, heads, ns, spine, sh, carry_sh, status, t, first, prev,
+                                   published);
+    if (spine) {
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) {
+            const Aff b = frame_get(frames, wave, j * 65 + lane);
+            frame_put(frames, wave, j * 65 + lane, cur);
+            if (j + 1 < kGroup) {
+                const Aff c = aff_compose(cur, b);
+                const bool h = (hm >> j) & 1u;
+                if (__builtin_amdgcn_ballot_w64(h) != 0ull) cur = aff_select(h, b, c);
+                else cur = c;
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();
+    return frame_get(frames, block, at);
+}
+
+// cos/sin of a lane's spine angles.
+template <int K>
+__device__ __forceinline__ void lane_sincos(const LaneRes<K, true> &lr, ResidueIn (&in)[K])
+{
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+        ok = ok && sincos_fast_ok(lr.om[j]) && sincos_fast_ok(lr.phi[j]) && sincos_fast_ok(lr.psi[j]);
+    if (__all(ok)) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            sincos_fast(lr.om[j], in[j].so, in[j].co);
+            sincos_fast(lr.phi[j], in[j].sp, in[j].cp);
+            sincos_fast(lr.psi[j], in[j].ss, in[j].cs);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            sincos_accurate(lr.om[j], in[j].so, in[j].co);
+            sincos_accurate(lr.phi[j], in[j].sp, in[j].cp);
+            sincos_accurate(lr.psi[j], in[j].ss, in[j].cs);
+        }
+    }
+}
+
+// The lane's unit: the product of its residues' spine transforms since its
+// last chain head (the identity for an empty lane).
+template <int K>
+__device__ __forceinline__ Aff spine_unit(const ResidueIn (&in)[K], const LaneRun<K> &L,
+                                          const BBParams &P)
+{
+    Aff m = aff_identity();
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        if (j < L.cnt) {
+            const bool h = (L.hm >> j) & 1u;
+            if (j == 0 || h) m = aff_first_transform(P.ct[0], P.st[0], P.d[0], in[j].co, in[j].so);
+            else aff_apply_transform(m, P.ct[0], P.st[0], P.d[0], in[j].co, in[j].so);
+            aff_apply_transform(m, P.ct[1], P.st[1], P.d[1], in[j].cp, in[j].sp);
+            aff_apply_transform(m, P.ct[2], P.st[2], P.d[2], in[j].cs, in[j].ss);
+        }
+    }
+    return m;
+}
+
+// ------------------------------------------------------------- the walk
+// A residue type's list of extra atoms (not at a frame's origin) as the walk
+// consumes it: N, CA, the side frames in order, C.
+struct TypeAt {
+    const FADevType *ft;
+    uint32_t counts, origin;
+    int n_side;
+    const FAAtom *ex;  // next extra atom
+};
+
+__device__ __forceinline__ TypeAt type_at(const FADevTable &tab, int type)
+{
+    TypeAt t;
+    t.ft = &tab.t[type];
+    t.counts = t.ft->counts;
+    t.origin = t.ft->origin;
+    t.n_side = (int)(t.counts >> 28);
+    t.ex = t.ft->ex;
+    return t;
+}
+
+// Extra atoms in position i of the walk (0 N, 1 CA, 2 + f side frame f, 6 C).
+__device__ __forceinline__ int extra_count(const TypeAt &t, int i)
+{
+    return (int)((t.counts >> (4 * i)) & 15u);
+}
+
+// Every extra atom of one frame placed by F: op(e, x, y, z).
+template <typename Op>
+__device__ __forceinline__ void walk_extras(TypeAt &t, int n, const Aff &F, int aloc, Op &&op)
+{
+    for (int i = 0; i < n; ++i) {
+        const FAAtom at = t.ex[i];
+        float x, y, z;
+        aff_point(F, at.x, at.y, at.z, x, y, z);
+        op(aloc + at.slot, x, y, z);
+    }
+    t.ex += n;
+}
+
+// Side frame f from the one before it (chi: its torsion; a frame without one
+// takes 0 whatever the plane holds).
+__device__ __forceinline__ void side_step(Aff &sf, const FADevType &ft, int f, float chi)
+{
+    const float4 g = ft.fr[f];  // ct, st, d, 1 where the frame has a chi
+    const float a = g.w != 0.f ? chi : 0.f;
+    float c, s;
+    if (__all(sincos_fast_ok(a))) sincos_fast(a, s, c);
+    else sincos_accurate(a, s, c);
+    aff_apply_transform(sf, g.x, g.y, g.z, c, s);
+}
+
+// All atoms of one residue from the frame before it (cur, advanced to the
+// residue's C frame): spine transforms omega, phi, psi, and the side chain
+// branching off the CA frame.  Each frame's first atom is its origin: the
+// frame's translation, no product.  Of the side frames' extra atoms nearly all
+// belong to a residue's last frame, so those run in one loop after the
+// frames, as long as the largest of the wave's lanes has atoms, whichever
+// frame is its last (8 rounds for random sequences, where a loop per frame to
+// the table's largest count took 15 for the 2.5 a residue has on average).
+template <bool LDS>
+__device__ __forceinline__ void fa_emit_residue(const FADevTable &tab, int type, Aff &cur,
+                                                const ResidueIn &in, const float (&chi)[4],
+                                                const BBParams &P, const Atoms<LDS> &out, int aloc)
+{
+    TypeAt t = type_at(tab, type);
+    auto put = [&](int e, float x, float y, float z) { out.put(e, x, y, z); };
+    aff_apply_transform(cur, P.ct[0], P.st[0], P.d[0], in.co, in.so);
+    put(aloc, cur.t0, cur.t1, cur.t2);
+    walk_extras(t, extra_count(t, 0), cur, aloc, put);
+    aff_apply_transform(cur, P.ct[1], P.st[1], P.d[1], in.cp, in.sp);
+    put(aloc + 1, cur.t0, cur.t1, cur.t2);
+    walk_extras(t, extra_count(t, 1), cur, aloc, put);
+    if (t.n_side > 0) {
+        Aff sf = cur;
+        aff_rot_x(sf, t.ft->pre_c, t.ft->pre_s);
+        int last = 0;  // extra atoms of the last side frame
+#pragma unroll
+        for (int f = 0; f < A2C_MAX_SIDE_FRAMES; ++f) {
+            if (f < t.n_side) {
+                side_step(sf, *t.ft, f, chi[f]);
+                put(aloc + (int)((t.origin >> (8 * f)) & 255u), sf.t0, sf.t1, sf.t2);
+                last = extra_count(t, 2 + f);
+                if (f + 1 < t.n_side && last > 0) walk_extras(t, last, sf, aloc, put);
+            }
+        }
+        walk_extras(t, last, sf, aloc, put);
     }
     aff_apply_transform(cur, P.ct[2], P.st[2], P.d[2], in.cs, in.ss);
-    emit_frame(tab, ft, 2, cur, sg, aloc);
+    put(aloc + 2, cur.t0, cur.t1, cur.t2);
+    walk_extras(t, extra_count(t, 6), cur, aloc, put);
 }
 
 // Forward over windows of the packed batch (window t: residues
-// [wstart[t], wstart[t + 1]), at most C = 64 W K), as the backbone forward:
-// the spine scan hands frames across window edges by window look-back; then
-// every lane re-walks its residues from its prefix frame, building the spine
+// [wstart[t], wstart[t + 1]), at most C = 64 W K): the spine scan leaves the
+// frame entering every residue in LDS (frames handed across window edges by
+// window look-back); then every lane walks its residues, building the spine
 // and side frames and writing each atom into the wave's LDS stage, which is
-// copied out with coalesced stores (STG; otherwise, for schedules whose
-// stage does not fit the LDS, straight to global memory).
+// copied out with coalesced stores (STG; otherwise, for schedules whose stage
+// does not fit the LDS, straight to global memory).  The stage takes the
+// frames' place once every lane holds its own.
+// Bound by VALU issue and waits in turn: 1137 instructions per wave of 64
+// residues at K = 1 (62 us of issue for 2.16 M residues in some 105 us, where
+// the 288 MB would take 56), 16 waves per CU (the LDS stages).  The spine scan
+// on a quarter of the waves, one loop over the last frame's atoms and 12-byte
+// stage accesses took 2000 chains of 50..2000 residues from 59.7 to 51.5 us at
+// (1, 4), 500 chains of 151 from 11.9 to 10.7 us at (1, 6).
 template <int K, int LB, bool STG = true>
 __global__ __launch_bounds__(LB) void fa_forward_flat_kernel(
     const float *__restrict__ ang, float *__restrict__ xyz, const uint32_t *__restrict__ head_bits,
     const int32_t *__restrict__ wstart, const int32_t *__restrict__ res_aoff,
-    const uint8_t *__restrict__ seq, const FATable *__restrict__ gtab,
+    const uint8_t *__restrict__ seq, const FADevTable *__restrict__ gtab,
     const int32_t *__restrict__ look_first,
     uint64_t *__restrict__ status, int64_t R, int64_t A, BBParams P, int stage_atoms)
 {
-    extern __shared__ float stage_mem[];
-    __shared__ __align__(16) FATable tab;
+    extern __shared__ __align__(16) float stage_mem[];
+    __shared__ __align__(16) FADevTable tab;
     __shared__ FwdShared sh;
     __shared__ float carry_sh[12];
+    __shared__ uint64_t unit_flags[kMaxWaves];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = blockIdx.x;
-    FAChunk k;
+    ChunkRange k;
     k.cs = wstart[t];
     k.ce = wstart[t + 1];
     k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
-    const LaneRun<K> L = lane_run<K>(k, head_bits, res_aoff);
+    const TableCopy tc = table_load(gtab);
     uint64_t prev = 0;
     int64_t first = t;
     if (wave == 0) {
         prev = lb_load(status + t * kLbWords);
         first = look_first[t];
     }
-    // the window's inputs ahead of the table copy (which ends in a barrier)
-    SpineAngles<K> a{};
-    if (L.active) a = load_spine_angles<K>(ang, R, L.rs, L.cnt);
+    const LaneRun<K> L = lane_run<K>(k, head_bits, res_aoff);
     const LaneRes<K, true> lr = load_lane_res<K, true>(L, seq, res_aoff, ang, R);
-    load_table(tab, gtab);
+    table_store(tab, tc);
     ResidueIn in[K];
-    int first_head = K;
-    Aff m = aff_identity();
-    if (L.active) m = fa_lane_aggregate<K>(a, L.cnt, L.hm, P, in, first_head);
-    const uint64_t heads = __builtin_amdgcn_ballot_w64(first_head < K);
-    const Aff X = block_prefix_windows(m, heads, k.nact, L.active, sh, carry_sh, status, t, first,
-                                       prev);
+    Aff unit = aff_identity();
+    if (L.active) {
+        lane_sincos<K>(lr, in);
+        unit = spine_unit<K>(in, L, P);
+    }
+    const int n_units = (int)((k.ce - k.cs + K - 1) / K);
+    Aff cur = entering_frame(unit, L.hm != 0u, n_units, stage_mem, unit_flags, sh, carry_sh, status,
+                             t, first, prev, false);
+    if (STG) __syncthreads();  // the stage takes the frames' place
     if (!L.active) return;
-    const Stage sg = STG ? Stage{stage_mem + (size_t)wave * 3 * stage_atoms, stage_atoms}
-                         : Stage{xyz + L.A0, A};
-    Aff cur = X;
+    float *st = stage_mem + (size_t)wave * 3 * stage_atoms;
+    const Atoms<STG> out = STG ? Atoms<STG>{st, 0} : Atoms<STG>{xyz + L.A0, A};
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         if (j < L.cnt) {
             if ((L.hm >> j) & 1u) cur = aff_identity();
-            fa_emit_residue(tab, tab.t[lr.type[j]], cur, in[j], lr.chi[j], P, sg,
-                            lr.aoff[j] - (int)L.A0);
+            fa_emit_residue<STG>(tab, lr.type[j], cur, in[j], lr.chi[j], P, out,
+                                 lr.aoff[j] - (int)L.A0);
         }
     }
     if (STG) {
         wave_lds_sync();
-        lds_to_run(sg, xyz, A, L.A0, L.natoms);
+        lds_to_run(st, xyz, A, L.A0, L.natoms);
     }
 }
 
@@ -652,21 +844,54 @@ __device__ __forceinline__ void fa_store_grads(float *__restrict__ gang, int64_t
     S_out = S;
 }
 
-// Backward over windows of the packed batch, last window first (rev:
-// reverse_window, so that window t runs on the XCD where the spine pass's
-// window t read the same angles; in order where the windows hold whole
-// chains, as the backbone adjoint): the
-// side chains' subtree sums give the chi gradients, the spine groups feed a
-// reverse scan over residues (window look-back for the wrench of later
-// windows), and u . (S_m - o x S_g) gives phi, psi, omega.
-// RECOMPUTE: frames from the angles, the frame entering the window composed
-// from the aggregates spine_aggregate_kernel published (status_fwd,
-// windows look_fwd[t] .. t - 1); otherwise positions and axes from the
-// forward's coordinates.
+// The adjoint's per-atom step where the frames are recomputed: the wrench of
+// the atom at (x, y, z) for its staged upstream gradient, or (GM = kGradMse)
+// for the loss gradient 2 (r - t) of its staged target, which the position
+// then replaces (the stage ends up holding the coordinates); the loss takes
+// |r - t|^2.
+template <int GM, bool STG>
+struct AtomForce {
+    Atoms<STG> g, out;
+    bool write;
+    float loss;
+    __device__ __forceinline__ void operator()(Wrench &w, int e, float x, float y, float z)
+    {
+        const F3 s = g.get(e);
+        if constexpr (GM == kGradMse) {
+            const float dx = x - s.x, dy = y - s.y, dz = z - s.z;
+            loss += dx * dx + dy * dy + dz * dz;
+            wrench_add_point(w, x, y, z, 2.f * dx, 2.f * dy, 2.f * dz);
+            if (write) out.put(e, x, y, z);
+        } else {
+            wrench_add_point(w, x, y, z, s.x, s.y, s.z);
+        }
+    }
+};
+
+// Backward over windows of the packed batch: the side chains' subtree sums
+// give the chi gradients, the spine groups feed a reverse scan over residues
+// (window look-ahead for the wrench of later windows), and
+// u . (S_m - o x S_g) gives phi, psi, omega.
+// RECOMPUTE: frames from the angles.  Window t publishes its spine aggregate,
+// takes the frames of the earlier windows its first chain spans, then
+// publishes its wrench and adds those of the later windows its last chain
+// runs into; a wrench waits only on aggregates and those on nothing, so the
+// windows go in order and a launch progresses as long as the device holds the
+// at most kMaxAhead + 1 workgroups a chain spans at once.  For longer chains
+// (spined) a spine pass has published the aggregates and the windows go last
+// to first.  Otherwise positions and axes from the forward's coordinates, last
+// window first (rev; in order where the windows hold whole chains).
 // GM = kGradMse (with RECOMPUTE): g points at a target t and the upstream
 // gradient is 2 (r - t), formed from the recomputed positions (the fused
 // training step); xyz_out (may be NULL) receives the positions, loss_out
 // (may be NULL) the batch's sum of |r - t|^2 (lb_loss_commit).
+// Bound as the forward, with 1759 instructions per wave at K = 1.  Without the
+// spine pass before it (6.5 us on 512 chains of 50..2000 residues), with the
+// spine scan on a quarter of the waves, the extra atoms in one loop and the
+// first rows of the gradients loaded ahead of the scan, the recomputing form
+// went from 87.1 to 67.0 us on 2000 such chains at (1, 4) and from 31.4 to
+// 20.8 us on 512, the fused step from 116 to 90.1 and 38.3 to 30.1 us; from
+// coordinates 12.7 to 9.1 us on 64 chains of 300 at (1, 6).
 // nt: the angle gradients go out with non-temporal stores (large plans).
 // STG: atoms go through the per-wave LDS stage; otherwise global memory is
 // addressed directly (schedules whose stage does not fit the LDS).
@@ -676,63 +901,68 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     float *__restrict__ gang, float *__restrict__ xyz_out, float *__restrict__ loss_out,
     const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart,
     const int32_t *__restrict__ res_aoff, const uint8_t *__restrict__ seq,
-    const FATable *__restrict__ gtab, const uint64_t *__restrict__ status_fwd,
+    const FADevTable *__restrict__ gtab, uint64_t *__restrict__ status_fwd,
     const int32_t *__restrict__ look_fwd,
     const int32_t *__restrict__ look_last, uint64_t *__restrict__ status, int64_t R, int64_t A,
-    BBParams P, int stage_atoms, int32_t rev, int32_t nt)
+    BBParams P, int stage_atoms, int32_t rev, int32_t spined, int32_t nt)
 {
     static_assert(GM == kGradLoad || RECOMPUTE, "the fused step recomputes the frames");
-    extern __shared__ float stage_mem[];
-    __shared__ __align__(16) FATable tab;
+    extern __shared__ __align__(16) float stage_mem[];
+    __shared__ __align__(16) FADevTable tab;
     __shared__ FwdShared shf;
     __shared__ BwdShared shb;
+    __shared__ float fcarry_sh[12];
     __shared__ float rcarry_sh[6];
+    __shared__ uint64_t unit_flags[kMaxWaves];
     __shared__ float loss_tot[GM == kGradMse ? kMaxWaves : 1];
-    float loss = 0.f;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-    FAChunk k;
+    ChunkRange k;
     k.cs = wstart[t];
     k.ce = wstart[t + 1];
     k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
-    const LaneRun<K> L = lane_run<K>(k, head_bits, res_aoff);
-    uint64_t prev = 0;
-    int64_t last = t;
+    const TableCopy tc = table_load(gtab);
+    uint64_t prev = 0, prev_f = 0;
+    int64_t last = t, first = t;
     if (wave == 0) {
         prev = lb_load(status + t * kLbWords);
         last = look_last[t];
+        if (RECOMPUTE) {
+            prev_f = lb_load(status_fwd + t * kLbWords);
+            first = look_fwd[t];
+        }
     }
-    // the window's inputs, and the upstream gradients (or targets) and
-    // coordinates into the stage, ahead of the table copy (which ends in a
-    // barrier) so that their latencies overlap
-    SpineAngles<K> a{};
-    if (RECOMPUTE && L.active) a = load_spine_angles<K>(ang, R, L.rs, L.cnt);
+    const LaneRun<K> L = lane_run<K>(k, head_bits, res_aoff);
     const LaneRes<K, RECOMPUTE> lr = load_lane_res<K, RECOMPUTE>(L, seq, res_aoff, ang, R);
-    const int planes = RECOMPUTE ? 3 : 6;
-    const Stage lds{stage_mem + (size_t)wave * planes * stage_atoms, stage_atoms};
-    if (STG && L.active) {
-        run_to_lds(lds, 0, g, A, L.A0, L.natoms);
-        if (!RECOMPUTE) run_to_lds(lds, 3, xyz, A, L.A0, L.natoms);
-    }
-    // the frame entering the window (wave 0; the aggregates are complete)
-    __shared__ float fcarry_sh[12];
-    if (RECOMPUTE && wave == 0) {
-        const uint32_t tag_f =
-            (uint32_t)(__builtin_amdgcn_readfirstlane((uint32_t)(lb_load(status_fwd + t * kLbWords) >> 32)));
-        const int64_t f = (int64_t)__builtin_amdgcn_readfirstlane(look_fwd[t]);
-        const Aff c = lb_carry_in(status_fwd, f, t, tag_f);
-        if (lane == 0) aff_store(fcarry_sh, c);
-    }
-    load_table(tab, gtab);
-    Aff X = aff_identity();
+    // the wave's upstream gradients (or targets): the first rows are under
+    // way during the spine scan
+    constexpr int planes = RECOMPUTE ? 3 : 6;
+    float *st = stage_mem + (size_t)wave * planes * stage_atoms;
+    float *stx = st + 3 * stage_atoms;  // coordinates (coordinate mode)
+    RunRows gr;
+    if (STG && L.active) gr = rows_load(g, A, L.A0, 0, L.natoms);
+    table_store(tab, tc);
+    Aff cur = aff_identity();
     ResidueIn in[K];
-    int first_head = K;
-    if (RECOMPUTE) {
-        Aff m = aff_identity();
-        if (L.active) m = fa_lane_aggregate<K>(a, L.cnt, L.hm, P, in, first_head);
-        Aff fcarry = aff_load(fcarry_sh);
-        X = block_exclusive_prefix<true>(m, first_head < K, k.nact, shf, fcarry);
+    if constexpr (RECOMPUTE) {
+        Aff unit = aff_identity();
+        if (L.active) {
+            lane_sincos<K>(lr, in);
+            unit = spine_unit<K>(in, L, P);
+        }
+        const int n_units = (int)((k.ce - k.cs + K - 1) / K);
+        cur = entering_frame(unit, L.hm != 0u, n_units, stage_mem, unit_flags, shf, fcarry_sh,
+                             status_fwd, t, first, prev_f, spined != 0);
+    }
+    __syncthreads();  // the stage takes the frames' place; the table is complete
+    if (STG && L.active) {
+        rows_to_lds(gr, st, 0, L.natoms);
+        run_to_lds_rest(st, g, A, L.A0, L.natoms);
+        if (!RECOMPUTE) {
+            rows_to_lds(rows_load(xyz, A, L.A0, 0, L.natoms), stx, 0, L.natoms);
+            run_to_lds_rest(stx, xyz, A, L.A0, L.natoms);
+        }
     }
     // the C atom before the lane's first residue (coordinate mode): in
     // the staged run for lanes > 0, from global memory for lane 0
@@ -744,121 +974,139 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     SpineGrad sp[K];
     Wrench agg = wrench_zero();
     bool f_end = false;
-    // upstream gradient (or target) sg, coordinates sx, positions out sout
-    const Stage sg = STG ? lds : Stage{const_cast<float *>(g) + L.A0, A};
-    const Stage sx = STG ? Stage{lds.st + 3 * lds.ns, lds.ns}
-                         : Stage{const_cast<float *>(xyz) + L.A0, A};
-    const Stage sout = STG ? sg : Stage{xyz_out + L.A0, A};
-    const bool write_so = STG || (GM == kGradMse && xyz_out != nullptr);
+    // upstream gradient (or target), coordinates in, positions out
+    const Atoms<STG> ga = STG ? Atoms<STG>{st, 0} : Atoms<STG>{const_cast<float *>(g) + L.A0, A};
+    const Atoms<STG> xa = STG ? Atoms<STG>{stx, 0} : Atoms<STG>{const_cast<float *>(xyz) + L.A0, A};
+    const Atoms<STG> oa = STG ? ga : Atoms<STG>{xyz_out + L.A0, A};
+    AtomForce<GM, STG> force{ga, oa, xyz_out != nullptr, 0.f};
     if (L.active) {
         wave_lds_sync();
         // first atom of the residue before the lane: the previous lane's last
         const int prev_aoff = __builtin_amdgcn_mov_dpp(lr.aoff[K - 1], kDppWaveShr1, 0xf, 0xf, true);
         if (!RECOMPUTE && lane > 0 && L.cnt > 0 && !(L.hm & 1u)) {
-            const int e = prev_aoff + 2 - (int)L.A0;
-            pcx = sx.st[e]; pcy = sx.st[sx.ns + e]; pcz = sx.st[2 * sx.ns + e];
+            const F3 p = xa.get(prev_aoff + 2 - (int)L.A0);
+            pcx = p.x; pcy = p.y; pcz = p.z;
         }
-        Aff cur = X;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             if (j < L.cnt) {
-                const FAType &ft = tab.t[lr.type[j]];
+                TypeAt ty = type_at(tab, lr.type[j]);
                 const int aloc = lr.aoff[j] - (int)L.A0;
                 const bool head = (L.hm >> j) & 1u;
                 // each group's wrench goes to the axes that move it once the
                 // residue is walked (N: every group; CA: its own, the side
                 // chain, C's; C: its own; side frame f: frames f and after)
-                SpineGrad g;
+                SpineGrad gq;
                 NodeGrad sc[A2C_MAX_SIDE_FRAMES];
                 Wrench wn = wrench_zero(), wca = wrench_zero(), wc = wrench_zero();
                 Wrench ws[A2C_MAX_SIDE_FRAMES];
-                if (RECOMPUTE) {
+                Wrench side = wrench_zero();  // starts as the last frame's extra atoms
+                if constexpr (RECOMPUTE) {
+                    auto into = [&](Wrench &w) {
+                        return [&](int e, float x, float y, float z) { force(w, e, x, y, z); };
+                    };
                     if (head) cur = aff_identity();
                     aff_apply_transform(cur, P.ct[0], P.st[0], P.d[0], in[j].co, in[j].so);
-                    g.n = node_of_frame(cur);
-                    if (GM == kGradMse) frame_wrench_mse(tab, ft, 0, cur, sg, sout, write_so, aloc, wn, loss);
-                    else frame_wrench(tab, ft, 0, cur, sg, aloc, wn);
+                    gq.n = node_of_frame(cur);
+                    force(wn, aloc, cur.t0, cur.t1, cur.t2);
+                    walk_extras(ty, extra_count(ty, 0), cur, aloc, into(wn));
                     aff_apply_transform(cur, P.ct[1], P.st[1], P.d[1], in[j].cp, in[j].sp);
-                    g.ca = node_of_frame(cur);
-                    if (GM == kGradMse) frame_wrench_mse(tab, ft, 1, cur, sg, sout, write_so, aloc, wca, loss);
-                    else frame_wrench(tab, ft, 1, cur, sg, aloc, wca);
-                    Aff sf = cur;
-                    aff_rot_x(sf, ft.pre_c, ft.pre_s);
+                    gq.ca = node_of_frame(cur);
+                    force(wca, aloc + 1, cur.t0, cur.t1, cur.t2);
+                    walk_extras(ty, extra_count(ty, 1), cur, aloc, into(wca));
+                    if (ty.n_side > 0) {
+                        Aff sf = cur;
+                        aff_rot_x(sf, ty.ft->pre_c, ty.ft->pre_s);
+                        int n_last = 0;
 #pragma unroll
-                    for (int f = 0; f < A2C_MAX_SIDE_FRAMES; ++f) {
-                        if (f < tab.max_side && f < ft.n_side) {
-                            side_step(sf, ft, f, lr.chi[j][f]);
-                            sc[f] = node_of_frame(sf);
-                            ws[f] = wrench_zero();
-                            if (GM == kGradMse) frame_wrench_mse(tab, ft, 3 + f, sf, sg, sout, write_so, aloc, ws[f], loss);
-                            else frame_wrench(tab, ft, 3 + f, sf, sg, aloc, ws[f]);
+                        for (int f = 0; f < A2C_MAX_SIDE_FRAMES; ++f) {
+                            if (f < ty.n_side) {
+                                side_step(sf, *ty.ft, f, lr.chi[j][f]);
+                                sc[f] = node_of_frame(sf);
+                                ws[f] = wrench_zero();
+                                force(ws[f], aloc + (int)((ty.origin >> (8 * f)) & 255u), sf.t0,
+                                      sf.t1, sf.t2);
+                                n_last = extra_count(ty, 2 + f);
+                                if (f + 1 < ty.n_side && n_last > 0)
+                                    walk_extras(ty, n_last, sf, aloc, into(ws[f]));
+                            }
                         }
+                        walk_extras(ty, n_last, sf, aloc, into(side));
                     }
                     aff_apply_transform(cur, P.ct[2], P.st[2], P.d[2], in[j].cs, in[j].ss);
-                    g.cc = node_of_frame(cur);
-                    if (GM == kGradMse) frame_wrench_mse(tab, ft, 2, cur, sg, sout, write_so, aloc, wc, loss);
-                    else frame_wrench(tab, ft, 2, cur, sg, aloc, wc);
+                    gq.cc = node_of_frame(cur);
+                    force(wc, aloc + 2, cur.t0, cur.t1, cur.t2);
+                    walk_extras(ty, extra_count(ty, 6), cur, aloc, into(wc));
                 } else {
-                    const float *px = sx.st, *py = sx.st + sx.ns, *pz = sx.st + 2 * sx.ns;
-                    const float nx = px[aloc], ny = py[aloc], nz = pz[aloc];
-                    const float cax = px[aloc + 1], cay = py[aloc + 1], caz = pz[aloc + 1];
-                    const float cx = px[aloc + 2], cy = py[aloc + 2], cz = pz[aloc + 2];
+                    auto add = [&](Wrench &w, int e) {
+                        const F3 p = xa.get(e), q = ga.get(e);
+                        wrench_add_point(w, p.x, p.y, p.z, q.x, q.y, q.z);
+                        return p;
+                    };
+                    auto extras = [&](int n, Wrench &w) {
+                        for (int i = 0; i < n; ++i) add(w, aloc + ty.ex[i].slot);
+                        ty.ex += n;
+                    };
+                    const F3 pn = add(wn, aloc);
+                    extras(extra_count(ty, 0), wn);
+                    const F3 pa = add(wca, aloc + 1);
+                    extras(extra_count(ty, 1), wca);
+                    const F3 pc = add(wc, aloc + 2);
                     if (head) { pcx = 0.f; pcy = 0.f; pcz = 0.f; }
-                    g.n = node_at(nx, ny, nz, (nx - pcx) * P.inv_d[0], (ny - pcy) * P.inv_d[0],
-                                  (nz - pcz) * P.inv_d[0]);
-                    g.ca = node_at(cax, cay, caz, (cax - nx) * P.inv_d[1],
-                                   (cay - ny) * P.inv_d[1], (caz - nz) * P.inv_d[1]);
-                    g.cc = node_at(cx, cy, cz, (cx - cax) * P.inv_d[2], (cy - cay) * P.inv_d[2],
-                                   (cz - caz) * P.inv_d[2]);
-                    frame_wrench_xyz(tab, ft, 0, sg, sx, aloc, wn);
-                    frame_wrench_xyz(tab, ft, 1, sg, sx, aloc, wca);
-                    float ppx = cax, ppy = cay, ppz = caz;
+                    gq.n = node_at(pn.x, pn.y, pn.z, (pn.x - pcx) * P.inv_d[0],
+                                   (pn.y - pcy) * P.inv_d[0], (pn.z - pcz) * P.inv_d[0]);
+                    gq.ca = node_at(pa.x, pa.y, pa.z, (pa.x - pn.x) * P.inv_d[1],
+                                    (pa.y - pn.y) * P.inv_d[1], (pa.z - pn.z) * P.inv_d[1]);
+                    gq.cc = node_at(pc.x, pc.y, pc.z, (pc.x - pa.x) * P.inv_d[2],
+                                    (pc.y - pa.y) * P.inv_d[2], (pc.z - pa.z) * P.inv_d[2]);
+                    F3 pp = pa;
+                    int n_last = 0;
 #pragma unroll
                     for (int f = 0; f < A2C_MAX_SIDE_FRAMES; ++f) {
-                        if (f < tab.max_side && f < ft.n_side) {
-                            const int eo = aloc + ft.origin_slot[3 + f];
-                            const float ox = px[eo], oy = py[eo], oz = pz[eo];
-                            sc[f] = node_at(ox, oy, oz, (ox - ppx) * ft.inv_d[f],
-                                            (oy - ppy) * ft.inv_d[f], (oz - ppz) * ft.inv_d[f]);
-                            ppx = ox; ppy = oy; ppz = oz;
+                        if (f < ty.n_side) {
+                            const float inv = (&ty.ft->inv_d.x)[f];
                             ws[f] = wrench_zero();
-                            frame_wrench_xyz(tab, ft, 3 + f, sg, sx, aloc, ws[f]);
+                            const F3 o = add(ws[f], aloc + (int)((ty.origin >> (8 * f)) & 255u));
+                            sc[f] = node_at(o.x, o.y, o.z, (o.x - pp.x) * inv, (o.y - pp.y) * inv,
+                                            (o.z - pp.z) * inv);
+                            pp = o;
+                            n_last = extra_count(ty, 2 + f);
+                            if (f + 1 < ty.n_side && n_last > 0) extras(n_last, ws[f]);
                         }
                     }
-                    frame_wrench_xyz(tab, ft, 2, sg, sx, aloc, wc);
-                    pcx = cx; pcy = cy; pcz = cz;
+                    extras(n_last, side);
+                    extras(extra_count(ty, 6), wc);
+                    pcx = pc.x; pcy = pc.y; pcz = pc.z;
                 }
                 // side frame f moves frames f and after: their wrench, summed
                 // from the last frame back, folds into each axis once
-                Wrench side = wrench_zero();
 #pragma unroll
                 for (int f = A2C_MAX_SIDE_FRAMES - 1; f >= 0; --f) {
-                    if (f < tab.max_side && f < ft.n_side) {
+                    if (f < ty.n_side) {
                         wrench_add(side, ws[f]);
                         node_fold(sc[f], side);
                     }
                 }
-                node_fold(g.cc, wc);      // C: the C group (with O)
+                node_fold(gq.cc, wc);      // C: the C group (with O)
                 wrench_add(wca, side);
                 wrench_add(wca, wc);
-                node_fold(g.ca, wca);     // CA: its group, the side chain, the C group
-                g.W = wn;
-                wrench_add(g.W, wca);
-                node_fold(g.n, g.W);      // N: the whole residue
+                node_fold(gq.ca, wca);     // CA: its group, the side chain, the C group
+                gq.W = wn;
+                wrench_add(gq.W, wca);
+                node_fold(gq.n, gq.W);     // N: the whole residue
                 // chi gradients are complete here (their subtrees end in the residue)
 #pragma unroll
                 for (int f = 0; f < A2C_MAX_SIDE_FRAMES; ++f)
                     grad_store(&gang[(3 + f) * R + L.rs + j],
-                               (f < tab.max_side && f < ft.n_side && ft.side_chi[f]) ? sc[f].c : 0.f,
-                               nt != 0);
-                sp[j] = g;
-                if (!f_end) wrench_add(agg, g.W);
+                               (f < ty.n_side && ty.ft->fr[f].w != 0.f) ? sc[f].c : 0.f, nt != 0);
+                sp[j] = gq;
+                if (!f_end) wrench_add(agg, gq.W);
                 if ((L.lm >> j) & 1u) f_end = true;
             }
         }
         wave_lds_sync();
         if (STG && GM == kGradMse && xyz_out) {
-            lds_to_run(sg, xyz_out, A, L.A0, L.natoms);  // the stage now holds r
+            lds_to_run(st, xyz_out, A, L.A0, L.natoms);  // the stage now holds r
             wave_lds_sync();
         }
     }
@@ -874,14 +1122,15 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
         }
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) lb_loss_commit(loss, status, t, gridDim.x, prev, loss_out, loss_tot);
+        if (loss_out) lb_loss_commit(force.loss, status, t, gridDim.x, prev, loss_out, loss_tot);
     }
 }
 
 template <int K, int LB, bool STG>
 hipError_t fa_fwd_kl(const a2c_plan &p, const float *ang, float *xyz, hipStream_t s)
 {
-    const size_t lds = STG ? (size_t)p.fs.W * 3 * p.fs.fa_stage_atoms * sizeof(float) : 0;
+    const size_t stage = STG ? (size_t)p.fs.W * 3 * p.fs.fa_stage_atoms * sizeof(float) : 0;
+    const size_t lds = std::max(stage, frame_bytes(p.fs.W));
     hipLaunchKernelGGL((fa_forward_flat_kernel<K, LB, STG>), dim3(p.fs.n_win), dim3(p.fs.W * kWave),
                        lds, s, ang, xyz, p.d_head_bits, p.fs.d_wstart, p.d_res_atom_off, p.d_seq,
                        p.d_fa, p.fs.d_look, p.fs.d_status, p.R, p.A, p.bb, p.fs.fa_stage_atoms);
@@ -908,17 +1157,17 @@ template <int K, bool RECOMPUTE, int LB, int GM, bool STG>
 void fa_bwd_launch(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
                    float *gang, hipStream_t s, float *xyz_out, float *loss_out)
 {
-    // whole-chain windows start at a chain head: none needs the spine pass
-    if (RECOMPUTE && !p.bs.whole_chains)
-        launch_spine_pass(ang, p.d_head_bits, p.bs, p.R, p.bb, s);
-    const size_t lds =
-        STG ? (size_t)p.bs.W * (RECOMPUTE ? 3 : 6) * p.bs.fa_stage_atoms * sizeof(float) : 0;
-    hipLaunchKernelGGL((fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, STG>), dim3(p.bs.n_win),
-                       dim3(p.bs.W * kWave), lds, s, ang, xyz, g, gang, xyz_out, loss_out,
-                       p.d_head_bits, p.bs.d_wstart, p.d_res_atom_off,
-                       p.d_seq, p.d_fa, p.bs.d_status_fwd, p.bs.d_look_fwd, p.bs.d_look,
-                       p.bs.d_status, p.R, p.A, p.bb, p.bs.fa_stage_atoms,
-                       p.bs.whole_chains ? 0 : 1, p.nt_grad ? 1 : 0);
+    const Sched &S = p.bs;
+    const bool spined = RECOMPUTE && S.spined;
+    if (spined) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
+    size_t lds = STG ? (size_t)S.W * (RECOMPUTE ? 3 : 6) * S.fa_stage_atoms * sizeof(float) : 0;
+    if (RECOMPUTE) lds = std::max(lds, frame_bytes(S.W));
+    const bool rev = RECOMPUTE ? spined : !S.whole_chains;
+    hipLaunchKernelGGL((fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, STG>), dim3(S.n_win),
+                       dim3(S.W * kWave), lds, s, ang, xyz, g, gang, xyz_out, loss_out,
+                       p.d_head_bits, S.d_wstart, p.d_res_atom_off, p.d_seq, p.d_fa,
+                       S.d_status_fwd, S.d_look_fwd, S.d_look, S.d_status, p.R, p.A, p.bb,
+                       S.fa_stage_atoms, rev ? 1 : 0, spined ? 1 : 0, p.nt_grad ? 1 : 0);
 }
 
 // mode 0: adjoint from coordinates, 1: recompute, 2: fused squared-distance step

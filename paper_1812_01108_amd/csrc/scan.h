@@ -1,18 +1,19 @@
 // Block-level segmented scans shared by the backbone and full-atom kernels.
 //
-// A workgroup of W waves owns one tile: a residue range [ts, te) holding
-// whole chains; lane t of the block owns K consecutive residues starting at
-// ts + t*K.  Chain heads come from a bit array (bit r set when residue r
+// A workgroup of W waves owns one window or tile: a residue range [ts, te);
+// lane t of the block owns K consecutive residues starting at ts + t*K.
+// Chain heads come from a bit array (bit r set when residue r
 // starts a chain; bit R is set too).
 //   - forward: segmented exclusive prefix product of per-lane 3x4 affine
 //     aggregates, (fa, A) . (fb, B) = (fa | fb, fb ? B : A B);
 //   - adjoint: segmented exclusive suffix sum of per-lane wrenches
 //     (force, moment), reset at chain ends.
-// A workgroup walks its tile in chunks of 64 W K residues and carries the
-// scan state from chunk to chunk.  Inside a chunk each scan is a 6-step DPP
-// scan inside the wave, then a scan of the wave totals: for the prefix
-// product and the suffix sum alike, wave 0 scans them between two
-// workgroup barriers and every wave reads the value it needs from LDS.
+// Each scan is a 6-step DPP scan inside the wave, then a scan of the wave
+// totals: for the prefix product and the suffix sum alike, wave 0 scans them
+// between two workgroup barriers and every wave reads the value it needs from
+// LDS.  Windows hand the state on through device memory (below); a workgroup
+// that walks a tile in chunks of 64 W K residues carries it from chunk to
+// chunk.
 #pragma once
 #include "a2c_internal.h"
 #include "affine.h"
@@ -271,7 +272,7 @@ __device__ __forceinline__ void aff_wave_scan(Aff &m, uint64_t heads, int n, int
 //            chain head; identity for an empty lane) and "a chain starts in
 //            this lane";
 //   nact     waves of the block holding residues of this chunk (a prefix);
-//   carry    (MULTI only) in: the frame after everything of the tile before
+//   carry    in: the frame after everything of the tile before
 //            this chunk (identity for the first chunk: tiles start at a chain
 //            head); out: the frame after this chunk, identical in every wave,
 //            also in waves idle in this chunk.
@@ -279,14 +280,11 @@ __device__ __forceinline__ void aff_wave_scan(Aff &m, uint64_t heads, int n, int
 // the lane's residues before its first chain head).  Every thread of the
 // block calls this.  Each wave scans its lanes; wave 0 alone then scans the
 // wave totals (two barriers) and every wave reads the prefix it needs.
-// MULTI = false: the tile is one chunk and the carry is neither read nor
-// written.
-template <bool MULTI>
 __device__ __forceinline__ Aff block_exclusive_prefix(Aff m, bool f, int nact, FwdShared &sh,
                                                       Aff &carry)
 {
-    // opaque inside chunk loops (MULTI), so lane masks are not hoisted out
-    const int lane = MULTI ? lane_id() : (int)(threadIdx.x & 63);
+    // opaque inside the chunk loop, so lane masks are not hoisted out
+    const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool wave_active = wave < nact;
     const uint64_t heads = __builtin_amdgcn_ballot_w64(f);
@@ -297,34 +295,28 @@ __device__ __forceinline__ Aff block_exclusive_prefix(Aff m, bool f, int nact, F
             sh.tot_flag[wave] = heads != 0ull ? 1 : 0;
         }
     }
-    // the wave totals' inclusive prefixes, by wave 0 (block-uniform branch)
-    if (MULTI || nact > 1) {
-        __syncthreads();
-        if (wave == 0) {
-            Aff t = aff_identity();
-            bool tf = false;
-            if (lane < nact) {
-                t = aff_load(sh.tot[lane]);
-                tf = sh.tot_flag[lane] != 0;
-            }
-            const uint64_t th = __builtin_amdgcn_ballot_w64(tf);
-            aff_wave_scan<true>(t, th, nact, lane);
-            if (lane < nact) {
-                aff_store(sh.pre[lane], t);
-                sh.pre_flag[lane] = (th & lanes_upto(lane)) != 0ull ? 1 : 0;
-            }
+    // the wave totals' inclusive prefixes, by wave 0
+    __syncthreads();
+    if (wave == 0) {
+        Aff t = aff_identity();
+        bool tf = false;
+        if (lane < nact) {
+            t = aff_load(sh.tot[lane]);
+            tf = sh.tot_flag[lane] != 0;
         }
-        __syncthreads();
+        const uint64_t th = __builtin_amdgcn_ballot_w64(tf);
+        aff_wave_scan<true>(t, th, nact, lane);
+        if (lane < nact) {
+            aff_store(sh.pre[lane], t);
+            sh.pre_flag[lane] = (th & lanes_upto(lane)) != 0ull ? 1 : 0;
+        }
     }
-    // carry-in of this wave (identity for wave 0 of a one-chunk tile)
-    Aff cw = aff_identity();
-    if (MULTI) cw = carry;
-    if (wave_active && wave > 0) {
-        const Aff p = aff_load(sh.pre[wave - 1]);
-        const bool pf = sh.pre_flag[wave - 1] != 0;
-        cw = MULTI ? aff_seg_after(carry, p, pf) : p;
-    }
-    if (MULTI) {  // every wave advances the carry, also one idle in this chunk
+    __syncthreads();
+    // carry-in of this wave
+    Aff cw = carry;
+    if (wave_active && wave > 0)
+        cw = aff_seg_after(carry, aff_load(sh.pre[wave - 1]), sh.pre_flag[wave - 1] != 0);
+    {  // every wave advances the carry, also one idle in this chunk
         const Aff p = aff_load(sh.pre[nact - 1]);
         const bool pf = sh.pre_flag[nact - 1] != 0;
         carry = aff_uniform(aff_seg_after(carry, p, pf));
@@ -410,7 +402,7 @@ __device__ __forceinline__ Wrench wrench_load(const float *src)
 // last to first.
 //   agg, f   lane aggregate (sum over the lane's atoms up to and including
 //            its first chain end) and "a chain ends in this lane";
-//   carry    (MULTI only) in: the wrench of what follows this chunk up to the
+//   carry    in: the wrench of what follows this chunk up to the
 //            end of the chain its last residue belongs to (zero for the last
 //            chunk: tiles end at a chain end); out: the same for the previous
 //            chunk, also in waves idle in this chunk (the last chunk, visited
@@ -420,12 +412,11 @@ __device__ __forceinline__ Wrench wrench_load(const float *src)
 // residue ends its chain).  Every thread of the block calls this.  Each wave
 // scans its lanes; wave 0 alone then scans the wave totals (two barriers)
 // and every wave reads the suffix it needs.
-template <bool MULTI>
 __device__ __forceinline__ Wrench block_exclusive_suffix(Wrench agg, bool f, int nact,
                                                          BwdShared &sh, Wrench &carry)
 {
-    // opaque inside chunk loops (MULTI), so lane masks are not hoisted out
-    const int lane = MULTI ? lane_id() : (int)(threadIdx.x & 63);
+    // opaque inside the chunk loop, so lane masks are not hoisted out
+    const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool wave_active = wave < nact;
     const uint64_t ends = __builtin_amdgcn_ballot_w64(f);
@@ -436,34 +427,31 @@ __device__ __forceinline__ Wrench block_exclusive_suffix(Wrench agg, bool f, int
             sh.tot_flag[wave] = ends != 0ull ? 1 : 0;
         }
     }
-    // the wave totals' inclusive suffixes, by wave 0 (block-uniform branch)
-    if (MULTI || nact > 1) {
-        __syncthreads();
-        if (wave == 0) {
-            Wrench t = wrench_zero();
-            bool tf = false;
-            if (lane < nact) {
-                t = wrench_load(sh.tot[lane]);
-                tf = sh.tot_flag[lane] != 0;
-            }
-            const uint64_t th = __builtin_amdgcn_ballot_w64(tf);
-            wrench_wave_rscan<true>(t, th, nact, lane);
-            if (lane < nact) {
-                wrench_store(sh.suf[lane], t);
-                sh.suf_flag[lane] = (th & (~0ull << lane)) != 0ull ? 1 : 0;
-            }
+    // the wave totals' inclusive suffixes, by wave 0
+    __syncthreads();
+    if (wave == 0) {
+        Wrench t = wrench_zero();
+        bool tf = false;
+        if (lane < nact) {
+            t = wrench_load(sh.tot[lane]);
+            tf = sh.tot_flag[lane] != 0;
         }
-        __syncthreads();
+        const uint64_t th = __builtin_amdgcn_ballot_w64(tf);
+        wrench_wave_rscan<true>(t, th, nact, lane);
+        if (lane < nact) {
+            wrench_store(sh.suf[lane], t);
+            sh.suf_flag[lane] = (th & (~0ull << lane)) != 0ull ? 1 : 0;
+        }
     }
-    // carry into this wave from the waves after it (and, MULTI, later chunks)
-    Wrench cw = wrench_zero();
-    if (MULTI) cw = carry;
+    __syncthreads();
+    // carry into this wave from the waves after it and later chunks
+    Wrench cw = carry;
     if (wave_active && wave + 1 < nact) {
         Wrench p = wrench_load(sh.suf[wave + 1]);
-        if (MULTI && sh.suf_flag[wave + 1] == 0) wrench_add(p, carry);
+        if (sh.suf_flag[wave + 1] == 0) wrench_add(p, carry);
         cw = p;
     }
-    if (MULTI) {  // every wave advances the carry, also one idle in this chunk
+    {  // every wave advances the carry, also one idle in this chunk
         Wrench p = wrench_load(sh.suf[0]);
         if (sh.suf_flag[0] == 0) wrench_add(p, carry);
         carry = p;
@@ -687,8 +675,9 @@ __device__ __forceinline__ int64_t reverse_window(int64_t b, int64_t n)
 // tile reads the aggregates of the tiles back to the one holding that head
 // (a host table) and composes them in order.  Each tile publishes before it
 // reads, so no wait depends on another wait; a tile only waits on tiles of
-// lower index, which start no later than it does (the adjoints, which wait on
-// later windows, take them in reverse: reverse_window).  Words are written and
+// lower index, which start no later than it does.  The adjoints, which wait on
+// later windows, take them in reverse (reverse_window) where they wait on
+// nothing else, and otherwise in order, looking at most kMaxAhead ahead.  Words are written and
 // read with relaxed device-scope atomics (each word carries its own tag, so
 // no ordering between words is needed).  The tag of a launch is one more than
 // the one a tile finds in its own words (all tiles start from 0 and every

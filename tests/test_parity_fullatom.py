@@ -153,6 +153,46 @@ def test_homopolymers(code):
         _check(plan, off, seq, ang, mode, label=f"poly-{code}")
 
 
+@pytest.mark.parametrize("mode", ["coords", "recompute"])
+def test_extra_atoms_in_any_frame(mode, tmp_path, monkeypatch):
+    """A residue table with atoms off the origin in every frame: N and CA,
+    side frames before the last one (two in the first), and the last one.  The
+    default table has such atoms in C and, but for one, in last frames only."""
+    import json
+    from oracle import residue_table as rt
+    from paper_1812_01108_amd.residues import ResidueTable
+    a2c = _a2c()
+    from workloads import ALPHABET
+    with open(rt.default_path()) as f:
+        spec = json.load(f)
+
+    def atom(name, frame, azimuth):
+        return {"name": name, "frame": frame, "kind": "azimuth", "bond": 1.05, "angle": 109.0,
+                "azimuth": azimuth}
+
+    for code, res in spec["residues"].items():
+        if code == "GLY":
+            res["atoms"] += [atom("H", "N", 180.0), atom("HA", "CA", 120.0),
+                             atom("HB", "CA", -120.0)]
+        elif code == "LYS":
+            res["atoms"] = ([atom("HB", "CB", 120.0)] + res["atoms"]
+                            + [atom("HC", "CB", -120.0), atom("HG", "CG", 120.0),
+                               atom("HD", "CD", 110.0), atom("H", "N", 180.0)])
+        elif code == "ALA":
+            res["atoms"] += [atom("HB1", "CB", 60.0), atom("HB2", "CB", 180.0),
+                             atom("HA", "CA", 120.0)]
+    path = tmp_path / "residues.json"
+    path.write_text(json.dumps(spec))
+    oracle.load_residue_table()
+    monkeypatch.setattr(oracle, "_FA", rt.load(str(path)))
+    seq = [ALPHABET.index(c) for c in "GKAWRKIGVFKA"] * 25
+    off, seq, ang = _batch([131, 1, 64, 104], 131, seq=seq)
+    for K, W in [(1, 1), (1, 3), (2, 1)]:
+        plan = a2c.Plan("fullatom", offsets=off, seq=seq, table=ResidueTable(str(path)))
+        plan.set_schedule(K, W)
+        _check(plan, off, seq, ang, mode, label=f"extra atoms K={K} W={W}")
+
+
 @pytest.mark.parametrize("name", ["fullatom_64x300", "ragged_fullatom_512"])
 def test_full_size_workloads(name):
     a2c = _a2c()
