@@ -16,6 +16,7 @@ constexpr int kMaxChunks = 64;        // chunks of 64 W K residues per tile
 // dynamic LDS allowed to the full-atom kernels (160 KB per workgroup on
 // gfx950, less the static tables)
 constexpr int kMaxDynamicLds = 136 * 1024;
+constexpr size_t kCuLds = 160 * 1024;  // LDS of a compute unit
 // Launch-bound classes of the scan kernels: up to 8 waves per workgroup
 // (512 lanes) a kernel may use up to 256 VGPRs without spilling; 16 waves
 // cap it at 128.  Launchers pick the class from the schedule's wave count.
@@ -94,13 +95,14 @@ constexpr int kMaxAhead = 31;
 //     backbone adjoint that recomputes the frames).  They hold whole chains
 //     where every chain fits in one and that packs well, and are fixed,
 //     [t C, t C + C), otherwise;
-//   - own windows (that adjoint, and the backbone fused step where the
-//     windows hold whole chains): whole chains wherever every chain fits in
-//     one;
-//   - tiles (that adjoint where a chain is longer than a chunk): chains of at
-//     most one chunk packed whole, a longer chain alone.
+//   - own windows (the backbone fused step): whole chains wherever every chain
+//     fits in one;
+//   - for that adjoint, whose chunk may differ (rec_K, rec_W: the default
+//     schedule's choice), windows of whole chains as well, or, where a chain
+//     is longer than a chunk, tiles: chains of at most one chunk packed whole,
+//     a longer chain alone.
 // n_tiles counts the layout the schedule reports: windows, or for the
-// backbone adjoint own windows or tiles.
+// backbone adjoint that last one.
 struct Sched {
     int32_t K = 4, W = 4, n_tiles = 0;
     int32_t n_win = 0;                   // windows (0: none)
@@ -122,7 +124,11 @@ struct Sched {
     int32_t n_own = 0;                   // own windows
     int32_t *d_own_wstart = nullptr;     // n_own + 1 boundaries
     uint64_t *d_own_status = nullptr;    // n_own x kLbWords tagged words (loss shares)
-    int32_t *d_tile_res = nullptr;       // n_tiles (first, end) residue pairs, longest first
+    int32_t rec_K = 4, rec_W = 4;        // backbone adjoint that recomputes the frames
+    bool rec_chunked = false;            // tiles, a chain longer than a chunk
+    int32_t n_rec = 0;                   // its windows or tiles
+    int32_t *d_rec_wstart = nullptr;     // n_rec + 1 boundaries
+    int32_t *d_tile_res = nullptr;       // n_rec (first, end) residue pairs, longest first
 };
 
 }  // namespace a2c

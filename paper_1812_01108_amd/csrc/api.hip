@@ -43,12 +43,13 @@ a2c_status upload(void **dst, const void *src, size_t bytes, hipStream_t s)
 std::vector<void *> sched_tables(const Sched &S)
 {
     return {S.d_tile_res, S.d_wstart,     S.d_look,      S.d_status, S.d_look_fwd, S.d_status_fwd,
-            S.d_own_wstart, S.d_own_status};
+            S.d_own_wstart, S.d_own_status, S.d_rec_wstart};
 }
 
 void forget_tables(Sched &S)
 {
     S.d_tile_res = S.d_wstart = S.d_look = S.d_look_fwd = S.d_own_wstart = nullptr;
+    S.d_rec_wstart = nullptr;
     S.d_status = S.d_status_fwd = S.d_own_status = nullptr;
 }
 
@@ -188,8 +189,10 @@ std::vector<int32_t> pack_tiles(const std::vector<int32_t> &off, int64_t cap)
 // Layouts of a schedule (see Sched).
 enum SchedRole { kRoleForward, kRoleAdjoint };
 
+// rec_K, rec_W: the chunk of the backbone adjoint that recomputes the frames
+// (0: the schedule's own).
 a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipStream_t s,
-                       SchedRole role)
+                       SchedRole role, int32_t rec_K = 0, int32_t rec_W = 0)
 {
     const int64_t cap = (int64_t)kWave * W * K;  // residues per chunk
     if (p->max_len > cap * kMaxChunks)
@@ -232,27 +235,37 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
     if (st == A2C_OK && !fwd && p->model == A2C_BACKBONE && p->R > 0) {
         const std::vector<int64_t> own = whole_chain_starts(p, cap);
         if (!own.empty()) {
-            S.n_tiles = S.n_own = (int32_t)own.size() - 1;
+            S.n_own = (int32_t)own.size() - 1;
             st = upload_starts(own, S.d_own_wstart, s);
             if (st == A2C_OK) st = new_words(S.d_own_status, S.n_own, s);
-        } else {
+        }
+        S.rec_K = rec_K > 0 ? rec_K : K;
+        S.rec_W = rec_K > 0 ? rec_W : W;
+        const int64_t rec_cap = (int64_t)kWave * S.rec_W * S.rec_K;
+        const std::vector<int64_t> rec = whole_chain_starts(p, rec_cap);
+        S.rec_chunked = rec.empty();
+        if (st == A2C_OK && !S.rec_chunked) {
+            S.n_rec = (int32_t)rec.size() - 1;
+            st = upload_starts(rec, S.d_rec_wstart, s);
+        } else if (st == A2C_OK) {
             // (first, end) residue pairs, longest tile first: tiles are
             // independent, and dispatching the long ones first keeps them out
             // of the tail of the launch
-            const std::vector<int32_t> tiles = pack_tiles(p->res_off, cap);
-            S.n_tiles = (int32_t)tiles.size() - 1;
-            std::vector<int32_t> order(S.n_tiles);
-            for (int32_t t = 0; t < S.n_tiles; ++t) order[t] = t;
+            const std::vector<int32_t> tiles = pack_tiles(p->res_off, rec_cap);
+            S.n_rec = (int32_t)tiles.size() - 1;
+            std::vector<int32_t> order(S.n_rec);
+            for (int32_t t = 0; t < S.n_rec; ++t) order[t] = t;
             std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
                 return tiles[a + 1] - tiles[a] > tiles[b + 1] - tiles[b];
             });
-            std::vector<int32_t> pairs(2 * (size_t)S.n_tiles);
-            for (int32_t t = 0; t < S.n_tiles; ++t) {
+            std::vector<int32_t> pairs(2 * (size_t)S.n_rec);
+            for (int32_t t = 0; t < S.n_rec; ++t) {
                 pairs[2 * t] = tiles[order[t]];
                 pairs[2 * t + 1] = tiles[order[t] + 1];
             }
             st = upload((void **)&S.d_tile_res, pairs.data(), pairs.size() * sizeof(int32_t), s);
         }
+        S.n_tiles = S.n_rec;
     }
     // the host tables above are read by the copies until here
     const hipError_t e = hipStreamSynchronize(s);
@@ -314,20 +327,123 @@ a2c_status apply_schedule(a2c_plan *p, int32_t K, int32_t W, hipStream_t s,
     return A2C_OK;
 }
 
-// One chunk per chain where a 16-wave chunk holds it; full-atom keeps four
-// waves so the per-wave atom staging stays small, and widens the chunk only
-// when its longest chain would need more than kMaxChunks chunks.
-void default_schedule(const a2c_plan &p, int32_t &K, int32_t &W)
+// ------------------------------------------------------ default schedules
+// Rules on the batch's residues R and longest chain, from timing every
+// schedule on batches of 150 to 3 M residues (one MI355X, launches back to
+// back in a graph; microseconds below).  Few residues want few per lane (the
+// walk over them is a serial chain, and waves are short in supply), many want
+// more (the wave scan costs the same whatever a lane holds).
+
+struct Shape {
+    int32_t K, W;
+};
+
+int32_t waves_for(int64_t len, int32_t K)
 {
-    K = p.model == A2C_BACKBONE ? 4 : 1;
-    const int64_t per_wave = (int64_t)kWave * K;
-    const int64_t wmax = p.model == A2C_BACKBONE ? kMaxWaves : 4;
-    W = (int32_t)std::min<int64_t>(wmax, std::max<int64_t>(1, (p.max_len + per_wave - 1) / per_wave));
-    while ((int64_t)p.max_len > (int64_t)kWave * W * K * kMaxChunks) {
-        if (W < kMaxWaves) W = std::min<int32_t>(kMaxWaves, 2 * W);
-        else if (K < 2) K = 2;
-        else break;  // plan_create has already rejected longer chains
+    return (int32_t)std::max<int64_t>(1, (len + (int64_t)kWave * K - 1) / (kWave * K));
+}
+
+// The fewest waves, from `least` to `most`, at which windows of whole chains
+// are no more than the device has CUs (one round, nothing handed over);
+// `least` where none is.  1000 chains of 100, K = 1: adjoint 5.9 at W = 2, 4.6
+// at W = 8; full-atom forward 11.5 and 10.8.
+int32_t pack_waves(const a2c_plan &p, int32_t K, int32_t least, int32_t most)
+{
+    for (int32_t W = least; W <= most; ++W) {
+        const std::vector<int64_t> st = whole_chain_starts(&p, (int64_t)kWave * K * W);
+        if (!st.empty() && (int64_t)st.size() - 1 <= p.n_cu) return W;
     }
+    return least;
+}
+
+Shape default_forward(const a2c_plan &p)
+{
+    const int64_t R = p.R;
+    if (p.model == A2C_FULLATOM) {
+        // one residue per lane; four waves (eight for batches of several
+        // rounds: 150 chains of 1000..6000 29.9 and 28.3, 4096 of 50..2000
+        // 124.7 and 119.9; 2000 of 151 23.2 and 24.2), and one window for a
+        // chain of up to 512 where that fits one round (64 x 300: 10.5 at
+        // W = 4, 9.2 at W = 6)
+        const int32_t whole = waves_for(p.max_len, 1);
+        const int32_t W = std::min<int32_t>(R > 400000 ? 8 : 4, whole);
+        return {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : W};
+    }
+    // a batch of a few chunks keeps a chunk that holds its longest chain
+    if (p.max_len > 1024 && p.max_len <= 4096 && R <= 4 * 4096) return {4, waves_for(p.max_len, 4)};
+    // 150 residues 7.0 at K = 4, 4.6 at K = 1; 256 x 700 8.4 at (4, 3), 7.3 at
+    // (2, 6); 700 chains of 20..1000 10.5 at (4, 4), 10.1 at (2, 12); 1500 of
+    // them 13.1 at (4, 4), 15.0 at (2, 8)
+    const int32_t K = R <= 16384 ? 1 : R <= 393216 ? 2 : 4;
+    const int32_t whole = waves_for(p.max_len, K);
+    // a chain of more waves than this is handed between smaller windows
+    // instead: 48 chains of 1500..6000 12.5 at (4, 16), 8.6 at (2, 8); 8 of
+    // 1500..4000 11.3 and 6.8 at (1, 4)
+    const int32_t most = K == 1 ? 16 : K == 2 ? 8 : 4;
+    if (whole > most) return {K, K == 2 ? 8 : 4};
+    return {K, pack_waves(p, K, whole, most)};
+}
+
+Shape default_adjoint(const a2c_plan &p, Shape &rec)
+{
+    const int64_t R = p.R;
+    if (p.model == A2C_FULLATOM) {
+        // as the forward, but four waves for large batches too (4096 chains,
+        // recomputing: 141.5 and 145.7 at W = 8)
+        const int32_t whole = waves_for(p.max_len, 1);
+        rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : 4};
+        if (rec.W > 4 && (int64_t)kWave * rec.W * p.n_cu < R) rec.W = 4;
+        return rec;
+    }
+    // from coordinates: 256 x 700 7.2 at (4, 3), 5.2 at (1, 12); 700 chains of
+    // 20..1000 9.2 at (4, 4), 8.3 at (2, 8); 6000 of them 41.4 and 41.9 at
+    // (4, 8), which takes the recomputing adjoint from 57.7 to 51.1 (packing
+    // whole chains leaves 12 % of its lanes idle instead of 26)
+    Shape s;
+    s.K = R <= 196608 ? 1 : R <= 524288 ? 2 : 4;
+    const int32_t whole = waves_for(p.max_len, s.K);
+    const int32_t most = s.K == 1 ? 16 : 8;
+    if (s.K == 4) s.W = 8;
+    else if (whole <= most) s.W = pack_waves(p, s.K, whole, most);
+    // long chains: 48 of 1500..6000, from coordinates 10.7 at (4, 16), 6.6 at
+    // (2, 8), fused step 22.1 and 14.6; 8 of 1500..4000, 5.3 and 11.6 at (1, 4)
+    else if (R <= 65536) s.W = 4;
+    else s = {2, 8};
+    // the adjoint that recomputes the frames hands nothing over: a chunk that
+    // holds the longest chain, up to 4096, and beyond that the one whose
+    // chunk walk is fastest (48 chains of 1500..6000: 73 at (4, 16), which
+    // spills, 46 at (4, 8), 66 at (2, 8))
+    if (waves_for(p.max_len, s.K) <= most) rec = s;
+    else if (p.max_len <= 4096) rec = {4, std::max(waves_for(p.max_len, 4), 4)};
+    else rec = {4, 8};
+    if (waves_for(p.max_len, rec.K) > rec.W && p.max_len <= 4096)
+        rec.W = waves_for(p.max_len, rec.K);
+    return s;
+}
+
+// The most residues a chain may have under `s` is kMaxChunks chunks: more
+// waves, then more residues per lane, until the longest chain fits
+// (plan_create has already rejected longer ones).
+void fit_longest(const a2c_plan &p, Shape &s, int32_t most_K)
+{
+    while ((int64_t)p.max_len > (int64_t)kWave * s.W * s.K * kMaxChunks) {
+        if (s.W < kMaxWaves) s.W = std::min<int32_t>(kMaxWaves, 2 * s.W);
+        else if (s.K < most_K) s.K *= 2;
+        else break;
+    }
+}
+
+a2c_status default_schedules(a2c_plan *p, hipStream_t s)
+{
+    const int32_t most_K = p->model == A2C_BACKBONE ? 4 : 2;
+    Shape rec{};
+    Shape f = default_forward(*p), b = default_adjoint(*p, rec);
+    fit_longest(*p, f, most_K);
+    fit_longest(*p, b, most_K);
+    fit_longest(*p, rec, most_K);
+    a2c_status st = build_sched(p, f.K, f.W, p->fs, s, kRoleForward);
+    if (st == A2C_OK) st = build_sched(p, b.K, b.W, p->bs, s, kRoleAdjoint, rec.K, rec.W);
+    return st;
 }
 
 bool check_device(const a2c_plan *p)
@@ -602,9 +718,7 @@ a2c_status a2c_plan_create(a2c_plan **out, int32_t model_id, int32_t n_chains,
         else bb_allow_large_lds();
     }
     if (st == A2C_OK) {
-        int32_t K, W;
-        default_schedule(*p, K, W);
-        st = apply_schedule(p, K, W, s);
+        st = default_schedules(p, s);
     }
     if (st != A2C_OK) {
         a2c_plan_destroy(p);

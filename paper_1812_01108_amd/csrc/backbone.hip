@@ -944,19 +944,20 @@ hipError_t bwd_kl(const a2c_plan &p, const float *ang, const float *xyz, const f
                   float *gang, hipStream_t s)
 {
     const Sched &S = p.bs;
-    const dim3 block(S.W * kWave);
-    const size_t lds = stage_bytes<K>(S.W);
+    const int W = xyz ? S.W : S.rec_W;
+    const dim3 block(W * kWave);
+    const size_t lds = stage_bytes<K>(W);
     if (xyz)
         hipLaunchKernelGGL((bb_backward_coords_flat_kernel<K, LB>), dim3(S.n_win), block, lds, s,
                            xyz, g, gang, p.d_head_bits, S.d_wstart, S.d_look, S.d_status, p.R, p.bb,
                            S.whole_chains ? 0 : 1, p.nt_grad ? 1 : 0);
-    else if (S.n_own)
+    else if (!S.rec_chunked)
         hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradLoad, false>),
-                           dim3(S.n_own), block, lds, s, ang, g, gang, nullptr, nullptr,
-                           p.d_head_bits, S.d_own_wstart, nullptr, nullptr, nullptr, nullptr, p.R,
+                           dim3(S.n_rec), block, lds, s, ang, g, gang, nullptr, nullptr,
+                           p.d_head_bits, S.d_rec_wstart, nullptr, nullptr, nullptr, nullptr, p.R,
                            p.bb, 0, p.nt_grad ? 1 : 0);
     else
-        hipLaunchKernelGGL((bb_backward_chunked_kernel<K, LB>), dim3(S.n_tiles), block, lds, s, ang,
+        hipLaunchKernelGGL((bb_backward_chunked_kernel<K, LB>), dim3(S.n_rec), block, lds, s, ang,
                            g, gang, S.d_tile_res, p.d_head_bits, p.R, p.bb);
     return hipGetLastError();
 }
@@ -999,8 +1000,9 @@ template <int K>
 hipError_t bwd_k(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
                  float *gang, hipStream_t s)
 {
-    return p.bs.W * kWave <= kLbSmall ? bwd_kl<K, kLbSmall>(p, ang, xyz, g, gang, s)
-                                      : bwd_kl<K, kLbLarge>(p, ang, xyz, g, gang, s);
+    return (xyz ? p.bs.W : p.bs.rec_W) * kWave <= kLbSmall
+               ? bwd_kl<K, kLbSmall>(p, ang, xyz, g, gang, s)
+               : bwd_kl<K, kLbLarge>(p, ang, xyz, g, gang, s);
 }
 
 }  // namespace
@@ -1035,7 +1037,7 @@ hipError_t launch_bb_forward_scan(const a2c_plan &p, const float *ang, float *xy
 hipError_t launch_bb_backward_scan(const a2c_plan &p, const float *ang, const float *xyz,
                                    const float *g, float *gang, hipStream_t s)
 {
-    switch (p.bs.K) {
+    switch (xyz ? p.bs.K : p.bs.rec_K) {
     case 1: return bwd_k<1>(p, ang, xyz, g, gang, s);
     case 2: return bwd_k<2>(p, ang, xyz, g, gang, s);
     case 4: return bwd_k<4>(p, ang, xyz, g, gang, s);

@@ -1206,10 +1206,18 @@ hipError_t fa_bwd_k(const a2c_plan &p, const float *ang, const float *xyz, const
                     float *gang, hipStream_t s)
 {
     // the staged coordinate form needs six planes; where they do not fit,
-    // the recompute form (three planes) computes the same gradient
-    if (xyz && !p.bs.fa_unstaged &&
-        (size_t)p.bs.W * 6 * p.bs.fa_stage_atoms * sizeof(float) > (size_t)kMaxDynamicLds)
-        xyz = nullptr;
+    // the recompute form (three planes) computes the same gradient, and where
+    // their LDS leaves the launch more than one round it is the faster one:
+    // (1, 4), us from coordinates and recomputing: 64 x 300 9.1 and 13.2, 1000
+    // chains of 100 10.5 and 13.8, 512 of 50..2000 24.4 and 20.0, 4096 of
+    // them 206 and 141
+    if (xyz && !p.bs.fa_unstaged) {
+        const size_t stage = (size_t)p.bs.W * 6 * p.bs.fa_stage_atoms * sizeof(float);
+        const size_t group = stage + sizeof(FADevTable) + sizeof(BwdShared) + 512;
+        if (stage > (size_t)kMaxDynamicLds ||
+            (int64_t)p.bs.n_win > (int64_t)(kCuLds / group) * p.n_cu)
+            xyz = nullptr;
+    }
     return xyz ? fa_bwd_mode<K, 0>(p, ang, xyz, g, gang, s)
                : fa_bwd_mode<K, 1>(p, ang, xyz, g, gang, s);
 }
