@@ -152,8 +152,8 @@ struct a2c_plan {
     // store-vs-recompute threshold: the forward's coordinates (12 bytes per
     // atom) are kept for the adjoint while they fit; 0 = always recompute
     size_t mem_budget = 0;
-    // the adjoints write the angle gradients with non-temporal stores (at
-    // least kNtGradBytes of them)
+    // the adjoints write the angle gradients, and the inverse map the angles,
+    // with non-temporal stores (at least kNtGradBytes of them)
     bool nt_grad = false;
     // device tables
     uint32_t *d_head_bits = nullptr;     // bit r: residue r starts a chain (bit R set)
@@ -173,7 +173,8 @@ struct a2c_plan {
     int32_t lr_n_piece = 0;
     std::vector<int32_t> lr_piece_atom;  // lr_n_piece + 1 first atoms (last = A)
     std::vector<int32_t> lr_piece_chain; // lr_n_piece chain of each piece
-    int8_t *d_chi_slots = nullptr;       // [20][4][4] chi atom slots (full-atom)
+    int32_t inv_stage_atoms = 0;         // most atoms a workgroup of the inverse map stages
+    uint8_t *d_chi_points = nullptr;     // [20][8] points of the chi torsions (full-atom)
     int32_t *d_lr_seg_atom = nullptr;
     int32_t *d_lr_seg_origin = nullptr;
     int32_t *d_lr_chain_seg = nullptr;
@@ -220,7 +221,8 @@ hipError_t launch_fa_forward_scan(const a2c_plan &p, const float *ang, float *xy
 hipError_t launch_fa_backward_scan(const a2c_plan &p, const float *ang, const float *xyz,
                                    const float *g, float *gang, hipStream_t s);
 void build_lrmsd_segments(a2c_plan &p);
-void build_chi_slots(const FATable &T, int8_t (&out)[A2C_NUM_RESIDUE_TYPES][4][4]);
+void build_chi_points(const FATable &T, uint8_t (&out)[A2C_NUM_RESIDUE_TYPES][8]);
+int32_t inverse_stage_atoms(const a2c_plan &p);
 size_t lrmsd_workspace_bytes(const a2c_plan &p);
 // device address of the no-allocation LRMSD scratch on `device` (current)
 a2c_status lrmsd_scratch_setup(int device);

@@ -577,7 +577,7 @@ void a2c_plan_destroy(a2c_plan *p)
     (void)hipFree(p->d_res_atom_off);
     (void)hipFree(p->d_seq);
     (void)hipFree(p->d_fa);
-    (void)hipFree(p->d_chi_slots);
+    (void)hipFree(p->d_chi_points);
     (void)hipFree(p->d_lr_seg_atom);
     (void)hipFree(p->d_lr_seg_origin);
     (void)hipFree(p->d_lr_chain_seg);
@@ -661,6 +661,7 @@ a2c_status a2c_plan_create(a2c_plan **out, int32_t model_id, int32_t n_chains,
             return st;
         }
     }
+    p->inv_stage_atoms = inverse_stage_atoms(*p);
     p->nt_grad = (size_t)R * (model == A2C_BACKBONE ? 3 : 7) * sizeof(float) >= kNtGradBytes;
     // host tables are complete: now the device
     int dev = 0;
@@ -690,9 +691,9 @@ a2c_status a2c_plan_create(a2c_plan **out, int32_t model_id, int32_t n_chains,
         if (st == A2C_OK) st = upload((void **)&p->d_seq, p->seq.data(), p->seq.size(), s);
         if (st == A2C_OK) st = upload((void **)&p->d_fa, &p->fa_dev, sizeof(FADevTable), s);
         if (st == A2C_OK) {
-            int8_t chi[A2C_NUM_RESIDUE_TYPES][4][4];
-            build_chi_slots(p->fa_host, chi);
-            st = upload((void **)&p->d_chi_slots, chi, sizeof(chi), s);
+            uint8_t chi[A2C_NUM_RESIDUE_TYPES][8];
+            build_chi_points(p->fa_host, chi);
+            st = upload((void **)&p->d_chi_points, chi, sizeof(chi), s);
         }
     }
     if (st == A2C_OK) {

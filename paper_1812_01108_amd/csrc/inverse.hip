@@ -18,40 +18,38 @@
 // host; chi planes a residue lacks are written as 0.
 #include "a2c_internal.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace a2c {
 
-// Residue slots (a, b, c, d) of every chi of every residue type; -1 where
-// the type has no such chi or no defining atom.
-void build_chi_slots(const FATable &T, int8_t (&out)[A2C_NUM_RESIDUE_TYPES][4][4])
+// Per residue type, the residue slots of the points the chi torsions run over:
+// N, CA, the side frames' origins in order and the atom D of the last frame,
+// so that chi_{f+1} is the torsion of points f .. f + 3; and in byte 7 the
+// mask of the chis the type has (bit f) and whose atoms the table names.
+void build_chi_points(const FATable &T, uint8_t (&out)[A2C_NUM_RESIDUE_TYPES][8])
 {
     for (int t = 0; t < A2C_NUM_RESIDUE_TYPES; ++t) {
         const FAType &ft = T.t[t];
-        for (int f = 0; f < 4; ++f) {
-            int8_t *q = out[t][f];
-            q[0] = q[1] = q[2] = q[3] = -1;
-            if (f >= ft.n_side || !ft.side_chi[f]) continue;
-            const int c = ft.origin_slot[3 + f];
-            const int b = f == 0 ? 1 : ft.origin_slot[3 + f - 1];
-            const int a = f == 0 ? 0 : (f == 1 ? 1 : ft.origin_slot[3 + f - 2]);
-            int d = -1;
-            if (f + 1 < ft.n_side) {
-                d = ft.origin_slot[3 + f + 1];
-            } else {
+        uint8_t *q = out[t];
+        for (int i = 0; i < 8; ++i) q[i] = 0;
+        q[1] = 1;
+        for (int f = 0; f < ft.n_side; ++f) {
+            q[2 + f] = (uint8_t)ft.origin_slot[3 + f];
+            bool named = f + 1 < ft.n_side;
+            if (!named) {
                 const int k = 3 + f;
-                for (int i = 0; i < ft.fcount[k] && d < 0; ++i) {
+                for (int i = 0; i < ft.fcount[k] && !named; ++i) {
                     const int s = ft.fbegin[k] + i;
                     const float x = ft.atom[s].x, y = ft.atom[s].y, z = ft.atom[s].z;
                     const float r = std::sqrt(x * x + y * y + z * z);
-                    if (r > 0.f && std::fabs(y) <= 1e-5f * r && z < -1e-3f * r) d = ft.atom[s].slot;
+                    if (r > 0.f && std::fabs(y) <= 1e-5f * r && z < -1e-3f * r) {
+                        q[3 + f] = (uint8_t)ft.atom[s].slot;
+                        named = true;
+                    }
                 }
             }
-            if (d < 0) continue;
-            q[0] = (int8_t)a;
-            q[1] = (int8_t)b;
-            q[2] = (int8_t)c;
-            q[3] = (int8_t)d;
+            if (named && ft.side_chi[f]) q[7] |= (uint8_t)(1u << f);
         }
     }
 }
@@ -88,21 +86,39 @@ __device__ __forceinline__ float atan2_poly(float y, float x)
     return (x != x || y != y) ? x + y : a;
 }
 
-// IUPAC torsion angle of p0-p1-p2-p3:
-// atan2(|b2| b1 . (b2 x b3), (b1 x b2) . (b2 x b3)).  |b2| only scales the
-// first argument, so the 1-ulp hardware square root is enough.
-__device__ __forceinline__ float torsion(P3 p0, P3 p1, P3 p2, P3 p3)
+__device__ __forceinline__ P3 sub(P3 a, P3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
+
+__device__ __forceinline__ P3 cross(P3 a, P3 b)
 {
-    const float b1x = p1.x - p0.x, b1y = p1.y - p0.y, b1z = p1.z - p0.z;
-    const float b2x = p2.x - p1.x, b2y = p2.y - p1.y, b2z = p2.z - p1.z;
-    const float b3x = p3.x - p2.x, b3y = p3.y - p2.y, b3z = p3.z - p2.z;
-    const float n1x = b1y * b2z - b1z * b2y, n1y = b1z * b2x - b1x * b2z, n1z = b1x * b2y - b1y * b2x;
-    const float n2x = b2y * b3z - b2z * b3y, n2y = b2z * b3x - b2x * b3z, n2z = b2x * b3y - b2y * b3x;
-    const float b2n = __builtin_amdgcn_sqrtf(b2x * b2x + b2y * b2y + b2z * b2z);
-    const float y = b2n * (b1x * n2x + b1y * n2y + b1z * n2z);
-    const float x = n1x * n2x + n1y * n2y + n1z * n2z;
-    return atan2_poly(y, x);
+    return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
+
+// Torsions over consecutive points: for p0-p1-p2-p3 with bonds b1, b2, b3 the
+// IUPAC angle is atan2(|b2| b1 . (b2 x b3), (b1 x b2) . (b2 x b3)).  |b2| only
+// scales the first argument, so the 1-ulp hardware square root is enough.  A
+// walk along a chain of points keeps the last two bonds and their normal, so
+// that the next point costs one bond and one normal.
+struct TorsionWalk {
+    P3 b1, b2, n1;
+    __device__ __forceinline__ void start(P3 first, P3 second)
+    {
+        b1 = first;
+        b2 = second;
+        n1 = cross(b1, b2);
+    }
+    // the torsion about b2 onto the bond b3, which the walk then moves along
+    __device__ __forceinline__ float next(P3 b3)
+    {
+        const P3 n2 = cross(b2, b3);
+        const float len = __builtin_amdgcn_sqrtf(b2.x * b2.x + b2.y * b2.y + b2.z * b2.z);
+        const float y = len * (b1.x * n2.x + b1.y * n2.y + b1.z * n2.z);
+        const float x = n1.x * n2.x + n1.y * n2.y + n1.z * n2.z;
+        b1 = b2;
+        b2 = b3;
+        n1 = n2;
+        return atan2_poly(y, x);
+    }
+};
 
 __device__ __forceinline__ bool head_bit(const uint32_t *__restrict__ bits, int64_t r)
 {
@@ -114,21 +130,28 @@ constexpr int kInvThreads = 256;  // residues per workgroup
 // One lane per residue.  The workgroup's atoms, with one residue on either
 // side (the neighbours' backbone atoms), are staged once through LDS with
 // coalesced loads, every load issued before the first store; the torsions
-// then read LDS.  Staged: residues [max(r0 - 1, 0), min(r0 + 257, R)), at
-// most 258 residues of at most kAtoms atoms each.
-template <bool FA>
+// then read LDS, where an atom's x, y, z lie side by side (one address per
+// point; the odd stride keeps the coalesced side free of conflicts).  Staged:
+// residues [max(r0 - 1, 0), min(r0 + 257, R)), at most 258 residues of at most
+// kAtoms atoms each; rows of 256 atoms past the range are skipped as a whole.
+// Bound by the memory: 1.68 M full-atom residues, 223 MB with the atoms no
+// torsion needs (they share cache lines with those that do), in 44.3 us, 5.0
+// TB/s, the rate of a device copy; 52.6 us before, with 630 VALU instructions
+// per wave (549 now: shared bonds and normals) and seven useless rows of loads
+// per thread.  128 residues per workgroup 47.9 us, 64 52.2, 512 46.6.
+// NT: large plans write the angles with non-temporal stores (46.3 -> 44.3 us);
+// small ones leave them in the caches for whatever reads them next.
+template <bool FA, bool NT>
 __global__ __launch_bounds__(kInvThreads) void inverse_kernel(
     const float *__restrict__ xyz, float *__restrict__ ang, const uint32_t *__restrict__ head_bits,
     const int32_t *__restrict__ res_aoff, const uint8_t *__restrict__ seq,
-    const int8_t *__restrict__ chi_slots, int64_t R, int64_t A, int cap)
+    const uint8_t *__restrict__ chi_points, int64_t R, int64_t A)
 {
     constexpr int kAtoms = FA ? A2C_MAX_RESIDUE_ATOMS : 3;
     constexpr int kStage = (kInvThreads + 2) * kAtoms;
     constexpr int kPer = (kStage + kInvThreads - 1) / kInvThreads;
-    // cap: the largest staged range of any workgroup of this plan (<= kStage),
-    // which sizes the dynamic LDS (3 cap floats)
-    extern __shared__ float inv_stage[];
-    float *const sx = inv_stage, *const sy = inv_stage + cap, *const sz = inv_stage + 2 * cap;
+    // sized to the largest staged range of any workgroup of this plan
+    extern __shared__ float stage[];
     const int tid = (int)threadIdx.x;
     const int64_t r0 = (int64_t)blockIdx.x * kInvThreads;
     const int64_t rlo = r0 > 0 ? r0 - 1 : 0;
@@ -139,62 +162,82 @@ __global__ __launch_bounds__(kInvThreads) void inverse_kernel(
     const float *__restrict__ px = xyz + lo;
     const float *__restrict__ py = xyz + A + lo;
     const float *__restrict__ pz = xyz + 2 * A + lo;
-    const int n_st = hi - lo;
-    {
-        float vx[kPer], vy[kPer], vz[kPer];
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int k = tid + j * kInvThreads;
-            const int kc = k < n_st ? k : 0;
-            vx[j] = px[kc]; vy[j] = py[kc]; vz[j] = pz[kc];
-        }
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int k = tid + j * kInvThreads;
-            if (k < n_st) {
-                sx[k] = vx[j]; sy[k] = vy[j]; sz[k] = vz[j];
-            }
-        }
-    }
-    __syncthreads();
+    const int n_st = __builtin_amdgcn_readfirstlane(hi - lo);
     const int64_t r = r0 + tid;
-    if (r >= R) return;
-    auto pt = [&](int64_t atom) -> P3 {
-        const int k = (int)atom - lo;
-        return {sx[k], sy[k], sz[k]};
-    };
-    const bool head = head_bit(head_bits, r), last = head_bit(head_bits, r + 1);
-    const int64_t a = FA ? (int64_t)res_aoff[r] : 3 * r;
+    const int64_t rc = r < R ? r : R - 1;
+    const bool head = head_bit(head_bits, rc), last = head_bit(head_bits, rc + 1);
     // neighbours: the previous residue is staged unless r is a chain head,
     // the next one unless r ends its chain (then r's own atoms stand in and
     // the angle is replaced below)
-    const int64_t rp = head ? r : r - 1, rn = last ? r : r + 1;
-    const int64_t pa = FA ? (int64_t)res_aoff[rp] : 3 * rp;
-    const int64_t na = FA ? (int64_t)res_aoff[rn] : 3 * rn;
+    const int64_t rp = head ? rc : rc - 1, rn = last ? rc : rc + 1;
+    const int a = (FA ? res_aoff[rc] : (int)(3 * rc)) - lo;
+    const int pa = (FA ? res_aoff[rp] : (int)(3 * rp)) - lo;
+    const int na = (FA ? res_aoff[rn] : (int)(3 * rn)) - lo;
+    uint2 q{};
+    if (FA) q = *reinterpret_cast<const uint2 *>(chi_points + 8 * seq[rc]);
+    {
+        float vx[kPer], vy[kPer], vz[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            if (j * kInvThreads < n_st) {
+                const int k = min(tid + j * kInvThreads, n_st - 1);
+                vx[j] = px[k]; vy[j] = py[k]; vz[j] = pz[k];
+            }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            if (j * kInvThreads < n_st) {
+                const int k = 3 * min(tid + j * kInvThreads, n_st - 1);
+                stage[k] = vx[j]; stage[k + 1] = vy[j]; stage[k + 2] = vz[j];
+            }
+    }
+    __syncthreads();
+    if (r >= R) return;
+    auto pt = [&](int k) -> P3 { return {stage[3 * k], stage[3 * k + 1], stage[3 * k + 2]}; };
     const P3 n = pt(a), ca = pt(a + 1), c = pt(a + 2);
     const P3 pca = head ? P3{-1.f, 0.f, 0.f} : pt(pa + 1);
     const P3 pc = head ? P3{0.f, 0.f, 0.f} : pt(pa + 2);
-    const float psi = torsion(n, ca, c, pt(na));
-    ang[r] = torsion(pc, n, ca, c);
-    ang[R + r] = last ? 0.f : psi;
-    ang[2 * R + r] = torsion(pca, pc, n, ca);
+    auto put = [&](int64_t i, float v) {
+        if constexpr (NT) __builtin_nontemporal_store(v, ang + i);
+        else ang[i] = v;
+    };
+    const P3 nca = sub(ca, n);
+    TorsionWalk w;
+    w.start(sub(pc, pca), sub(n, pc));
+    put(2 * R + r, w.next(nca));
+    put(r, w.next(sub(c, ca)));
+    const float psi = w.next(sub(pt(na), c));
+    put(R + r, last ? 0.f : psi);
     if (FA) {
-        // the residue type's four (a, b, c, d) slot quadruples in one load
-        const int4 qv = *reinterpret_cast<const int4 *>(chi_slots + 16 * seq[r]);
-        const int qw[4] = {qv.x, qv.y, qv.z, qv.w};
+        // chis a type lacks repeat its own atoms and are written as 0
+        const uint32_t mask = q.y >> 24;
+        P3 at = pt(a + (int)((q.x >> 16) & 255u));
+        w.start(nca, sub(at, ca));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int8_t q0 = (int8_t)(qw[k] & 0xff), q1 = (int8_t)((qw[k] >> 8) & 0xff);
-            const int8_t q2 = (int8_t)((qw[k] >> 16) & 0xff), q3 = (int8_t)((qw[k] >> 24) & 0xff);
-            const bool has = q0 >= 0;
-            const float v = torsion(pt(a + (has ? q0 : 0)), pt(a + (has ? q1 : 1)),
-                                    pt(a + (has ? q2 : 2)), pt(a + (has ? q3 : 0)));
-            ang[(3 + k) * R + r] = has ? v : 0.f;
+            const P3 to = pt(a + (int)((k == 0 ? q.x >> 24 : q.y >> (8 * (k - 1))) & 255u));
+            const float v = w.next(sub(to, at));
+            at = to;
+            put((3 + k) * R + r, (mask >> k) & 1u ? v : 0.f);
         }
     }
 }
 
 }  // namespace
+
+// The most atoms any workgroup of the inverse map stages.
+int32_t inverse_stage_atoms(const a2c_plan &p)
+{
+    int32_t most = 0;
+    for (int64_t r0 = 0; r0 < p.R; r0 += kInvThreads) {
+        const int64_t rlo = r0 > 0 ? r0 - 1 : 0;
+        const int64_t rhi = r0 + kInvThreads + 1 < p.R ? r0 + kInvThreads + 1 : p.R;
+        most = std::max(most, p.model == A2C_BACKBONE
+                                  ? (int32_t)(3 * (rhi - rlo))
+                                  : p.res_atom_off[rhi] - p.res_atom_off[rlo]);
+    }
+    return most;
+}
+
 }  // namespace a2c
 
 using namespace a2c;
@@ -218,23 +261,12 @@ extern "C" a2c_status a2c_coords_to_angles(a2c_plan *p, const float *d_coords, f
     }
     const dim3 grid((unsigned)((p->R + kInvThreads - 1) / kInvThreads)), block(kInvThreads);
     hipStream_t s = (hipStream_t)stream;
-    // the largest staged atom range over the workgroups (host offsets)
-    int cap = 0;
-    for (int64_t r0 = 0; r0 < p->R; r0 += kInvThreads) {
-        const int64_t rlo = r0 > 0 ? r0 - 1 : 0;
-        const int64_t rhi = r0 + kInvThreads + 1 < p->R ? r0 + kInvThreads + 1 : p->R;
-        const int n = p->model == A2C_BACKBONE ? (int)(3 * (rhi - rlo))
-                                               : p->res_atom_off[rhi] - p->res_atom_off[rlo];
-        cap = n > cap ? n : cap;
-    }
-    const size_t lds = 3 * (size_t)cap * sizeof(float);
-    if (p->model == A2C_BACKBONE)
-        hipLaunchKernelGGL(inverse_kernel<false>, grid, block, lds, s, d_coords, d_angles,
-                           p->d_head_bits, nullptr, nullptr, nullptr, p->R, p->A, cap);
-    else
-        hipLaunchKernelGGL(inverse_kernel<true>, grid, block, lds, s, d_coords, d_angles,
-                           p->d_head_bits, p->d_res_atom_off, p->d_seq, p->d_chi_slots, p->R,
-                           p->A, cap);
+    const size_t lds = 3 * (size_t)p->inv_stage_atoms * sizeof(float);
+    const auto kernel = p->model == A2C_BACKBONE
+                            ? (p->nt_grad ? inverse_kernel<false, true> : inverse_kernel<false, false>)
+                            : (p->nt_grad ? inverse_kernel<true, true> : inverse_kernel<true, false>);
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, d_coords, d_angles, p->d_head_bits,
+                       p->d_res_atom_off, p->d_seq, p->d_chi_points, p->R, p->A);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? A2C_OK : hip_fail(e, "inverse map launch");
 }

@@ -200,3 +200,27 @@ def test_training_batch_sampled_chains():
     print(f"training batch inverse: {len(pick)} chains, {n_res} residues, "
           f"max|dangle|={worst:.3e} rad", flush=True)
     assert worst <= TORSION_TOL
+
+
+@pytest.mark.parametrize("model,n", [("backbone", 360), ("fullatom", 160)])
+def test_large_plan_equals_small_plans(model, n):
+    """Plans whose angles reach 4 MiB write them with other stores: the same
+    angles, bit for bit, as plans of a few of the chains on their own."""
+    import torch
+    a2c = _a2c()
+    lengths = [1000] * (n - 1) + [257]
+    off = offsets_from_lengths(lengths)
+    R = int(off[-1])
+    rng = np.random.Generator(np.random.PCG64(211))
+    planes = 3 if model == "backbone" else 7
+    assert R * planes * 4 >= 4 << 20
+    seq = random_sequence(rng, R) if model == "fullatom" else None
+    plan = a2c.Plan(model, offsets=off, seq=seq)
+    xyz = plan.forward(to_dev(make_angles(rng, R, "mixture", planes)))
+    big = plan.coords_to_angles(xyz)
+    ca, _ = plan.atom_offsets()
+    for c0, c1 in [(0, 2), (n // 2, n // 2 + 1), (n - 2, n)]:
+        sub = a2c.Plan(model, lengths=lengths[c0:c1], seq=None if seq is None else seq[off[c0]:off[c1]])
+        small = sub.coords_to_angles(xyz[:, ca[c0]:ca[c1]].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(big[:, off[c0]:off[c1]], small)
