@@ -51,8 +51,17 @@ def library_version() -> str:
     return _lib.load().a2c_version().decode()
 
 
-def _stream_ptr(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_F32 = torch.float32
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_ptr(device) -> int:
+    """The current stream of a CUDA device as the C ABI takes it.  The public
+    call makes a Stream object each time (2.1 us of a 7 us call); the raw
+    handle is the same value."""
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _geometry_struct(geom: dict | None):
@@ -119,6 +128,12 @@ class Plan:
         check(lib.a2c_plan_sizes(self._h, ctypes.byref(n_res), ctypes.byref(n_atoms)),
               "a2c_plan_sizes")
         self.n_res, self.n_atoms = n_res.value, n_atoms.value
+        self._angle_shape = (self.n_planes, self.n_res)
+        self._coord_shape = (3, self.n_atoms)
+        k = ctypes.c_int32()
+        check(lib.a2c_plan_keep_coords(self._h, ctypes.byref(k)), "a2c_plan_keep_coords")
+        self._keep_coords = bool(k.value)
+        self._lrmsd_bytes = None
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -131,9 +146,7 @@ class Plan:
     def keep_coords(self) -> bool:
         """The plan's store-vs-recompute choice: keep the forward's
         coordinates for the adjoint (True) or recompute the frames (False)."""
-        k = ctypes.c_int32()
-        check(_lib.load().a2c_plan_keep_coords(self._h, ctypes.byref(k)), "a2c_plan_keep_coords")
-        return bool(k.value)
+        return self._keep_coords
 
     def atom_offsets(self):
         """(chain atom offsets [n_chains+1], residue atom offsets [R+1])."""
@@ -216,8 +229,8 @@ class Plan:
         k, w = ctypes.c_int32(), ctypes.c_int32()
         with torch.cuda.device(self.device):
             check(_lib.load().a2c_plan_autotune(
-                self._h, ctypes.c_void_p(angles.data_ptr()), ctypes.c_void_p(coords.data_ptr()),
-                ctypes.c_void_p(grad_coords.data_ptr()), ctypes.c_void_p(grad.data_ptr()),
+                self._h, angles.data_ptr(), coords.data_ptr(),
+                grad_coords.data_ptr(), grad.data_ptr(),
                 mode, reps,
                 None if cache_path is None else cache_path.encode(), ctypes.byref(k),
                 ctypes.byref(w), _stream_ptr(self.device)), "a2c_plan_autotune")
@@ -225,42 +238,42 @@ class Plan:
 
     # -- raw calls (no autograd) ------------------------------------------
     def _check_tensor(self, t, shape, name):
-        if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()
-                and tuple(t.shape) == tuple(shape)):
+        if not (t.is_cuda and t.dtype == _F32 and t.is_contiguous() and t.shape == shape):
             raise ValueError(f"{name} must be a contiguous float32 CUDA tensor of shape {shape}, "
                              f"got {tuple(t.shape)} {t.dtype} on {t.device}")
 
     def forward(self, angles: torch.Tensor, coords: torch.Tensor | None = None,
                 variant: str = "scan", workspace: torch.Tensor | None = None) -> torch.Tensor:
-        self._check_tensor(angles, (self.n_planes, self.n_res), "angles")
+        self._check_tensor(angles, self._angle_shape, "angles")
         if coords is None:
-            coords = torch.empty((3, self.n_atoms), dtype=torch.float32, device=angles.device)
-        self._check_tensor(coords, (3, self.n_atoms), "coords")
-        check(_lib.load().a2c_forward(
-            self._h, _VARIANTS[variant], ctypes.c_void_p(angles.data_ptr()),
-            ctypes.c_void_p(coords.data_ptr()),
-            None if workspace is None else ctypes.c_void_p(workspace.data_ptr()),
-            _stream_ptr(angles.device)), "a2c_forward")
+            coords = torch.empty(self._coord_shape, dtype=_F32, device=angles.device)
+        else:
+            self._check_tensor(coords, self._coord_shape, "coords")
+        st = _lib.load().a2c_forward(
+            self._h, _VARIANTS[variant], angles.data_ptr(), coords.data_ptr(),
+            None if workspace is None else workspace.data_ptr(), _stream_ptr(angles.device))
+        if st:
+            check(st, "a2c_forward")
         return coords
 
     def backward(self, angles: torch.Tensor, grad_coords: torch.Tensor,
                  coords: torch.Tensor | None = None, grad_angles: torch.Tensor | None = None,
                  variant: str = "scan", workspace: torch.Tensor | None = None) -> torch.Tensor:
-        self._check_tensor(angles, (self.n_planes, self.n_res), "angles")
-        self._check_tensor(grad_coords, (3, self.n_atoms), "grad_coords")
+        self._check_tensor(angles, self._angle_shape, "angles")
+        self._check_tensor(grad_coords, self._coord_shape, "grad_coords")
         if coords is not None:
-            self._check_tensor(coords, (3, self.n_atoms), "coords")
+            self._check_tensor(coords, self._coord_shape, "coords")
         if grad_angles is None:
             grad_angles = torch.empty_like(angles)
-        self._check_tensor(grad_angles, (self.n_planes, self.n_res), "grad_angles")
-        check(_lib.load().a2c_backward(
-            self._h, _VARIANTS[variant], ctypes.c_void_p(angles.data_ptr()),
-            None if coords is None else ctypes.c_void_p(coords.data_ptr()),
-            ctypes.c_void_p(grad_coords.data_ptr()), ctypes.c_void_p(grad_angles.data_ptr()),
-            None if workspace is None else ctypes.c_void_p(workspace.data_ptr()),
-            _stream_ptr(angles.device)), "a2c_backward")
+        self._check_tensor(grad_angles, self._angle_shape, "grad_angles")
+        st = _lib.load().a2c_backward(
+            self._h, _VARIANTS[variant], angles.data_ptr(),
+            None if coords is None else coords.data_ptr(), grad_coords.data_ptr(),
+            grad_angles.data_ptr(), None if workspace is None else workspace.data_ptr(),
+            _stream_ptr(angles.device))
+        if st:
+            check(st, "a2c_backward")
         return grad_angles
-
 
     # -- inverse map ----------------------------------------------------
     def coords_to_angles(self, coords: torch.Tensor,
@@ -272,7 +285,7 @@ class Plan:
                               device=coords.device)
         self._check_tensor(out, (self.n_planes, self.n_res), "angles")
         check(_lib.load().a2c_coords_to_angles(
-            self._h, ctypes.c_void_p(coords.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+            self._h, coords.data_ptr(), out.data_ptr(),
             _stream_ptr(coords.device)), "a2c_coords_to_angles")
         return out
 
@@ -302,21 +315,23 @@ class Plan:
         elif loss:
             out = torch.empty(1, dtype=torch.float32, device=angles.device)
         check(_lib.load().a2c_mse_step(
-            self._h, ctypes.c_void_p(angles.data_ptr()), ctypes.c_void_p(target.data_ptr()),
-            None if coords is None else ctypes.c_void_p(coords.data_ptr()),
-            None if out is None else ctypes.c_void_p(out.data_ptr()),
-            ctypes.c_void_p(grad_angles.data_ptr()), _stream_ptr(angles.device)),
+            self._h, angles.data_ptr(), target.data_ptr(),
+            None if coords is None else coords.data_ptr(),
+            None if out is None else out.data_ptr(),
+            grad_angles.data_ptr(), _stream_ptr(angles.device)),
             "a2c_mse_step")
         return (None if out is None else out[0]), grad_angles
 
     # -- LRMSD loss -------------------------------------------------------
     def lrmsd_workspace(self) -> torch.Tensor | None:
-        n = ctypes.c_size_t()
-        check(_lib.load().a2c_lrmsd_workspace_bytes(self._h, ctypes.byref(n)),
-              "a2c_lrmsd_workspace_bytes")
-        if n.value == 0:
+        if self._lrmsd_bytes is None:
+            n = ctypes.c_size_t()
+            check(_lib.load().a2c_lrmsd_workspace_bytes(self._h, ctypes.byref(n)),
+                  "a2c_lrmsd_workspace_bytes")
+            self._lrmsd_bytes = n.value
+        if self._lrmsd_bytes == 0:
             return None
-        return torch.empty(n.value // 4, dtype=torch.float32, device=self.device)
+        return torch.empty(self._lrmsd_bytes // 4, dtype=torch.float32, device=self.device)
 
     def lrmsd_forward(self, coords: torch.Tensor, target: torch.Tensor, workspace=None,
                       out: torch.Tensor | None = None) -> torch.Tensor:
@@ -328,9 +343,9 @@ class Plan:
             out = torch.empty(self.n_chains, dtype=torch.float32, device=coords.device)
         self._check_tensor(out, (self.n_chains,), "out")
         check(_lib.load().a2c_lrmsd_forward(
-            self._h, ctypes.c_void_p(coords.data_ptr()), ctypes.c_void_p(target.data_ptr()),
-            ctypes.c_void_p(out.data_ptr()),
-            None if workspace is None else ctypes.c_void_p(workspace.data_ptr()),
+            self._h, coords.data_ptr(), target.data_ptr(),
+            out.data_ptr(),
+            None if workspace is None else workspace.data_ptr(),
             _stream_ptr(coords.device)), "a2c_lrmsd_forward")
         return out
 
@@ -343,8 +358,8 @@ class Plan:
         self._check_tensor(target, (3, self.n_atoms), "target")
         self._check_tensor(out, (self.n_chains,), "out")
         check(_lib.load().a2c_lrmsd_forward_noalloc(
-            self._h, ctypes.c_void_p(coords.data_ptr()), ctypes.c_void_p(target.data_ptr()),
-            ctypes.c_void_p(out.data_ptr()), _stream_ptr(coords.device)),
+            self._h, coords.data_ptr(), target.data_ptr(),
+            out.data_ptr(), _stream_ptr(coords.device)),
             "a2c_lrmsd_forward_noalloc")
         return out
 
@@ -358,9 +373,9 @@ class Plan:
             grad_coords = torch.zeros_like(coords)
         self._check_tensor(grad_coords, (3, self.n_atoms), "grad_coords")
         check(_lib.load().a2c_lrmsd_backward(
-            self._h, ctypes.c_void_p(coords.data_ptr()), ctypes.c_void_p(target.data_ptr()),
-            ctypes.c_void_p(grad_lrmsd.data_ptr()), ctypes.c_void_p(grad_coords.data_ptr()),
-            None if workspace is None else ctypes.c_void_p(workspace.data_ptr()),
+            self._h, coords.data_ptr(), target.data_ptr(),
+            grad_lrmsd.data_ptr(), grad_coords.data_ptr(),
+            None if workspace is None else workspace.data_ptr(),
             _stream_ptr(coords.device)), "a2c_lrmsd_backward")
         return grad_coords
 
