@@ -370,7 +370,7 @@ class Plan:
         self._check_tensor(target, (3, self.n_atoms), "target")
         self._check_tensor(grad_lrmsd, (self.n_chains,), "grad_lrmsd")
         if grad_coords is None:
-            grad_coords = torch.zeros_like(coords)
+            grad_coords = torch.empty_like(coords)  # every atom is written
         self._check_tensor(grad_coords, (3, self.n_atoms), "grad_coords")
         check(_lib.load().a2c_lrmsd_backward(
             self._h, coords.data_ptr(), target.data_ptr(),
