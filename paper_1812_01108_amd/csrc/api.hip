@@ -186,6 +186,18 @@ std::vector<int32_t> pack_tiles(const std::vector<int32_t> &off, int64_t cap)
     return tiles;
 }
 
+// The most atoms of one wave's run of `run` residues in the windows `starts`.
+int64_t most_run_atoms(const a2c_plan &p, const std::vector<int64_t> &starts, int64_t run)
+{
+    int64_t most = 1;
+    for (size_t t = 0; t + 1 < starts.size(); ++t)
+        for (int64_t rb = starts[t]; rb < starts[t + 1]; rb += run) {
+            const int64_t re = std::min<int64_t>(rb + run, starts[t + 1]);
+            most = std::max<int64_t>(most, p.res_atom_off[re] - p.res_atom_off[rb]);
+        }
+    return most;
+}
+
 // Layouts of a schedule (see Sched).
 enum SchedRole { kRoleForward, kRoleAdjoint };
 
@@ -208,12 +220,7 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
         // per-wave LDS stage of three planes (the adjoint from coordinates
         // stages six where they fit): the most atoms of one wave's run of
         // 64 K residues
-        int64_t most = 1;
-        for (size_t t = 0; t + 1 < starts.size(); ++t)
-            for (int64_t rb = starts[t]; rb < starts[t + 1]; rb += (int64_t)kWave * K) {
-                const int64_t re = std::min<int64_t>(rb + (int64_t)kWave * K, starts[t + 1]);
-                most = std::max<int64_t>(most, p->res_atom_off[re] - p->res_atom_off[rb]);
-            }
+        const int64_t most = most_run_atoms(*p, starts, (int64_t)kWave * K);
         if ((size_t)W * 3 * most * sizeof(float) > (size_t)kMaxDynamicLds)
             S.fa_unstaged = true;  // atoms straight to global memory
         else
@@ -356,6 +363,44 @@ int32_t pack_waves(const a2c_plan &p, int32_t K, int32_t least, int32_t most)
     return least;
 }
 
+// Whether a full-atom launch of schedule (K, W) is one round of workgroups: the
+// LDS (the waves' stages, and the tables and scan state, `fixed` bytes) and the
+// registers (simd_waves per SIMD, a workgroup's waves dealt out over the four)
+// let the device hold all of them at once.
+bool one_round(const a2c_plan &p, int32_t K, int32_t W, size_t fixed, int32_t simd_waves)
+{
+    constexpr size_t kGranule = 1280;  // LDS is handed out in pieces of this
+    const int64_t run = (int64_t)kWave * K;
+    const auto holds = [&](int64_t n_win, int64_t run_atoms) {
+        const size_t stage = (size_t)W * 3 * run_atoms * sizeof(float);
+        if (stage > (size_t)kMaxDynamicLds) return false;
+        const size_t group = (stage + fixed + kGranule - 1) / kGranule * kGranule;
+        return n_win <= std::min<int64_t>(kCuLds / group, simd_waves / ((W + 3) / 4)) * p.n_cu;
+    };
+    // the least there can be, before the windows are laid out
+    if (!holds((p.R + run * W - 1) / (run * W), run * p.A / std::max<int64_t>(1, p.R))) return false;
+    bool whole;
+    const std::vector<int64_t> st = window_starts(&p, run * W, whole);
+    return holds((int64_t)st.size() - 1, most_run_atoms(p, st, run));
+}
+
+// A launch just over one round takes nearly two: `s` if it is one round, else
+// the fewest residues per lane (one, up to most_K) and waves that make it one,
+// else `s`.  simd_waves[K - 1]: waves a SIMD's registers hold.  Forward: 2000
+// chains of 151, 1573 windows at W = 3 23.2, 500 of four chains at W = 10 15.9;
+// 580 chains of 50..2000, 24.3 at W = 4, 16.8 at W = 6.  Recomputing adjoint:
+// 550 of them, 30.8 at (1, 4), 23.7 at (2, 3).
+Shape prefer_one_round(const a2c_plan &p, Shape s, size_t fixed, int32_t most_K,
+                       const int32_t (&simd_waves)[2])
+{
+    if (one_round(p, s.K, s.W, fixed, simd_waves[s.K - 1])) return s;
+    // (two residues per lane and more than eight waves spill)
+    for (int32_t K = 1; K <= most_K; ++K)
+        for (int32_t W = 2; W <= kMaxWaves / K; ++W)
+            if (one_round(p, K, W, fixed, simd_waves[K - 1])) return {K, W};
+    return s;
+}
+
 Shape default_forward(const a2c_plan &p)
 {
     const int64_t R = p.R;
@@ -366,8 +411,9 @@ Shape default_forward(const a2c_plan &p)
         // chain of up to 512 where that fits one round (64 x 300: 10.5 at
         // W = 4, 9.2 at W = 6)
         const int32_t whole = waves_for(p.max_len, 1);
-        const int32_t W = std::min<int32_t>(R > 400000 ? 8 : 4, whole);
-        return {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : W};
+        const Shape s{1, whole <= 8 ? pack_waves(p, 1, whole, 8)
+                                    : std::min<int32_t>(R > 400000 ? 8 : 4, whole)};
+        return prefer_one_round(p, s, 6032, 1, {6, 5});
     }
     // a batch of a few chunks keeps a chunk that holds its longest chain
     if (p.max_len > 1024 && p.max_len <= 4096 && R <= 4 * 4096) return {4, waves_for(p.max_len, 4)};
@@ -393,7 +439,7 @@ Shape default_adjoint(const a2c_plan &p, Shape &rec)
         const int32_t whole = waves_for(p.max_len, 1);
         rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : 4};
         if (rec.W > 4 && (int64_t)kWave * rec.W * p.n_cu < R) rec.W = 4;
-        return rec;
+        return rec = prefer_one_round(p, rec, 7024, 2, {4, 3});
     }
     // from coordinates: 256 x 700 7.2 at (4, 3), 5.2 at (1, 12); 700 chains of
     // 20..1000 9.2 at (4, 4), 8.3 at (2, 8); 6000 of them 41.4 and 41.9 at

@@ -469,6 +469,7 @@ __device__ __forceinline__ LaneRes<K, ANG> load_lane_res(const LaneRun<K> &L,
 constexpr int kGroup = 4;                        // units per spine lane
 constexpr int kSpineUnits = kWave * kGroup;      // units per spine wave
 constexpr int kFrameBlock = 3 * kGroup * 65 * 4; // floats
+using SpineShared = FwdSharedOf<kMaxWaves / kGroup>;
 
 inline size_t frame_bytes(int waves)
 {
@@ -502,7 +503,7 @@ __device__ __forceinline__ Aff frame_get(const float *frames, int block, int i)
 // barrier.
 __device__ __forceinline__ Aff entering_frame(const Aff &unit, bool head, int n_units,
                                               float *frames, uint64_t (&flags)[kMaxWaves],
-                                              FwdShared &sh, float (&carry_sh)[12],
+                                              SpineShared &sh, float (&carry_sh)[12],
                                               uint64_t *__restrict__ status, int64_t t,
                                               int64_t first, uint64_t prev, bool published)
 {
@@ -729,7 +730,7 @@ __global__ __launch_bounds__(LB) void fa_forward_flat_kernel(
 {
     extern __shared__ __align__(16) float stage_mem[];
     __shared__ __align__(16) FADevTable tab;
-    __shared__ FwdShared sh;
+    __shared__ SpineShared sh;
     __shared__ float carry_sh[12];
     __shared__ uint64_t unit_flags[kMaxWaves];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -909,7 +910,7 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     static_assert(GM == kGradLoad || RECOMPUTE, "the fused step recomputes the frames");
     extern __shared__ __align__(16) float stage_mem[];
     __shared__ __align__(16) FADevTable tab;
-    __shared__ FwdShared shf;
+    __shared__ SpineShared shf;
     __shared__ BwdShared shb;
     __shared__ float fcarry_sh[12];
     __shared__ float rcarry_sh[6];

@@ -85,12 +85,14 @@ __device__ __forceinline__ float wrench_torque(const Wrench &S, float ox, float 
     return fmaf(uz, tz, fmaf(uy, ty, ux * tx));
 }
 
-struct FwdShared {
-    float tot[kMaxWaves][12];   // wave totals
-    int tot_flag[kMaxWaves];    // a chain starts in the wave
-    float pre[kMaxWaves][12];   // inclusive prefixes of the wave totals
-    int pre_flag[kMaxWaves];    // a chain starts in waves 0..w
+template <int WAVES>
+struct FwdSharedOf {
+    float tot[WAVES][12];   // wave totals
+    int tot_flag[WAVES];    // a chain starts in the wave
+    float pre[WAVES][12];   // inclusive prefixes of the wave totals
+    int pre_flag[WAVES];    // a chain starts in waves 0..w
 };
+using FwdShared = FwdSharedOf<kMaxWaves>;
 
 struct BwdShared {
     float tot[kMaxWaves][6];    // wave totals
@@ -761,9 +763,9 @@ __device__ __forceinline__ Aff lb_carry_in(const uint64_t *status, int64_t first
 // LINK = false (windows of whole chains): no window needs another's frame, so
 // nothing is published or read (status, first, prev and carry_sh unused).
 // published: an earlier launch has published the aggregates (the spine pass).
-template <bool LINK = true>
+template <bool LINK = true, typename Shared>
 __device__ __forceinline__ Aff block_prefix_windows(Aff m, uint64_t heads, int nact, bool active,
-                                                    FwdShared &sh, float (&carry_sh)[12],
+                                                    Shared &sh, float (&carry_sh)[12],
                                                     uint64_t *__restrict__ status, int64_t t,
                                                     int64_t first, uint64_t prev,
                                                     bool published = false)

@@ -193,6 +193,22 @@ def test_extra_atoms_in_any_frame(mode, tmp_path, monkeypatch):
         _check(plan, off, seq, ang, mode, label=f"extra atoms K={K} W={W}")
 
 
+@pytest.mark.parametrize("n, longest", [(1200, 151), (2000, 151), (2900, 151), (560, 1000)])
+def test_default_schedules_about_one_round(n, longest):
+    """Batches on both sides of the sizes at which a launch of the default
+    schedules holds all its workgroups at once: few chains to a window,
+    several, and more than any window packs in one round; and chains over
+    several windows."""
+    a2c = _a2c()
+    rng = np.random.Generator(np.random.PCG64(n))
+    lengths = [longest] * n if longest == 151 else [int(v) for v in rng.integers(50, longest + 1, n)]
+    off, seq, ang = _batch(lengths, n)
+    plan = a2c.Plan("fullatom", offsets=off, seq=seq)
+    label = f"{n} chains {plan.schedule} {plan.adjoint_schedule}"
+    for mode in ("coords", "recompute"):
+        _check(plan, off, seq, ang, mode, label=label)
+
+
 @pytest.mark.parametrize("name", ["fullatom_64x300", "ragged_fullatom_512"])
 def test_full_size_workloads(name):
     a2c = _a2c()
