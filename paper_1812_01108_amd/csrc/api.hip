@@ -186,7 +186,8 @@ std::vector<int32_t> pack_tiles(const std::vector<int32_t> &off, int64_t cap)
     return tiles;
 }
 
-// The most atoms of one wave's run of `run` residues in the windows `starts`.
+// The most atoms of one wave's run of `run` residues in the windows `starts`,
+// in whole pieces of the kernels' copies (four atoms).
 int64_t most_run_atoms(const a2c_plan &p, const std::vector<int64_t> &starts, int64_t run)
 {
     int64_t most = 1;
@@ -195,7 +196,7 @@ int64_t most_run_atoms(const a2c_plan &p, const std::vector<int64_t> &starts, in
             const int64_t re = std::min<int64_t>(rb + run, starts[t + 1]);
             most = std::max<int64_t>(most, p.res_atom_off[re] - p.res_atom_off[rb]);
         }
-    return most;
+    return (most + 3) / 4 * 4;
 }
 
 // Layouts of a schedule (see Sched).

@@ -249,10 +249,11 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
     const int32_t *__restrict__ wstart, const int32_t *__restrict__ look_first,
     uint64_t *__restrict__ status, int64_t R, BBParams P)
 {
-    extern __shared__ float stage_mem[];
+    extern __shared__ __align__(16) float stage_mem[];
     __shared__ FwdShared sh;
     __shared__ float carry_sh[12];
     constexpr int RUN = kWave * K;  // residues per wave
+    constexpr int VA = K == 2 ? 1 : piece_floats(K), VC = K == 2 ? 1 : piece_floats(3 * K);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = blockIdx.x;
@@ -276,12 +277,12 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
     float phi[K], psi[K], om[K];
     if (active) {
         float v0[K], v1[K], v2[K];
-        run_load<K>(ang + rbase, nres, full, v0);
-        run_load<K>(ang + R + rbase, nres, full, v1);
-        run_load<K>(ang + 2 * R + rbase, nres, full, v2);
-        run_to_lanes<K>(buf, v0, phi);
-        run_to_lanes<K>(buf, v1, psi);
-        run_to_lanes<K>(buf, v2, om);
+        run_load<K, VA>(ang + rbase, nres, full, v0);
+        run_load<K, VA>(ang + R + rbase, nres, full, v1);
+        run_load<K, VA>(ang + 2 * R + rbase, nres, full, v2);
+        run_to_lanes<K, VA>(buf, v0, phi);
+        run_to_lanes<K, VA>(buf, v1, psi);
+        run_to_lanes<K, VA>(buf, v2, om);
     }
     float x[3 * K], y[3 * K], z[3 * K];
     Aff m = aff_identity();
@@ -354,9 +355,9 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
         }
     }
     float *out = xyz + 3 * rbase;
-    lanes_to_run<3 * K>(buf, x, out, 3 * nres, full);
-    lanes_to_run<3 * K>(buf, y, out + A, 3 * nres, full);
-    lanes_to_run<3 * K>(buf, z, out + 2 * A, 3 * nres, full);
+    lanes_to_run<3 * K, false, VC>(buf, x, out, 3 * nres, full);
+    lanes_to_run<3 * K, false, VC>(buf, y, out + A, 3 * nres, full);
+    lanes_to_run<3 * K, false, VC>(buf, z, out + 2 * A, 3 * nres, full);
 }
 
 // Backward that recomputes the frames from the angles for batches with a chain
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(LB) void bb_backward_chunked_kernel(
     const int32_t *__restrict__ tile_res, const uint32_t *__restrict__ head_bits, int64_t R,
     BBParams P0)
 {
-    extern __shared__ float stage_mem[];
+    extern __shared__ __align__(16) float stage_mem[];
     __shared__ FwdShared shf[2];
     __shared__ BwdShared shb[2];
     __shared__ float fwd_carry[kMaxChunks][12];
@@ -554,19 +555,19 @@ __device__ __forceinline__ void bb_lane_torques(
 }
 
 // The three gradient planes of a wave's run (non-temporal stores when nt).
-template <int K>
+template <int K, int V = piece_floats(K)>
 __device__ __forceinline__ void bb_store_torques(float *buf, const float (&gr)[3][K],
                                                  float *__restrict__ gang, int64_t R, int64_t rbase,
                                                  int nres, bool full, bool nt)
 {
     if (nt) {
-        lanes_to_run<K, true>(buf, gr[1], gang + rbase, nres, full);          // phi  (slot CA)
-        lanes_to_run<K, true>(buf, gr[2], gang + R + rbase, nres, full);      // psi  (slot C)
-        lanes_to_run<K, true>(buf, gr[0], gang + 2 * R + rbase, nres, full);  // omega (slot N)
+        lanes_to_run<K, true, V>(buf, gr[1], gang + rbase, nres, full);          // phi  (slot CA)
+        lanes_to_run<K, true, V>(buf, gr[2], gang + R + rbase, nres, full);      // psi  (slot C)
+        lanes_to_run<K, true, V>(buf, gr[0], gang + 2 * R + rbase, nres, full);  // omega (slot N)
     } else {
-        lanes_to_run<K>(buf, gr[1], gang + rbase, nres, full);
-        lanes_to_run<K>(buf, gr[2], gang + R + rbase, nres, full);
-        lanes_to_run<K>(buf, gr[0], gang + 2 * R + rbase, nres, full);
+        lanes_to_run<K, false, V>(buf, gr[1], gang + rbase, nres, full);
+        lanes_to_run<K, false, V>(buf, gr[2], gang + R + rbase, nres, full);
+        lanes_to_run<K, false, V>(buf, gr[0], gang + 2 * R + rbase, nres, full);
     }
 }
 
@@ -609,7 +610,7 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     const int32_t *__restrict__ look_last, uint64_t *__restrict__ status, int64_t R, BBParams P,
     int32_t spined, int32_t nt)
 {
-    extern __shared__ float stage_mem[];
+    extern __shared__ __align__(16) float stage_mem[];
     __shared__ FwdShared shf;
     __shared__ BwdShared shb;
     __shared__ float fcarry_sh[12];
@@ -742,10 +743,11 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     const int32_t *__restrict__ look_last, uint64_t *__restrict__ status, int64_t R, BBParams P,
     int32_t rev, int32_t nt)
 {
-    extern __shared__ float stage_mem[];
+    extern __shared__ __align__(16) float stage_mem[];
     __shared__ BwdShared sh;
     __shared__ float carry_sh[6];
     constexpr int RUN = kWave * K;  // residues per wave
+    constexpr int V = K == 2 ? 1 : piece_floats(3 * K);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
@@ -779,18 +781,18 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
         }
         float w0[3 * K], w1[3 * K], w2[3 * K], w3[3 * K], w4[3 * K], w5[3 * K];
         const float *xb = xyz + 3 * rbase, *gb = g + 3 * rbase;
-        run_load<3 * K>(xb, 3 * nres, full, w0);
-        run_load<3 * K>(xb + A, 3 * nres, full, w1);
-        run_load<3 * K>(xb + 2 * A, 3 * nres, full, w2);
-        run_load<3 * K>(gb, 3 * nres, full, w3);
-        run_load<3 * K>(gb + A, 3 * nres, full, w4);
-        run_load<3 * K>(gb + 2 * A, 3 * nres, full, w5);
-        run_to_lanes<3 * K>(buf, w0, x);
-        run_to_lanes<3 * K>(buf, w1, y);
-        run_to_lanes<3 * K>(buf, w2, z);
-        run_to_lanes<3 * K>(buf, w3, gx);
-        run_to_lanes<3 * K>(buf, w4, gy);
-        run_to_lanes<3 * K>(buf, w5, gz);
+        run_load<3 * K, V>(xb, 3 * nres, full, w0);
+        run_load<3 * K, V>(xb + A, 3 * nres, full, w1);
+        run_load<3 * K, V>(xb + 2 * A, 3 * nres, full, w2);
+        run_load<3 * K, V>(gb, 3 * nres, full, w3);
+        run_load<3 * K, V>(gb + A, 3 * nres, full, w4);
+        run_load<3 * K, V>(gb + 2 * A, 3 * nres, full, w5);
+        run_to_lanes<3 * K, V>(buf, w0, x);
+        run_to_lanes<3 * K, V>(buf, w1, y);
+        run_to_lanes<3 * K, V>(buf, w2, z);
+        run_to_lanes<3 * K, V>(buf, w3, gx);
+        run_to_lanes<3 * K, V>(buf, w4, gy);
+        run_to_lanes<3 * K, V>(buf, w5, gz);
         const float lx = dpp_f<kDppWaveShr1>(x[3 * K - 1]);
         const float ly = dpp_f<kDppWaveShr1>(y[3 * K - 1]);
         const float lz = dpp_f<kDppWaveShr1>(z[3 * K - 1]);
@@ -809,7 +811,7 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     if (!active) return;
     float gr[3][K];
     bb_lane_torques<K>(S, x, y, z, gx, gy, gz, px, py, pz, hm, lm, P, gr);
-    bb_store_torques<K>(buf, gr, gang, R, rbase, nres, full, nt != 0);
+    bb_store_torques<K, K == 2 ? 1 : piece_floats(K)>(buf, gr, gang, R, rbase, nres, full, nt != 0);
 }
 
 // ---------------------------------------------------------------- plain form

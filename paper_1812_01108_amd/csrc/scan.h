@@ -549,57 +549,111 @@ __device__ __forceinline__ void stage_store(float *buf, const float (&in)[N], fl
 
 
 // ------------------------------------------------------- staging for windows
-// Same transposes as above for the wave runs of a window, with every LDS and
-// global address formed from a per-lane base and compile-time offsets.
+// Transposes as above for the wave runs of a window, in pieces of V = 4, 2 or
+// 1 floats (the most that divides N; single floats for the 24 of eight
+// residues, which spill and where pieces lost 1-2 %): lane l of a wave moves
+// piece l + 64 m of the run in one access, and its own N elements are the
+// P = N / V pieces from l P on.  One piece a lane (P = 1) needs no LDS at all.
+// Larger pieces lie in LDS as in memory, where rows of three meet no bank
+// conflicts, single floats in rows of N + (N even).  Global addresses are
+// aligned to a float only (a window starts at any residue and a plane at any
+// atom), LDS ones to the piece; all are formed from a per-lane base and
+// compile-time offsets.
 // `full` (wave-uniform): all 64 N elements are valid; otherwise only the
 // first n are (a window's last wave).
+// The forward and the adjoint from coordinates keep single floats at two
+// residues per lane: 4096 chains of 20..1000, forward at (8, 4) and adjoint at
+// (2, 3) 62.7 us in a graph, 64.5 with pieces of two in that adjoint.
+// Against single floats in padded rows, buffers out of cache: 1500 chains of
+// 20..1000 residues, forward 14.5 to 13.9 us, adjoint from coordinates 15.4 to
+// 14.9, recomputing 18.9 to 18.2, fused step 25.1 to 23.3 us; 6000 of them,
+// fused step 82.8 to 80.4 us (the others within 2 %).
 
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 
-// Coalesced loads of run[0 .. 64N): element lane + 64 m goes to v[m] (0 past n).
-template <int N>
+constexpr int piece_floats(int n) { return n >= 24 ? 1 : n % 4 == 0 ? 4 : (n % 2 == 0 ? 2 : 1); }
+
+template <int N, int V_ = piece_floats(N)>
+struct Pieces {
+    static constexpr int V = V_;
+    static constexpr int P = N / V;
+    // pieces a row in LDS, and the place of piece lane + 64 m there: a base
+    // that repeats with `period` in m, up to a constant step
+    static constexpr int S = V == 1 && N % 2 == 0 ? P + 1 : P;
+    static constexpr int period = S == P ? 1 : P / cgcd(P, 64);
+    static constexpr int step = 64 * period + (64 * period / P) * (S - P);
+    typedef float lds_t __attribute__((ext_vector_type(V)));
+    typedef float mem_t __attribute__((ext_vector_type(V), aligned(4)));
+
+    int base[period];
+    __device__ __forceinline__ Pieces()
+    {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int m = 0; m < period; ++m) {
+            const unsigned q = (unsigned)(lane + 64 * m);
+            base[m] = (int)(q + (q / P) * (S - P));
+        }
+    }
+    __device__ __forceinline__ int at(int m) const
+    {
+        return base[m % period] + (m / period) * step;
+    }
+};
+
+// Coalesced loads of run[0 .. 64N): v[V m + i] is element V (lane + 64 m) + i
+// (0 past n).
+template <int N, int V = piece_floats(N)>
 __device__ __forceinline__ void run_load(const float *__restrict__ run, int n, bool full,
                                          float (&v)[N])
 {
+    using Q = Pieces<N, V>;
     const int lane = threadIdx.x & 63;
     if (full) {
 #pragma unroll
-        for (int m = 0; m < N; ++m) v[m] = run[lane + 64 * m];
+        for (int m = 0; m < Q::P; ++m) {
+            const typename Q::mem_t q =
+                *reinterpret_cast<const typename Q::mem_t *>(run + Q::V * (lane + 64 * m));
+#pragma unroll
+            for (int i = 0; i < Q::V; ++i) v[Q::V * m + i] = q[i];
+        }
     } else {
 #pragma unroll
-        for (int m = 0; m < N; ++m) {
-            const int e = lane + 64 * m;
-            v[m] = e < n ? run[e] : 0.f;
-        }
+        for (int m = 0; m < Q::P; ++m)
+#pragma unroll
+            for (int i = 0; i < Q::V; ++i) {
+                const int e = Q::V * (lane + 64 * m) + i;
+                v[Q::V * m + i] = e < n ? run[e] : 0.f;
+            }
     }
 }
 
 // Coalesced run (from run_load) -> lane l holds elements l N .. l N + N - 1.
-// Rows of S = N + (N even) floats in LDS: element e = lane + 64 m sits at
-// index e + (e / N)(S - N), which repeats with period P = N / gcd(N, 64) in m
-// up to a constant step, so P per-lane bases serve all N writes; each lane
-// then reads its own row.
-template <int N>
+template <int N, int V = piece_floats(N)>
 __device__ __forceinline__ void run_to_lanes(float *buf, const float (&v)[N], float (&out)[N])
 {
-    if constexpr (N == 1) {
-        out[0] = v[0];
+    using Q = Pieces<N, V>;
+    if constexpr (Q::P == 1) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) out[i] = v[i];
     } else {
+        const Q place;
         const int lane = threadIdx.x & 63;
-        constexpr int S = (N & 1) ? N : N + 1;
-        constexpr int P = N / cgcd(N, 64);
-        constexpr int STEP = 64 * P + (64 * P / N) * (S - N);
-        int base[P];
+        typename Q::lds_t *b = reinterpret_cast<typename Q::lds_t *>(buf);
 #pragma unroll
-        for (int m0 = 0; m0 < P; ++m0) {
-            const unsigned e = (unsigned)(lane + 64 * m0);
-            base[m0] = (int)(e + (e / N) * (S - N));
+        for (int m = 0; m < Q::P; ++m) {
+            typename Q::lds_t q;
+#pragma unroll
+            for (int i = 0; i < Q::V; ++i) q[i] = v[Q::V * m + i];
+            b[place.at(m)] = q;
         }
-#pragma unroll
-        for (int m = 0; m < N; ++m) buf[base[m % P] + (m / P) * STEP] = v[m];
         wave_lds_sync();
 #pragma unroll
-        for (int i = 0; i < N; ++i) out[i] = buf[lane * S + i];
+        for (int m = 0; m < Q::P; ++m) {
+            const typename Q::lds_t q = b[lane * Q::S + m];
+#pragma unroll
+            for (int i = 0; i < Q::V; ++i) out[Q::V * m + i] = q[i];
+        }
         wave_lds_sync();
     }
 }
@@ -613,44 +667,59 @@ __device__ __forceinline__ void out_store(float *p, float v)
     else *p = v;
 }
 
-// run[l N + i] = in[i] of lane l for indices below n, written with 64
-// consecutive floats per instruction.  Rows of N + (N even) floats in LDS;
-// the read address of element e = lane + 64 m repeats with period
-// P = N / gcd(N, 64) in m up to a constant step, so P per-lane bases serve
-// all N reads.  NT: non-temporal stores.
-template <int N, bool NT = false>
+// run[l N + i] = in[i] of lane l for indices below n, a piece per lane and
+// instruction.  NT: non-temporal stores.
+template <int N, bool NT = false, int V = piece_floats(N)>
 __device__ __forceinline__ void lanes_to_run(float *buf, const float (&in)[N],
                                              float *__restrict__ run, int n, bool full)
 {
+    using Q = Pieces<N, V>;
+    const Q place;
     const int lane = threadIdx.x & 63;
-    if constexpr (N == 1) {
-        if (full || lane < n) out_store<NT>(&run[lane], in[0]);
-    } else {
-        constexpr int S = (N & 1) ? N : N + 1;
-        constexpr int P = N / cgcd(N, 64);
-        constexpr int STEP = 64 * P + (64 * P / N) * (S - N);
+    typename Q::lds_t *b = reinterpret_cast<typename Q::lds_t *>(buf);
+    if constexpr (Q::P > 1) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) buf[lane * S + i] = in[i];
-        wave_lds_sync();
-        int base[P];
+        for (int m = 0; m < Q::P; ++m) {
+            typename Q::lds_t q;
 #pragma unroll
-        for (int m0 = 0; m0 < P; ++m0) {
-            const unsigned e = (unsigned)(lane + 64 * m0);
-            base[m0] = (int)(e + (e / N) * (S - N));
-        }
-        if (full) {
-#pragma unroll
-            for (int m = 0; m < N; ++m)
-                out_store<NT>(&run[lane + 64 * m], buf[base[m % P] + (m / P) * STEP]);
-        } else {
-#pragma unroll
-            for (int m = 0; m < N; ++m) {
-                const int e = lane + 64 * m;
-                if (e < n) out_store<NT>(&run[e], buf[base[m % P] + (m / P) * STEP]);
-            }
+            for (int i = 0; i < Q::V; ++i) q[i] = in[Q::V * m + i];
+            b[lane * Q::S + m] = q;
         }
         wave_lds_sync();
     }
+    const auto piece = [&](int m) {
+        typename Q::mem_t q;
+        if constexpr (Q::P > 1) {
+            q = b[place.at(m)];
+        } else {
+#pragma unroll
+            for (int i = 0; i < Q::V; ++i) q[i] = in[i];
+        }
+        return q;
+    };
+    const auto put = [&](int e, typename Q::mem_t q) {
+        typename Q::mem_t *o = reinterpret_cast<typename Q::mem_t *>(run + e);
+        if constexpr (NT) __builtin_nontemporal_store(q, o);
+        else *o = q;
+    };
+    if (full) {  // straight line: the reads are all issued before the first store
+#pragma unroll
+        for (int m = 0; m < Q::P; ++m) put(Q::V * (lane + 64 * m), piece(m));
+    } else {
+#pragma unroll
+        for (int m = 0; m < Q::P; ++m) {
+            const int e = Q::V * (lane + 64 * m);
+            if (e + Q::V <= n) {
+                put(e, piece(m));
+            } else if (e < n) {
+                const typename Q::mem_t q = piece(m);
+#pragma unroll
+                for (int i = 0; i < Q::V; ++i)
+                    if (e + i < n) out_store<NT>(run + e + i, q[i]);
+            }
+        }
+    }
+    if constexpr (Q::P > 1) wave_lds_sync();
 }
 
 // Window of workgroup b in a launch that takes its n windows last to first.

@@ -361,3 +361,49 @@ def test_graph_replay_matches_eager():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(coords, ex) and torch.equal(grad, eg)
+
+
+@pytest.mark.parametrize("model", ["backbone", "fullatom"])
+@pytest.mark.parametrize("K", [1, 2, 4])
+def test_buffers_at_any_float(model, K):
+    """Every call takes contiguous tensors that start at any float of an
+    allocation, at sizes whose planes start at other offsets still: the wave
+    runs move several floats per access.  The arithmetic is the same, so the
+    results are too."""
+    import torch
+    a2c = _a2c()
+    if model == "fullatom" and K == 4:
+        pytest.skip("the full-atom kernels take one or two residues per lane")
+    rng = np.random.Generator(np.random.PCG64(77 + K))
+    for lengths in ([1], [3, 0, 1], [67, 131, 1, 259], [64 * K] * 3, [1203]):
+        off = offsets_from_lengths(lengths)
+        R = int(off[-1])
+        seq = rng.integers(0, 20, R).astype(np.uint8) if model == "fullatom" else None
+        plan = a2c.Plan(model, offsets=off, seq=seq)
+        plan.set_schedule(K, 2)
+        g0 = torch.randn(3, plan.n_atoms, device="cuda")
+        want = None
+        for shift in range(4):
+            def at(t, k=shift):
+                buf = torch.full((t.numel() + 8,), float("nan"), device="cuda")
+                v = buf[k:k + t.numel()].view(t.shape)
+                return v.copy_(t), buf
+            ang, _ = at(torch.linspace(-3, 3, plan.n_planes * R, device="cuda").view(-1, R))
+            g, _ = at(g0)
+            outs = [at(torch.zeros(3, plan.n_atoms, device="cuda")),
+                    at(torch.zeros(plan.n_planes, R, device="cuda")),
+                    at(torch.zeros(plan.n_planes, R, device="cuda")),
+                    at(torch.zeros(3, plan.n_atoms, device="cuda")),
+                    at(torch.zeros(plan.n_planes, R, device="cuda"))]
+            views = [v for v, _ in outs]
+            plan.forward(ang, views[0])
+            plan.backward(ang, g, coords=views[0], grad_angles=views[1])
+            plan.backward(ang, g, grad_angles=views[2])
+            plan.mse_step(ang, g, coords=views[3], grad_angles=views[4])
+            got = [v.clone() for v in views]
+            want = want or got
+            for a, b in zip(got, want):
+                assert torch.equal(a, b)
+            for v, buf in outs:  # nothing outside the tensor is written
+                assert bool(torch.isnan(buf[:shift]).all())
+                assert bool(torch.isnan(buf[shift + v.numel():]).all())
