@@ -129,6 +129,7 @@ struct Sched {
     int32_t n_rec = 0;                   // its windows or tiles
     int32_t *d_rec_wstart = nullptr;     // n_rec + 1 boundaries
     int32_t *d_tile_res = nullptr;       // n_rec (first, end) residue pairs, longest first
+    int32_t cap() const { return kWave * K * W; }  // residues of a fixed window
 };
 
 }  // namespace a2c

@@ -243,12 +243,14 @@ __device__ __forceinline__ void load_angles(float *buf, const float *__restrict_
 // QUAT: the comparison form with a unit quaternion + translation scan state
 // (Quat) in place of the 3x4 affine (lane aggregates converted after their
 // polar step).
-template <int K, int LB, bool QUAT = false>
+// LINK: as in the recomputing adjoint (the comparison form reads its windows).
+template <int K, int LB, bool LINK, bool QUAT>
 __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
     const float *__restrict__ ang, float *__restrict__ xyz, const uint32_t *__restrict__ head_bits,
-    const int32_t *__restrict__ wstart, const int32_t *__restrict__ look_first,
+    const int32_t *__restrict__ wstart, int32_t cap, const int32_t *__restrict__ look_first,
     uint64_t *__restrict__ status, int64_t R, BBParams P)
 {
+    static_assert(LINK || !QUAT, "the comparison form links its windows");
     extern __shared__ __align__(16) float stage_mem[];
     __shared__ FwdShared sh;
     __shared__ float carry_sh[12];
@@ -257,7 +259,8 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = blockIdx.x;
-    const int64_t ts = wstart[t], te = wstart[t + 1];
+    int64_t ts, te;
+    window_range<LINK && !QUAT>(wstart, cap, R, t, ts, te);
     const int nact = (int)((te - ts + RUN - 1) / RUN);
     const int64_t rbase = ts + (int64_t)wave * RUN;
     const int nres = (int)max((int64_t)0, min((int64_t)RUN, te - rbase));
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
     // read ahead of the angles so that their latency overlaps
     uint64_t prev = 0;
     int64_t first = t;
-    if (wave == 0) {
+    if (LINK && wave == 0) {
         prev = lb_load(status + t * kLbWords);
         first = look_first[t];
     }
@@ -341,7 +344,7 @@ __global__ __launch_bounds__(LB, 4) void bb_forward_flat_kernel(
         X = block_prefix_windows_quat(quat_from_aff(m), heads, nact, active, sh, carry_sh, status, t,
                                       first, prev);
     else
-        X = block_prefix_windows(m, heads, nact, active, sh, carry_sh, status, t, first, prev);
+        X = block_prefix_windows<LINK>(m, heads, nact, active, sh, carry_sh, status, t, first, prev);
     if (!active) return;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
@@ -605,7 +608,7 @@ template <int K, int LB, int GM, bool LINK>
 __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     const float *__restrict__ ang, const float *__restrict__ g, float *__restrict__ gang,
     float *__restrict__ xyz_out, float *__restrict__ loss_out,
-    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart,
+    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart, int32_t cap,
     const int32_t *__restrict__ look_first, uint64_t *__restrict__ status_fwd,
     const int32_t *__restrict__ look_last, uint64_t *__restrict__ status, int64_t R, BBParams P,
     int32_t spined, int32_t nt)
@@ -621,7 +624,8 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t =
         LINK && spined ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-    const int64_t ts = wstart[t], te = wstart[t + 1];
+    int64_t ts, te;
+    window_range<LINK>(wstart, cap, R, t, ts, te);
     const int nact = (int)((te - ts + RUN - 1) / RUN);
     const int64_t rbase = ts + (int64_t)wave * RUN;
     const int nres = (int)max((int64_t)0, min((int64_t)RUN, te - rbase));
@@ -736,10 +740,11 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
 //      wrench of everything after the atom in its chain, then add the atom;
 //   4. LDS transpose, coalesced stores of the phi, psi, omega planes
 //      (non-temporal when nt: large plans).
-template <int K, int LB>
+// LINK: as in the recomputing adjoint.
+template <int K, int LB, bool LINK>
 __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     const float *__restrict__ xyz, const float *__restrict__ g, float *__restrict__ gang,
-    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart,
+    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart, int32_t cap,
     const int32_t *__restrict__ look_last, uint64_t *__restrict__ status, int64_t R, BBParams P,
     int32_t rev, int32_t nt)
 {
@@ -750,8 +755,9 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     constexpr int V = K == 2 ? 1 : piece_floats(3 * K);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t = rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-    const int64_t ts = wstart[t], te = wstart[t + 1];
+    const int64_t t = LINK && rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    int64_t ts, te;
+    window_range<LINK>(wstart, cap, R, t, ts, te);
     const int nact = (int)((te - ts + RUN - 1) / RUN);
     const int64_t rbase = ts + (int64_t)wave * RUN;
     const int nres = (int)max((int64_t)0, min((int64_t)RUN, te - rbase));
@@ -761,7 +767,7 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     const int64_t A = 3 * R;
     uint64_t prev = 0;
     int64_t last = t;
-    if (wave == 0) {
+    if (LINK && wave == 0) {
         prev = lb_load(status + t * kLbWords);
         last = look_last[t];
     }
@@ -807,7 +813,7 @@ __global__ __launch_bounds__(LB) void bb_backward_coords_flat_kernel(
     bool f = false;
     if (active) agg = bb_lane_wrench<K>(x, y, z, gx, gy, gz, lm, f);
     const uint64_t ends = __builtin_amdgcn_ballot_w64(f);
-    const Wrench S = block_suffix_windows(agg, ends, nact, active, sh, carry_sh, status, t, last, prev);
+    const Wrench S = block_suffix_windows<LINK>(agg, ends, nact, active, sh, carry_sh, status, t, last, prev);
     if (!active) return;
     float gr[3][K];
     bb_lane_torques<K>(S, x, y, z, gx, gy, gz, px, py, pz, hm, lm, P, gr);
@@ -920,9 +926,10 @@ template <int K, int LB, bool QUAT>
 hipError_t fwd_kl(const a2c_plan &p, const float *ang, float *xyz, hipStream_t s)
 {
     const dim3 grid(p.fs.n_win), block(p.fs.W * kWave);
-    hipLaunchKernelGGL((bb_forward_flat_kernel<K, LB, QUAT>), grid, block, stage_bytes<K>(p.fs.W), s,
-                       ang, xyz, p.d_head_bits, p.fs.d_wstart, p.fs.d_look, p.fs.d_status, p.R,
-                       p.bb);
+    hipLaunchKernelGGL((p.fs.whole_chains && !QUAT ? bb_forward_flat_kernel<K, LB, QUAT, QUAT>
+                                                   : bb_forward_flat_kernel<K, LB, true, QUAT>),
+                       grid, block, stage_bytes<K>(p.fs.W), s, ang, xyz, p.d_head_bits,
+                       p.fs.d_wstart, p.fs.cap(), p.fs.d_look, p.fs.d_status, p.R, p.bb);
     return hipGetLastError();
 }
 
@@ -950,13 +957,15 @@ hipError_t bwd_kl(const a2c_plan &p, const float *ang, const float *xyz, const f
     const dim3 block(W * kWave);
     const size_t lds = stage_bytes<K>(W);
     if (xyz)
-        hipLaunchKernelGGL((bb_backward_coords_flat_kernel<K, LB>), dim3(S.n_win), block, lds, s,
-                           xyz, g, gang, p.d_head_bits, S.d_wstart, S.d_look, S.d_status, p.R, p.bb,
+        hipLaunchKernelGGL((S.whole_chains ? bb_backward_coords_flat_kernel<K, LB, false>
+                                           : bb_backward_coords_flat_kernel<K, LB, true>),
+                           dim3(S.n_win), block, lds, s, xyz, g, gang, p.d_head_bits, S.d_wstart,
+                           S.cap(), S.d_look, S.d_status, p.R, p.bb,
                            S.whole_chains ? 0 : 1, p.nt_grad ? 1 : 0);
     else if (!S.rec_chunked)
         hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradLoad, false>),
                            dim3(S.n_rec), block, lds, s, ang, g, gang, nullptr, nullptr,
-                           p.d_head_bits, S.d_rec_wstart, nullptr, nullptr, nullptr, nullptr, p.R,
+                           p.d_head_bits, S.d_rec_wstart, 0, nullptr, nullptr, nullptr, nullptr, p.R,
                            p.bb, 0, p.nt_grad ? 1 : 0);
     else
         hipLaunchKernelGGL((bb_backward_chunked_kernel<K, LB>), dim3(S.n_rec), block, lds, s, ang,
@@ -977,13 +986,13 @@ hipError_t mse_kl(const a2c_plan &p, const float *ang, const float *tgt, float *
     // them 24.9 and 27.1 us at (4, 8).
     if (S.n_own)
         hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradMse, false>), dim3(S.n_own),
-                           block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_own_wstart,
+                           block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_own_wstart, 0,
                            nullptr, nullptr, nullptr, S.d_own_status, p.R, p.bb, 0,
                            p.nt_grad ? 1 : 0);
     else {
         if (S.spined) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
         hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradMse, true>), dim3(S.n_win),
-                           block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_wstart,
+                           block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_wstart, S.cap(),
                            S.d_look_fwd, S.d_status_fwd, S.d_look, S.d_status, p.R, p.bb,
                            S.spined ? 1 : 0, p.nt_grad ? 1 : 0);
     }
@@ -1014,10 +1023,12 @@ void bb_allow_large_lds()
 {
     static bool done = false;
     if (done) return;
-    for (const void *k : {(const void *)bb_forward_flat_kernel<8, kLbSmall>,
-                          (const void *)bb_forward_flat_kernel<8, kLbLarge>,
-                          (const void *)bb_forward_flat_kernel<8, kLbSmall, true>,
-                          (const void *)bb_forward_flat_kernel<8, kLbLarge, true>})
+    for (const void *k : {(const void *)bb_forward_flat_kernel<8, kLbSmall, false, false>,
+                          (const void *)bb_forward_flat_kernel<8, kLbLarge, false, false>,
+                          (const void *)bb_forward_flat_kernel<8, kLbSmall, true, false>,
+                          (const void *)bb_forward_flat_kernel<8, kLbLarge, true, false>,
+                          (const void *)bb_forward_flat_kernel<8, kLbSmall, true, true>,
+                          (const void *)bb_forward_flat_kernel<8, kLbLarge, true, true>})
         (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)stage_bytes<8>(kMaxWaves));
     done = true;

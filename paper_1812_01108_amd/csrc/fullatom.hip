@@ -464,12 +464,10 @@ __device__ __forceinline__ LaneRun<K> lane_run(const ChunkRange &k,
     L.cnt = (int)max((int64_t)0, min((int64_t)K, k.ce - L.rs));
     L.hm = lane_head_mask<K>(head_bits, L.rs, k.ce, L.cnt);
     L.lm = lane_head_mask<K>(head_bits, L.rs + 1, k.ce + 1, L.cnt);
-    L.A0 = 0;
-    L.natoms = 0;
-    if (L.active) {
-        L.A0 = __builtin_amdgcn_readfirstlane(res_aoff[L.rbase]);
-        L.natoms = __builtin_amdgcn_readfirstlane(res_aoff[L.rbase + L.nres]) - (int)L.A0;
-    }
+    // (waves past the window's end: no atoms, and no branch around the loads)
+    const int64_t rb = min(L.rbase, k.ce);
+    L.A0 = __builtin_amdgcn_readfirstlane(res_aoff[rb]);
+    L.natoms = __builtin_amdgcn_readfirstlane(res_aoff[rb + L.nres]) - (int)L.A0;
     return L;
 }
 
@@ -555,8 +553,9 @@ __device__ __forceinline__ Aff frame_get(const float *frames, int block, int i)
 // transforms since its last chain head (the identity for an empty lane);
 // head: a chain starts in the lane; n_units: lanes holding residues.  Every
 // thread of the block calls it; flags (kMaxWaves words) and frames
-// (frame_bytes) are LDS.  The frames are free again after the caller's next
+// (frame_bytes) are LDS.  LINK as in block_prefix_windows.  The frames are free again after the caller's next
 // barrier.
+template <bool LINK>
 __device__ __forceinline__ Aff entering_frame(const Aff &unit, bool head, int n_units,
                                               float *frames, uint64_t (&flags)[kMaxWaves],
                                               SpineShared &sh, float (&carry_sh)[12],
@@ -604,8 +603,8 @@ __device__ __forceinline__ Aff entering_frame(const Aff &unit, bool head, int n_
         aff_orthonormalise(m);
     }
     const uint64_t heads = __builtin_amdgcn_ballot_w64(hm != 0u);
-    Aff cur = block_prefix_windows(m, heads, ns, spine, sh, carry_sh, status, t, first, prev,
-                                   published);
+    Aff cur = block_prefix_windows<LINK>(m, heads, ns, spine, sh, carry_sh, status, t, first, prev,
+                                         published);
     if (spine) {
 #pragma unroll
         for (int j = 0; j < kGroup; ++j) {
@@ -776,10 +775,13 @@ __device__ __forceinline__ void fa_emit_residue(const FADevTable &tab, int type,
 // on a quarter of the waves, one loop over the last frame's atoms and 12-byte
 // stage accesses took 2000 chains of 50..2000 residues from 59.7 to 51.5 us at
 // (1, 4), 500 chains of 151 from 11.9 to 10.7 us at (1, 6).
-template <int K, int LB, bool STG = true>
+// LINK = false: windows of whole chains, none of which needs another's frame
+// (no words read or written: forward and adjoint of 64 chains of 300 17.05 to
+// 16.4 us); true: fixed windows.
+template <int K, int LB, bool LINK, bool STG>
 __global__ __launch_bounds__(LB) void fa_forward_flat_kernel(
     const float *__restrict__ ang, float *__restrict__ xyz, const uint32_t *__restrict__ head_bits,
-    const int32_t *__restrict__ wstart, const int32_t *__restrict__ res_aoff,
+    const int32_t *__restrict__ wstart, int32_t cap, const int32_t *__restrict__ res_aoff,
     const uint8_t *__restrict__ seq, const FADevTable *__restrict__ gtab,
     const int32_t *__restrict__ look_first,
     uint64_t *__restrict__ status, int64_t R, int64_t A, BBParams P, int stage_atoms)
@@ -792,13 +794,12 @@ __global__ __launch_bounds__(LB) void fa_forward_flat_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = blockIdx.x;
     ChunkRange k;
-    k.cs = wstart[t];
-    k.ce = wstart[t + 1];
+    window_range<LINK>(wstart, cap, R, t, k.cs, k.ce);
     k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
     const TableCopy tc = table_load(gtab);
     uint64_t prev = 0;
     int64_t first = t;
-    if (wave == 0) {
+    if (LINK && wave == 0) {
         prev = lb_load(status + t * kLbWords);
         first = look_first[t];
     }
@@ -812,8 +813,8 @@ __global__ __launch_bounds__(LB) void fa_forward_flat_kernel(
         unit = spine_unit<K>(in, L, P);
     }
     const int n_units = (int)((k.ce - k.cs + K - 1) / K);
-    Aff cur = entering_frame(unit, L.hm != 0u, n_units, stage_mem, unit_flags, sh, carry_sh, status,
-                             t, first, prev, false);
+    Aff cur = entering_frame<LINK>(unit, L.hm != 0u, n_units, stage_mem, unit_flags, sh, carry_sh,
+                                   status, t, first, prev, false);
     if (STG) __syncthreads();  // the stage takes the frames' place
     if (!L.active) return;
     float *st = stage_mem + (size_t)wave * 3 * stage_atoms;
@@ -952,11 +953,12 @@ struct AtomForce {
 // nt: the angle gradients go out with non-temporal stores (large plans).
 // STG: atoms go through the per-wave LDS stage; otherwise global memory is
 // addressed directly (schedules whose stage does not fit the LDS).
-template <int K, bool RECOMPUTE, int LB, int GM = kGradLoad, bool STG = true>
+// LINK: as in the forward.
+template <int K, bool RECOMPUTE, int LB, int GM, bool LINK, bool STG>
 __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     const float *__restrict__ ang, const float *__restrict__ xyz, const float *__restrict__ g,
     float *__restrict__ gang, float *__restrict__ xyz_out, float *__restrict__ loss_out,
-    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart,
+    const uint32_t *__restrict__ head_bits, const int32_t *__restrict__ wstart, int32_t cap,
     const int32_t *__restrict__ res_aoff, const uint8_t *__restrict__ seq,
     const FADevTable *__restrict__ gtab, uint64_t *__restrict__ status_fwd,
     const int32_t *__restrict__ look_fwd,
@@ -974,21 +976,23 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     __shared__ float loss_tot[GM == kGradMse ? kMaxWaves : 1];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t = rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const int64_t t = LINK && rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
     ChunkRange k;
-    k.cs = wstart[t];
-    k.ce = wstart[t + 1];
+    window_range<LINK>(wstart, cap, R, t, k.cs, k.ce);
     k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
     const TableCopy tc = table_load(gtab);
-    uint64_t prev = 0, prev_f = 0;
+    uint64_t prev = 0, prev_f = 0, prev_l = 0;
     int64_t last = t, first = t;
     if (wave == 0) {
-        prev = lb_load(status + t * kLbWords);
-        last = look_last[t];
-        if (RECOMPUTE) {
-            prev_f = lb_load(status_fwd + t * kLbWords);
-            first = look_fwd[t];
+        if constexpr (LINK) {
+            prev = lb_load(status + t * kLbWords);
+            last = look_last[t];
+            if (RECOMPUTE) {
+                prev_f = lb_load(status_fwd + t * kLbWords);
+                first = look_fwd[t];
+            }
         }
+        if (GM == kGradMse && loss_out) prev_l = lb_load(status + t * kLbWords + kLbLossWord);
     }
     const LaneRun<K> L = lane_run<K>(k, head_bits, res_aoff);
     const LaneRes<K, RECOMPUTE> lr = load_lane_res<K, RECOMPUTE>(L, seq, res_aoff, ang, R);
@@ -1009,8 +1013,8 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
             unit = spine_unit<K>(in, L, P);
         }
         const int n_units = (int)((k.ce - k.cs + K - 1) / K);
-        cur = entering_frame(unit, L.hm != 0u, n_units, stage_mem, unit_flags, shf, fcarry_sh,
-                             status_fwd, t, first, prev_f, spined != 0);
+        cur = entering_frame<LINK>(unit, L.hm != 0u, n_units, stage_mem, unit_flags, shf,
+                                   fcarry_sh, status_fwd, t, first, prev_f, spined != 0);
     }
     __syncthreads();  // the stage takes the frames' place; the table is complete
     if (STG && L.active) {
@@ -1164,8 +1168,8 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
             wave_lds_sync();
         }
     }
-    Wrench S = block_suffix_windows(agg, __builtin_amdgcn_ballot_w64(f_end), k.nact, L.active, shb,
-                                    rcarry_sh, status, t, last, prev);
+    Wrench S = block_suffix_windows<LINK>(agg, __builtin_amdgcn_ballot_w64(f_end), k.nact, L.active,
+                                          shb, rcarry_sh, status, t, last, prev);
     if (L.active) {
 #pragma unroll
         for (int j = K - 1; j >= 0; --j) {
@@ -1176,7 +1180,7 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
         }
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) lb_loss_commit(force.loss, status, t, gridDim.x, prev, loss_out, loss_tot);
+        if (loss_out) lb_loss_commit(force.loss, status, t, gridDim.x, prev_l, loss_out, loss_tot);
     }
 }
 
@@ -1185,9 +1189,11 @@ hipError_t fa_fwd_kl(const a2c_plan &p, const float *ang, float *xyz, hipStream_
 {
     const size_t stage = STG ? (size_t)p.fs.W * 3 * p.fs.fa_stage_atoms * sizeof(float) : 0;
     const size_t lds = std::max(stage, frame_bytes(p.fs.W));
-    hipLaunchKernelGGL((fa_forward_flat_kernel<K, LB, STG>), dim3(p.fs.n_win), dim3(p.fs.W * kWave),
-                       lds, s, ang, xyz, p.d_head_bits, p.fs.d_wstart, p.d_res_atom_off, p.d_seq,
-                       p.d_fa, p.fs.d_look, p.fs.d_status, p.R, p.A, p.bb, p.fs.fa_stage_atoms);
+    hipLaunchKernelGGL((p.fs.whole_chains ? fa_forward_flat_kernel<K, LB, false, STG>
+                                          : fa_forward_flat_kernel<K, LB, true, STG>),
+                       dim3(p.fs.n_win), dim3(p.fs.W * kWave), lds, s, ang, xyz, p.d_head_bits,
+                       p.fs.d_wstart, p.fs.cap(), p.d_res_atom_off, p.d_seq, p.d_fa, p.fs.d_look,
+                       p.fs.d_status, p.R, p.A, p.bb, p.fs.fa_stage_atoms);
     return hipGetLastError();
 }
 
@@ -1217,9 +1223,10 @@ void fa_bwd_launch(const a2c_plan &p, const float *ang, const float *xyz, const 
     size_t lds = STG ? (size_t)S.W * (RECOMPUTE ? 3 : 6) * S.fa_stage_atoms * sizeof(float) : 0;
     if (RECOMPUTE) lds = std::max(lds, frame_bytes(S.W));
     const bool rev = RECOMPUTE ? spined : !S.whole_chains;
-    hipLaunchKernelGGL((fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, STG>), dim3(S.n_win),
-                       dim3(S.W * kWave), lds, s, ang, xyz, g, gang, xyz_out, loss_out,
-                       p.d_head_bits, S.d_wstart, p.d_res_atom_off, p.d_seq, p.d_fa,
+    hipLaunchKernelGGL((S.whole_chains ? fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, false, STG>
+                                       : fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, true, STG>),
+                       dim3(S.n_win), dim3(S.W * kWave), lds, s, ang, xyz, g, gang, xyz_out, loss_out,
+                       p.d_head_bits, S.d_wstart, S.cap(), p.d_res_atom_off, p.d_seq, p.d_fa,
                        S.d_status_fwd, S.d_look_fwd, S.d_look, S.d_status, p.R, p.A, p.bb,
                        S.fa_stage_atoms, rev ? 1 : 0, spined ? 1 : 0, p.nt_grad ? 1 : 0);
 }
@@ -1314,13 +1321,20 @@ static void allow_lds(F kernel)
                               kMaxDynamicLds);
 }
 
+template <int K, int LB, bool LINK>
+static void allow_lds_kll()
+{
+    allow_lds(fa_forward_flat_kernel<K, LB, LINK, true>);
+    allow_lds(fa_backward_flat_kernel<K, false, LB, kGradLoad, LINK, true>);
+    allow_lds(fa_backward_flat_kernel<K, true, LB, kGradLoad, LINK, true>);
+    allow_lds(fa_backward_flat_kernel<K, true, LB, kGradMse, LINK, true>);
+}
+
 template <int K, int LB>
 static void allow_lds_kl()
 {
-    allow_lds(fa_forward_flat_kernel<K, LB>);
-    allow_lds(fa_backward_flat_kernel<K, false, LB>);
-    allow_lds(fa_backward_flat_kernel<K, true, LB>);
-    allow_lds(fa_backward_flat_kernel<K, true, LB, kGradMse, true>);
+    allow_lds_kll<K, LB, false>();
+    allow_lds_kll<K, LB, true>();
 }
 
 void fa_allow_large_lds()

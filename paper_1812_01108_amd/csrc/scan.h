@@ -722,6 +722,23 @@ __device__ __forceinline__ void lanes_to_run(float *buf, const float (&in)[N],
     if constexpr (Q::P > 1) wave_lds_sync();
 }
 
+// Residues [ts, te) of window t: fixed windows of cap residues follow from t
+// alone (FIXED), so that nothing waits for a load before the inputs' own (one
+// memory latency of every workgroup; full-atom forward and adjoint of 4096
+// chains of 50..2000 264.9 to 261.6 us); others are read.
+template <bool FIXED>
+__device__ __forceinline__ void window_range(const int32_t *__restrict__ wstart, int32_t cap,
+                                             int64_t R, int64_t t, int64_t &ts, int64_t &te)
+{
+    if constexpr (FIXED) {
+        ts = t * cap;
+        te = min(ts + cap, R);
+    } else {
+        ts = wstart[t];
+        te = wstart[t + 1];
+    }
+}
+
 // Window of workgroup b in a launch that takes its n windows last to first.
 // Workgroups are spread over the eight XCDs round robin (b mod 8), so within
 // each class b mod 8 the windows go last to first: window t then runs on the
