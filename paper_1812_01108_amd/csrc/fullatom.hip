@@ -770,7 +770,7 @@ __device__ __forceinline__ void fa_emit_residue(const FADevTable &tab, int type,
 // does not fit the LDS, straight to global memory).  The stage takes the
 // frames' place once every lane holds its own.
 // Bound by VALU issue and waits in turn: 1137 instructions per wave of 64
-// residues at K = 1 (62 us of issue for 2.16 M residues in some 105 us, where
+// residues at K = 1 (62 us of issue for 2.16 M residues in some 114 us, where
 // the 288 MB would take 56), 16 waves per CU (the LDS stages).  The spine scan
 // on a quarter of the waves, one loop over the last frame's atoms and 12-byte
 // stage accesses took 2000 chains of 50..2000 residues from 59.7 to 51.5 us at
