@@ -221,10 +221,10 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  *     adjoints take fixed windows last to first, in each class of workgroup
  *     index mod 8 separately, and whole-chain ones in order; those that
  *     recompute the frames take them in order and also wait on the windows
- *     their last chain runs into, unless a chain spans more than 32 windows:
+ *     their last chain runs into, unless a chain spans more than 8 windows:
  *     then a spine-only pass over the same windows, which waits on nothing,
- *     goes first); a launch therefore progresses whenever the device
- *     holds 32 of its workgroups at once.  Consequently two such calls on one
+ *     goes first, and they take them last to first too); a launch therefore
+ *     progresses whenever the device holds 8 of its workgroups at once.  Consequently two such calls on one
  *     plan must not run at the same time (on different streams).
  *   - The backbone adjoint that recomputes the frames (a2c_backward without
  *     d_coords) hands nothing between workgroups.  Where every chain fits in

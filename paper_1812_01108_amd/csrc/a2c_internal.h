@@ -85,9 +85,12 @@ struct FADevTable {
 };
 
 // Windows ahead of its own that a window of a recomputing adjoint may wait
-// on: a device (or a partition of one) that holds 32 workgroups at once makes
-// progress.  Batches with a chain over more windows take a spine pass.
-constexpr int kMaxAhead = 31;
+// on.  A launch whose windows wait ahead progresses only where the device (a
+// partition, a masked stream, what other work leaves of it) holds all of them
+// at once: 8 workgroups, as the adjoints that take their windows last to first
+// need too (reverse_window).  Batches with a chain over more windows take a
+// spine pass and then go last to first.
+constexpr int kMaxAhead = 7;
 
 // One scan schedule: K residues per lane, W waves per workgroup, and the
 // layouts built for them, in chunks of C = 64 W K residues.

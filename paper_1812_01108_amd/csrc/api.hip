@@ -385,20 +385,49 @@ bool one_round(const a2c_plan &p, int32_t K, int32_t W, size_t fixed, int32_t si
     return holds((int64_t)st.size() - 1, most_run_atoms(p, st, run));
 }
 
+// Whether some chain runs over more than kMaxAhead + 1 fixed windows of `cap`
+// residues, so that the recomputing adjoints take a spine pass first.
+bool spans_far(const a2c_plan &p, int64_t cap)
+{
+    if (p.max_len <= kMaxAhead * cap) return false;
+    for (size_t c = 0; c + 1 < p.res_off.size(); ++c)
+        if (p.res_off[c + 1] > p.res_off[c] &&
+            (p.res_off[c + 1] - 1) / cap - p.res_off[c] / cap > kMaxAhead)
+            return true;
+    return false;
+}
+
+// Waves of the recomputing adjoints where chains run over several windows:
+// four, or eight where that saves the spine pass, which costs more than eight
+// waves do.  Full-atom, one residue per lane, recomputing and fused step, us:
+// 512 chains of 50..2000 25.7 and 31.8 at W = 4 with the pass, 19.8 and 26.3 at
+// W = 8; 4096 of them 149 and 206, 146 and 199; where eight need the pass too
+// (20 of 3000..6000) 18.4 and 22.2 at W = 4, 20.3 and 24.7 at W = 8.  Backbone
+// fused step, 8 chains of 1500..4000 15.2 and 12.2 (from coordinates 5.2 and 5.4).
+int32_t linked_waves(const a2c_plan &p, int32_t K)
+{
+    const int64_t run = (int64_t)kWave * K;
+    return spans_far(p, 4 * run) && !spans_far(p, 8 * run) ? 8 : 4;
+}
+
 // A launch just over one round takes nearly two: `s` if it is one round, else
-// the fewest residues per lane (one, up to most_K) and waves that make it one,
-// else `s`.  simd_waves[K - 1]: waves a SIMD's registers hold.  Forward: 2000
+// the fewest residues per lane (one, up to most_K) and waves that make it one
+// (adjoint: and that need no spine pass where `s` needs none), else `s`.
+// simd_waves[K - 1]: waves a SIMD's registers hold.  Forward: 2000
 // chains of 151, 1573 windows at W = 3 23.2, 500 of four chains at W = 10 15.9;
 // 580 chains of 50..2000, 24.3 at W = 4, 16.8 at W = 6.  Recomputing adjoint:
 // 550 of them, 30.8 at (1, 4), 23.7 at (2, 3).
 Shape prefer_one_round(const a2c_plan &p, Shape s, size_t fixed, int32_t most_K,
-                       const int32_t (&simd_waves)[2])
+                       const int32_t (&simd_waves)[2], bool adjoint)
 {
     if (one_round(p, s.K, s.W, fixed, simd_waves[s.K - 1])) return s;
+    const auto far = [&](int32_t K, int32_t W) { return spans_far(p, (int64_t)kWave * K * W); };
+    const bool near_only = adjoint && !far(s.K, s.W);
     // (two residues per lane and more than eight waves spill)
     for (int32_t K = 1; K <= most_K; ++K)
         for (int32_t W = 2; W <= kMaxWaves / K; ++W)
-            if (one_round(p, K, W, fixed, simd_waves[K - 1])) return {K, W};
+            if (one_round(p, K, W, fixed, simd_waves[K - 1]) && !(near_only && far(K, W)))
+                return {K, W};
     return s;
 }
 
@@ -414,7 +443,7 @@ Shape default_forward(const a2c_plan &p)
         const int32_t whole = waves_for(p.max_len, 1);
         const Shape s{1, whole <= 8 ? pack_waves(p, 1, whole, 8)
                                     : std::min<int32_t>(R > 400000 ? 8 : 4, whole)};
-        return prefer_one_round(p, s, 6032, 1, {6, 5});
+        return prefer_one_round(p, s, 6032, 1, {6, 5}, false);
     }
     // a batch of a few chunks keeps a chunk that holds its longest chain
     if (p.max_len > 1024 && p.max_len <= 4096 && R <= 4 * 4096) return {4, waves_for(p.max_len, 4)};
@@ -435,12 +464,11 @@ Shape default_adjoint(const a2c_plan &p, Shape &rec)
 {
     const int64_t R = p.R;
     if (p.model == A2C_FULLATOM) {
-        // as the forward, but four waves for large batches too (4096 chains,
-        // recomputing: 141.5 and 145.7 at W = 8)
+        // as the forward, but four waves for large batches too
         const int32_t whole = waves_for(p.max_len, 1);
-        rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : 4};
-        if (rec.W > 4 && (int64_t)kWave * rec.W * p.n_cu < R) rec.W = 4;
-        return rec = prefer_one_round(p, rec, 7024, 2, {4, 3});
+        rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : linked_waves(p, 1)};
+        if (whole <= 8 && rec.W > 4 && (int64_t)kWave * rec.W * p.n_cu < R) rec.W = 4;
+        return rec = prefer_one_round(p, rec, 7024, 2, {4, 3}, true);
     }
     // from coordinates: 256 x 700 7.2 at (4, 3), 5.2 at (1, 12); 700 chains of
     // 20..1000 9.2 at (4, 4), 8.3 at (2, 8); 6000 of them 41.4 and 41.9 at
@@ -454,7 +482,7 @@ Shape default_adjoint(const a2c_plan &p, Shape &rec)
     else if (whole <= most) s.W = pack_waves(p, s.K, whole, most);
     // long chains: 48 of 1500..6000, from coordinates 10.7 at (4, 16), 6.6 at
     // (2, 8), fused step 22.1 and 14.6; 8 of 1500..4000, 5.3 and 11.6 at (1, 4)
-    else if (R <= 65536) s.W = 4;
+    else if (R <= 65536) s.W = linked_waves(p, s.K);
     else s = {2, 8};
     // the adjoint that recomputes the frames hands nothing over: a chunk that
     // holds the longest chain, up to 4096, and beyond that the one whose
