@@ -258,7 +258,13 @@ a2c_status a2c_plan_get_schedule(const a2c_plan *plan, int32_t *res_per_lane,
  * set or report one of them alone (same arguments, checks and
  * synchronisation as a2c_plan_set_schedule; on failure that schedule is
  * unchanged), except that the backbone forward also takes 8 residues per
- * lane.  Results do not depend on the schedules beyond float32 rounding. */
+ * lane.  The adjoint schedule a plan starts with may give the backbone adjoint
+ * that recomputes the frames a chunk of its own (one that holds the longest
+ * chain, or whose chunk walk is faster); setting that pair again, by either
+ * setter, brings the same chunk back, and any other pair is the chunk of every
+ * adjoint form.  n_tiles of the adjoint schedule counts the windows
+ * (full-atom) or the whole-chain tiles (backbone) of the reported pair.
+ * Results do not depend on the schedules beyond float32 rounding. */
 a2c_status a2c_plan_set_forward_schedule(a2c_plan *plan, int32_t res_per_lane,
                                          int32_t waves_per_group, void *stream);
 a2c_status a2c_plan_set_adjoint_schedule(a2c_plan *plan, int32_t res_per_lane,

@@ -92,6 +92,12 @@ struct FADevTable {
 // spine pass and then go last to first.
 constexpr int kMaxAhead = 7;
 
+// Residues per lane and waves per workgroup.
+struct Shape {
+    int32_t K, W;
+    bool operator==(const Shape &o) const { return K == o.K && W == o.W; }
+};
+
 // One scan schedule: K residues per lane, W waves per workgroup, and the
 // layouts built for them, in chunks of C = 64 W K residues.
 //   - windows of at most C residues with look tables (every kernel but the
@@ -100,12 +106,12 @@ constexpr int kMaxAhead = 7;
 //     [t C, t C + C), otherwise;
 //   - own windows (the backbone fused step): whole chains wherever every chain
 //     fits in one;
-//   - for that adjoint, whose chunk may differ (rec_K, rec_W: the default
-//     schedule's choice), windows of whole chains as well, or, where a chain
-//     is longer than a chunk, tiles: chains of at most one chunk packed whole,
-//     a longer chain alone.
-// n_tiles counts the layout the schedule reports: windows, or for the
-// backbone adjoint that last one.
+//   - for that adjoint, whose chunk may differ (rec: the default adjoint
+//     schedule has one of its own), windows of whole chains as well, or, where
+//     a chain is longer than a chunk, tiles: chains of at most one chunk packed
+//     whole, a longer chain alone.
+// n_tiles is what the schedule reports: windows, or for the backbone adjoint
+// the tiles its own chunk C would take.
 struct Sched {
     int32_t K = 4, W = 4, n_tiles = 0;
     int32_t n_win = 0;                   // windows (0: none)
@@ -127,7 +133,7 @@ struct Sched {
     int32_t n_own = 0;                   // own windows
     int32_t *d_own_wstart = nullptr;     // n_own + 1 boundaries
     uint64_t *d_own_status = nullptr;    // n_own x kLbWords tagged words (loss shares)
-    int32_t rec_K = 4, rec_W = 4;        // backbone adjoint that recomputes the frames
+    Shape rec{4, 4};                     // backbone adjoint that recomputes the frames
     bool rec_chunked = false;            // tiles, a chain longer than a chunk
     int32_t n_rec = 0;                   // its windows or tiles
     int32_t *d_rec_wstart = nullptr;     // n_rec + 1 boundaries
@@ -156,6 +162,10 @@ struct a2c_plan {
     // store-vs-recompute threshold: the forward's coordinates (12 bytes per
     // atom) are kept for the adjoint while they fit; 0 = always recompute
     size_t mem_budget = 0;
+    // the schedules the plan starts with, and the chunk its backbone adjoint
+    // that recomputes the frames has under them (build_sched: the same pair
+    // always brings the same chunk)
+    a2c::Shape def_fwd{0, 0}, def_adj{0, 0}, def_rec{0, 0};
     // the adjoints write the angle gradients, and the inverse map the angles,
     // with non-temporal stores (at least kNtGradBytes of them)
     bool nt_grad = false;

@@ -202,10 +202,8 @@ int64_t most_run_atoms(const a2c_plan &p, const std::vector<int64_t> &starts, in
 // Layouts of a schedule (see Sched).
 enum SchedRole { kRoleForward, kRoleAdjoint };
 
-// rec_K, rec_W: the chunk of the backbone adjoint that recomputes the frames
-// (0: the schedule's own).
 a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipStream_t s,
-                       SchedRole role, int32_t rec_K = 0, int32_t rec_W = 0)
+                       SchedRole role)
 {
     const int64_t cap = (int64_t)kWave * W * K;  // residues per chunk
     if (p->max_len > cap * kMaxChunks)
@@ -247,9 +245,10 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
             st = upload_starts(own, S.d_own_wstart, s);
             if (st == A2C_OK) st = new_words(S.d_own_status, S.n_own, s);
         }
-        S.rec_K = rec_K > 0 ? rec_K : K;
-        S.rec_W = rec_K > 0 ? rec_W : W;
-        const int64_t rec_cap = (int64_t)kWave * S.rec_W * S.rec_K;
+        // the chunk of the recomputing adjoint: the schedule's own, but for the
+        // default pair, whether it is the plan's first schedule or set again
+        S.rec = Shape{K, W} == p->def_adj ? p->def_rec : Shape{K, W};
+        const int64_t rec_cap = (int64_t)kWave * S.rec.W * S.rec.K;
         const std::vector<int64_t> rec = whole_chain_starts(p, rec_cap);
         S.rec_chunked = rec.empty();
         if (st == A2C_OK && !S.rec_chunked) {
@@ -273,7 +272,8 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
             }
             st = upload((void **)&S.d_tile_res, pairs.data(), pairs.size() * sizeof(int32_t), s);
         }
-        S.n_tiles = S.n_rec;
+        S.n_tiles = S.rec == Shape{K, W} ? S.n_rec
+                                         : (int32_t)pack_tiles(p->res_off, cap).size() - 1;
     }
     // the host tables above are read by the copies until here
     const hipError_t e = hipStreamSynchronize(s);
@@ -341,10 +341,6 @@ a2c_status apply_schedule(a2c_plan *p, int32_t K, int32_t W, hipStream_t s,
 // back in a graph; microseconds below).  Few residues want few per lane (the
 // walk over them is a serial chain, and waves are short in supply), many want
 // more (the wave scan costs the same whatever a lane holds).
-
-struct Shape {
-    int32_t K, W;
-};
 
 int32_t waves_for(int64_t len, int32_t K)
 {
@@ -516,8 +512,11 @@ a2c_status default_schedules(a2c_plan *p, hipStream_t s)
     fit_longest(*p, f, most_K);
     fit_longest(*p, b, most_K);
     fit_longest(*p, rec, most_K);
+    p->def_fwd = f;
+    p->def_adj = b;
+    p->def_rec = rec;
     a2c_status st = build_sched(p, f.K, f.W, p->fs, s, kRoleForward);
-    if (st == A2C_OK) st = build_sched(p, b.K, b.W, p->bs, s, kRoleAdjoint, rec.K, rec.W);
+    if (st == A2C_OK) st = build_sched(p, b.K, b.W, p->bs, s, kRoleAdjoint);
     return st;
 }
 

@@ -953,7 +953,7 @@ hipError_t bwd_kl(const a2c_plan &p, const float *ang, const float *xyz, const f
                   float *gang, hipStream_t s)
 {
     const Sched &S = p.bs;
-    const int W = xyz ? S.W : S.rec_W;
+    const int W = xyz ? S.W : S.rec.W;
     const dim3 block(W * kWave);
     const size_t lds = stage_bytes<K>(W);
     if (xyz)
@@ -1011,7 +1011,7 @@ template <int K>
 hipError_t bwd_k(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
                  float *gang, hipStream_t s)
 {
-    return (xyz ? p.bs.W : p.bs.rec_W) * kWave <= kLbSmall
+    return (xyz ? p.bs.W : p.bs.rec.W) * kWave <= kLbSmall
                ? bwd_kl<K, kLbSmall>(p, ang, xyz, g, gang, s)
                : bwd_kl<K, kLbLarge>(p, ang, xyz, g, gang, s);
 }
@@ -1050,7 +1050,7 @@ hipError_t launch_bb_forward_scan(const a2c_plan &p, const float *ang, float *xy
 hipError_t launch_bb_backward_scan(const a2c_plan &p, const float *ang, const float *xyz,
                                    const float *g, float *gang, hipStream_t s)
 {
-    switch (xyz ? p.bs.K : p.bs.rec_K) {
+    switch (xyz ? p.bs.K : p.bs.rec.K) {
     case 1: return bwd_k<1>(p, ang, xyz, g, gang, s);
     case 2: return bwd_k<2>(p, ang, xyz, g, gang, s);
     case 4: return bwd_k<4>(p, ang, xyz, g, gang, s);

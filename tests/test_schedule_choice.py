@@ -1,0 +1,73 @@
+"""The schedules a plan starts with, and what becomes of them: set again, they
+are the same schedules."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import to_dev
+from workloads import make_angles, offsets_from_lengths, random_sequence, upstream_grad
+
+
+def _a2c():
+    import paper_1812_01108_amd as a2c
+    return a2c
+
+
+def _plan(model, lengths, seed=901, **kw):
+    off = offsets_from_lengths(lengths)
+    R = int(off[-1])
+    rng = np.random.Generator(np.random.PCG64(seed))
+    seq = random_sequence(rng, R) if model == "fullatom" else None
+    plan = _a2c().Plan(model, offsets=off, seq=seq, **kw)
+    return plan, to_dev(make_angles(rng, R, "mixture", plan.n_planes))
+
+
+def _pair(sched):
+    return sched["res_per_lane"], sched["waves_per_group"]
+
+
+def _whole_chain_tiles(lengths, cap):
+    """Tiles of whole chains packed in order: at most cap residues, a longer
+    chain alone."""
+    n, cur = 0, cap + 1
+    for L in lengths:
+        if L == 0:
+            continue
+        if cur + L > cap:
+            n, cur = n + 1, 0
+        cur += L
+    return n
+
+
+# chains a chunk of the recomputing adjoint's own holds whole (100 of 2000
+# residues), and chains that it walks chunk by chunk
+LONG_BATCHES = {"whole": [2000, 400, 400, 400] * 100,
+                "walked": [6000, 1500, 2500, 400] * 20}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch", sorted(LONG_BATCHES))
+@pytest.mark.parametrize("setter", ["set_adjoint_schedule", "set_schedule"])
+def test_reported_adjoint_schedule_set_again(batch, setter):
+    """A plan's own adjoint schedule, read and set again (at once, and after
+    another one), runs every adjoint form as before, bit for bit."""
+    import torch
+    lengths = LONG_BATCHES[batch]
+    plan, ang = _plan("backbone", lengths)
+    g = to_dev(upstream_grad(5, plan.n_atoms))
+    coords = plan.forward(ang)
+
+    def results():
+        return [plan.backward(ang, g), plan.backward(ang, g, coords=coords),
+                plan.mse_step(ang, g)[1]]
+
+    first, sched = results(), plan.adjoint_schedule
+    K, W = _pair(sched)
+    assert sched["n_tiles"] == _whole_chain_tiles(lengths, 64 * K * W)
+    getattr(plan, setter)(K, W)
+    for _ in range(2):
+        assert plan.adjoint_schedule == sched
+        for a, b in zip(first, results()):
+            assert torch.equal(a, b)
+        getattr(plan, setter)(4, 3)   # away and back
+        plan.backward(ang, g)
+        getattr(plan, setter)(K, W)
