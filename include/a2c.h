@@ -272,12 +272,12 @@ a2c_status a2c_plan_set_adjoint_schedule(a2c_plan *plan, int32_t res_per_lane,
 a2c_status a2c_plan_get_adjoint_schedule(const a2c_plan *plan, int32_t *res_per_lane,
                                          int32_t *waves_per_group, int32_t *n_tiles);
 
-/* Autotuner: times the forward (A2C_SCAN) under every schedule
- * a2c_plan_set_forward_schedule accepts for the plan and keeps the fastest,
- * then the adjoint under every schedule a2c_plan_set_adjoint_schedule
- * accepts, on the caller's buffers (candidates in order of residues per
- * lane, then waves; a later one must be 1 % faster than the best so far to
- * replace it, so ties resolve to the smaller schedule).
+/* Autotuner: times the forward (A2C_SCAN), then the adjoint, on the caller's
+ * buffers and keeps the fastest schedule of each.  Candidates: the schedule
+ * the plan started with, its present one, then those with 1, 2, 3, 4, 6, 8, 12
+ * or 16 waves that a2c_plan_set_forward_schedule (a2c_plan_set_adjoint_schedule)
+ * accepts, in order of residues per lane, then waves; a later one must be 1 %
+ * faster than the best so far to replace it.
  *   d_angles, d_coords, d_grad_coords, d_grad_angles: buffers of the plan's
  *     sizes; their contents are overwritten (coords and grad_angles) or read.
  *   backward_from_coords: the adjoint timed: 1 a2c_backward with d_coords

@@ -211,9 +211,9 @@ class Plan:
     def autotune(self, angles: torch.Tensor, grad_coords: torch.Tensor | None = None,
                  from_coords: bool = True, reps: int = 5, cache_path: str | None = None,
                  mse_target: torch.Tensor | None = None):
-        """Time every valid schedule on these buffers and keep the fastest
-        forward and the fastest adjoint schedule (synchronises; call before
-        capturing a graph).  With mse_target, the fused training step
+        """Time the plan's default schedules, its present ones and a grid of
+        others on these buffers, and keep the fastest forward and the fastest
+        adjoint schedule (synchronises; call before capturing a graph).  With mse_target, the fused training step
         (mse_step) is timed as the adjoint.  Returns (forward, adjoint)
         schedules."""
         self._check_tensor(angles, (self.n_planes, self.n_res), "angles")

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "a2c.h"
+#include "schedule.h"
 
 namespace a2c {
 
@@ -91,12 +92,6 @@ struct FADevTable {
 // need too (reverse_window).  Batches with a chain over more windows take a
 // spine pass and then go last to first.
 constexpr int kMaxAhead = 7;
-
-// Residues per lane and waves per workgroup.
-struct Shape {
-    int32_t K, W;
-    bool operator==(const Shape &o) const { return K == o.K && W == o.W; }
-};
 
 // One scan schedule: K residues per lane, W waves per workgroup, and the
 // layouts built for them, in chunks of C = 64 W K residues.

@@ -1,7 +1,7 @@
-// Schedule autotuner: for every valid (residues per lane, waves per
-// workgroup) times the forward and the adjoint (or the fused step) separately
-// with HIP events, and keeps the fastest of each as the plan's forward and
-// adjoint schedules; choices can be kept in a small text cache.
+// Schedule autotuner: times the forward and the adjoint (or the fused step)
+// separately, with HIP events, under the plan's default schedules, its present
+// ones and a grid of (residues per lane, waves per workgroup), and keeps the
+// fastest of each; choices can be kept in a small text cache.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -132,8 +132,6 @@ extern "C" a2c_status a2c_plan_autotune(a2c_plan *p, const float *d_angles, floa
             return A2C_OK;
         }
     }
-    const int Ks[4] = {1, 2, 4, 8};
-    const int Ws[8] = {1, 2, 3, 4, 6, 8, 12, 16};
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return hip_fail(hipGetLastError(), "hipEventCreate");
@@ -172,37 +170,37 @@ extern "C" a2c_status a2c_plan_autotune(a2c_plan *p, const float *d_angles, floa
     // hold it); later ones replace the tuner's own (freed).
     bool own_f = false, own_b = false;
     for (int part = 0; part < 2 && st == A2C_OK; ++part) {
-        for (int k : Ks) {
-            for (int w : Ws) {
-                st = part == 0 ? check_forward_schedule_args(p, k, w)
-                               : check_schedule_args(p, k, w);
-                if (st == A2C_ERR_INVALID_ARG) {  // not a schedule of this kernel
-                    st = A2C_OK;
-                    continue;
-                }
-                st = part == 0 ? plan_apply_forward_schedule(p, k, w, s, !own_f)
-                               : plan_apply_adjoint_schedule(p, k, w, s, !own_b);
-                if (st == A2C_ERR_UNSUPPORTED) {  // too many chunks, or staging beyond LDS
-                    st = A2C_OK;
-                    continue;
-                }
-                if (st != A2C_OK) break;
-                (part == 0 ? own_f : own_b) = true;
-                float t = 0.f;
-                st = time_part(part, t);
-                if (st != A2C_OK) break;
-                // a later candidate (more residues per lane or waves) must be
-                // 1 % faster to win: exact ties keep the smaller schedule,
-                // while a margin as large as the timing noise would favour
-                // the smaller schedules (tried first) over better later ones
-                float &best = part == 0 ? best_f : best_b;
-                if (t < 0.99f * best) {
-                    best = t;
-                    (part == 0 ? fK : bK) = k;
-                    (part == 0 ? fW : bW) = w;
-                }
+        const std::vector<Shape> cands =
+            part == 0 ? tune_candidates(p->def_fwd, {p->fs.K, p->fs.W})
+                      : tune_candidates(p->def_adj, {p->bs.K, p->bs.W});
+        for (const Shape &c : cands) {
+            st = part == 0 ? check_forward_schedule_args(p, c.K, c.W)
+                           : check_schedule_args(p, c.K, c.W);
+            if (st == A2C_ERR_INVALID_ARG) {  // not a schedule of this kernel
+                st = A2C_OK;
+                continue;
+            }
+            st = part == 0 ? plan_apply_forward_schedule(p, c.K, c.W, s, !own_f)
+                           : plan_apply_adjoint_schedule(p, c.K, c.W, s, !own_b);
+            if (st == A2C_ERR_UNSUPPORTED) {  // too many chunks, or staging beyond LDS
+                st = A2C_OK;
+                continue;
             }
             if (st != A2C_OK) break;
+            (part == 0 ? own_f : own_b) = true;
+            float t = 0.f;
+            st = time_part(part, t);
+            if (st != A2C_OK) break;
+            // a later candidate must be 1 % faster to win: exact ties keep the
+            // default, then the smaller schedule, while a margin as large as
+            // the timing noise would favour the schedules tried first over
+            // better later ones
+            float &best = part == 0 ? best_f : best_b;
+            if (t < 0.99f * best) {
+                best = t;
+                (part == 0 ? fK : bK) = c.K;
+                (part == 0 ? fW : bW) = c.W;
+            }
         }
         if (st == A2C_OK && part == 0) {
             st = plan_apply_forward_schedule(p, fK, fW, s, !own_f);

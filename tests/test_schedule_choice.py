@@ -1,5 +1,8 @@
 """The schedules a plan starts with, and what becomes of them: set again, they
-are the same schedules."""
+are the same schedules, and the autotuner times them before any other."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -71,3 +74,22 @@ def test_reported_adjoint_schedule_set_again(batch, setter):
         getattr(plan, setter)(4, 3)   # away and back
         plan.backward(ang, g)
         getattr(plan, setter)(K, W)
+
+
+@pytest.mark.parametrize("default,present", [((1, 11), (1, 11)), ((2, 6), (1, 5)), ((4, 4), (8, 3)),
+                                             ((1, 1), (1, 1))])
+def test_autotuner_times_default_and_present_first(tmp_path, default, present):
+    """The candidate list, compiled for the host: the plan's default schedule,
+    its present one, then the grid; nothing twice."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src, exe = tmp_path / "list.cpp", tmp_path / "list"
+    src.write_text('#include <cstdio>\n#include "schedule.h"\nint main() { for (a2c::Shape s : '
+                   'a2c::tune_candidates({%d, %d}, {%d, %d})) std::printf("%%d %%d\\n", s.K, s.W); }\n'
+                   % (*default, *present))
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(root, "paper_1812_01108_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    cands = [tuple(int(v) for v in ln.split()) for ln in out.splitlines()]
+    assert cands[0] == default and present in cands[:2]
+    assert len(set(cands)) == len(cands)
+    assert {(k, w) for k in (1, 2, 4, 8) for w in (1, 2, 3, 4, 6, 8, 12, 16)} <= set(cands)
