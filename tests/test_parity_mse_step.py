@@ -183,3 +183,26 @@ def test_optional_outputs_and_empty_plan():
     l0, g0 = empty.mse_step(e, e)
     torch.cuda.synchronize()
     assert float(l0) == 0.0 and g0.numel() == 0
+
+
+@pytest.mark.parametrize("model,K,W", [
+    # the spine pass with 1, 2, 4 and 8 residues per lane (the most of them
+    # that divides a wave's share of the window), full last waves or not
+    ("backbone", 1, 3), ("backbone", 2, 1), ("backbone", 1, 4), ("backbone", 1, 12),
+    ("backbone", 2, 4), ("backbone", 4, 2),
+    ("fullatom", 1, 3), ("fullatom", 2, 1), ("fullatom", 1, 4), ("fullatom", 2, 4)])
+def test_chain_over_more_windows_than_one_waits_on(model, K, W):
+    """A chain over ten windows, so that a spine pass goes first, between
+    shorter ones; the full-atom recomputing adjoint (the unfused path) takes it
+    too.  Three calls: the tags move on."""
+    a2c = _a2c()
+    cap = 64 * K * W
+    lengths = [cap // 2 + 1, 9 * cap + 5, 7, cap + 3]
+    off, seq, ang, t = _case(model, lengths, 351 + K + W)
+    plan = (a2c.Plan("backbone", offsets=off) if model == "backbone"
+            else a2c.Plan("fullatom", offsets=off, seq=seq))
+    plan.set_schedule(K, W)
+    # the coordinates' bound as in test_windows_across_chains
+    tol = COORD_TOL_A * max(1.0, (max(lengths) / 1000.0) ** 1.5)
+    for _ in range(3):
+        _run(plan, model, off, seq, ang, t, f"{model} K={K} W={W}", coord_tol=tol)
