@@ -18,9 +18,11 @@ constexpr int kMaxChunks = 64;        // chunks of 64 W K residues per tile
 // gfx950, less the static tables)
 constexpr int kMaxDynamicLds = 136 * 1024;
 constexpr size_t kCuLds = 160 * 1024;  // LDS of a compute unit
-// Launch-bound classes of the scan kernels: up to 8 waves per workgroup
-// (512 lanes) a kernel may use up to 256 VGPRs without spilling; 16 waves
-// cap it at 128.  Launchers pick the class from the schedule's wave count.
+// Launch-bound classes of the scan kernels: a workgroup of up to 8 waves (512
+// lanes) leaves a kernel up to 256 VGPRs, one of 16 waves 128 (the backbone
+// forward and the adjoint that recomputes its frames on windows ask for four
+// waves per SIMD, 128 VGPRs, in either class).  Launchers pick the class from
+// the schedule's wave count.
 constexpr int kLbSmall = 512, kLbLarge = 1024;
 // Source of the upstream coordinate gradient in the recompute adjoints: read
 // from memory, or 2 (r - t) of the squared distance to a target (the fused
@@ -220,8 +222,8 @@ hipError_t launch_bb_forward_plain(const a2c_plan &p, const float *ang, float *x
                                    hipStream_t s);
 hipError_t launch_bb_backward_plain(const a2c_plan &p, const float *ang, const float *g,
                                     float *gang, const float *ws, hipStream_t s);
-// loss (may be NULL): receives sum |r - t|^2, from the schedule's per-tile
-// shares (bs.d_loss_part, bs.d_loss_count)
+// loss (may be NULL): receives sum |r - t|^2, from the windows' shares, which
+// travel in the adjoint's tagged words (lb_loss_commit)
 hipError_t launch_bb_mse_step(const a2c_plan &p, const float *ang, const float *tgt, float *xyz,
                               float *loss, float *gang, hipStream_t s);
 hipError_t launch_fa_mse_step(const a2c_plan &p, const float *ang, const float *tgt, float *xyz,

@@ -33,7 +33,8 @@ __device__ __forceinline__ SpineAngles<K> load_spine_angles(const float *__restr
 }
 
 // Lane-serial spine aggregate of K residues (reset at chain heads), with one
-// polar step; keeps the spine cos/sin per residue for the re-walk.
+// polar step.  first_head: the lane's first residue that starts a chain (K:
+// none).
 template <int K>
 __device__ __forceinline__ Aff fa_lane_aggregate(const SpineAngles<K> &a, int cnt, uint32_t hm,
                                                  const BBParams &P, ResidueIn (&in)[K],
@@ -79,18 +80,8 @@ __device__ __forceinline__ Aff fa_lane_aggregate(const SpineAngles<K> &a, int cn
     return m;
 }
 
-template <int K>
-__device__ __forceinline__ Aff fa_lane_aggregate(const float *__restrict__ ang, int64_t R,
-                                                 int64_t rs, int cnt, uint32_t hm,
-                                                 const BBParams &P, ResidueIn (&in)[K],
-                                                 int &first_head)
-{
-    return fa_lane_aggregate<K>(load_spine_angles<K>(ang, R, rs, cnt), cnt, hm, P, in,
-                                first_head);
-}
-
 // Spine aggregates for the recomputing adjoints whose windows cannot wait on
-// each other in both directions (a chain over more than kMaxAhead windows):
+// each other in both directions (a chain over more than kMaxAhead + 1 windows):
 // a spine-only pass over the same windows publishes each window's aggregate
 // (the product of its spine transforms from its last chain head, or its
 // start, to its end) as tagged words and waits on nothing; the adjoint, last
