@@ -222,10 +222,12 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  *     index mod 8 separately, and whole-chain ones in order; those that
  *     recompute the frames take them in order and also wait on the windows
  *     their last chain runs into, unless a chain spans more than 8 windows:
- *     then a spine-only pass over the same windows, which waits on nothing,
- *     goes first, and they take them last to first too); a launch therefore
- *     progresses whenever the device holds 8 of its workgroups at once.  Consequently two such calls on one
- *     plan must not run at the same time (on different streams).
+ *     then the windows' aggregates are published first, by a spine-only pass
+ *     or by as many workgroups more at the head of the launch, which wait on
+ *     nothing, and the windows are taken last to first too); a launch
+ *     therefore progresses whenever the device holds 8 of its workgroups at
+ *     once.  Consequently two such calls on one plan must not run at the same
+ *     time (on different streams).
  *   - The backbone adjoint that recomputes the frames (a2c_backward without
  *     d_coords) hands nothing between workgroups.  Where every chain fits in
  *     one chunk, it and the backbone fused step run on windows of whole

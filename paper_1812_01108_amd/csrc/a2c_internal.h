@@ -91,8 +91,9 @@ struct FADevTable {
 // on.  A launch whose windows wait ahead progresses only where the device (a
 // partition, a masked stream, what other work leaves of it) holds all of them
 // at once: 8 workgroups, as the adjoints that take their windows last to first
-// need too (reverse_window).  Batches with a chain over more windows take a
-// spine pass and then go last to first.
+// need too (reverse_window).  In batches with a chain over more windows the
+// spine aggregates are published first, by leads or a spine pass, and the
+// windows then go last to first.
 constexpr int kMaxAhead = 7;
 
 // One scan schedule: K residues per lane, W waves per workgroup, and the
@@ -124,7 +125,8 @@ struct Sched {
     // chain spans (from d_look_fwd[t] to t - 1)
     int32_t *d_look_fwd = nullptr;       // n_win, first window to compose
     uint64_t *d_status_fwd = nullptr;    // n_win x kLbWords tagged words
-    bool spined = false;                 // a chain spans more than kMaxAhead + 1 windows
+    bool spined = false;                 // a chain spans more than kMaxAhead + 1 windows,
+    bool leads = false;                  // and leads publish the aggregates (else a pass)
     int32_t fa_stage_atoms = 0;          // per-wave staging (floats per plane)
     bool fa_unstaged = false;            // stage too large for the LDS: direct I/O
     int32_t n_own = 0;                   // own windows
@@ -136,6 +138,8 @@ struct Sched {
     int32_t *d_rec_wstart = nullptr;     // n_rec + 1 boundaries
     int32_t *d_tile_res = nullptr;       // n_rec (first, end) residue pairs, longest first
     int32_t cap() const { return kWave * K * W; }  // residues of a fixed window
+    bool pass() const { return spined && !leads; }
+    int32_t linked_groups() const { return leads ? 2 * n_win : n_win; }
 };
 
 }  // namespace a2c

@@ -199,6 +199,18 @@ int64_t most_run_atoms(const a2c_plan &p, const std::vector<int64_t> &starts, in
     return (most + 3) / 4 * 4;
 }
 
+// Whether leads publish the spine aggregates of a launch of n windows that
+// needs them published first: where the device holds both halves of the launch
+// at once (four waves, four workgroups a CU); more windows take a spine pass,
+// which has eight residues per lane.  Built for one residue per lane.
+// Recomputing adjoint and fused step at (1, 4), us, with the pass and with
+// leads: full-atom, one chain of 6000 17.9 and 19.9, 13.9 and 15.9; 40 of
+// 1500..6000 (508 windows) 20.1 and 22.8, 16.5 and 19.1; 60 (790) 24.1 and
+// 26.8, 23.3 and 26.2; 150 (1911) 44.3 and 48.5, 45.1 and 50.4.  Backbone fused
+// step, one chain of 6000 15.1 and 10.8, 40 (508) 18.3 and 16.2, 60 (790) 21.4
+// and 20.7.
+bool lead_windows(const a2c_plan &p, int64_t n) { return n <= 2 * (int64_t)p.n_cu; }
+
 // Layouts of a schedule (see Sched).
 enum SchedRole { kRoleForward, kRoleAdjoint };
 
@@ -237,6 +249,7 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
         // loss shares travel in the adjoint's own tagged words)
         int32_t n2 = 0;
         st = build_windows(p, starts, true, S.d_look_fwd, S.d_status_fwd, n2, S.spined, s);
+        S.leads = S.spined && K == 1 && !S.fa_unstaged && lead_windows(*p, S.n_win);
     }
     if (st == A2C_OK && !fwd && p->model == A2C_BACKBONE && p->R > 0) {
         const std::vector<int64_t> own = whole_chain_starts(p, cap);
@@ -382,7 +395,7 @@ bool one_round(const a2c_plan &p, int32_t K, int32_t W, size_t fixed, int32_t si
 }
 
 // Whether some chain runs over more than kMaxAhead + 1 fixed windows of `cap`
-// residues, so that the recomputing adjoints take a spine pass first.
+// residues, so that the recomputing adjoints need the spine aggregates first.
 bool spans_far(const a2c_plan &p, int64_t cap)
 {
     if (p.max_len <= kMaxAhead * cap) return false;
@@ -393,22 +406,25 @@ bool spans_far(const a2c_plan &p, int64_t cap)
     return false;
 }
 
-// Waves of the recomputing adjoints where chains run over several windows:
-// four, or eight where that saves the spine pass, which costs more than eight
-// waves do.  Full-atom, one residue per lane, recomputing and fused step, us:
-// 512 chains of 50..2000 25.7 and 31.8 at W = 4 with the pass, 19.8 and 26.3 at
-// W = 8; 4096 of them 149 and 206, 146 and 199; where eight need the pass too
-// (20 of 3000..6000) 18.4 and 22.2 at W = 4, 20.3 and 24.7 at W = 8.  Backbone
-// fused step, 8 chains of 1500..4000 15.2 and 12.2 (from coordinates 5.2 and 5.4).
-int32_t linked_waves(const a2c_plan &p, int32_t K)
+// Waves of the recomputing adjoints where chains run over several windows, at
+// one residue per lane: four, or eight where that saves the spine pass, which
+// costs more than eight waves do (leads cost less).  Full-atom, recomputing and
+// fused step, us: 512 chains of 50..2000 25.7 and 31.8 at W = 4 with the pass,
+// 19.8 and 26.3 at W = 8; 4096 of them 149 and 206, 146 and 199; where eight
+// need the pass too (100 of 1500..6000) 37.0 and 41.1 at W = 4, 39.2 and 42.6
+// at W = 8; with leads (128 of 50..2000) 14.6 and 17.1 at W = 4, 14.9 and 17.4
+// at W = 8.
+int32_t linked_waves(const a2c_plan &p)
 {
-    const int64_t run = (int64_t)kWave * K;
-    return spans_far(p, 4 * run) && !spans_far(p, 8 * run) ? 8 : 4;
+    const int64_t four = 4 * kWave, eight = 8 * kWave;
+    if (!spans_far(p, four) || lead_windows(p, (p.R + four - 1) / four)) return 4;
+    return spans_far(p, eight) ? 4 : 8;
 }
 
 // A launch just over one round takes nearly two: `s` if it is one round, else
 // the fewest residues per lane (one, up to most_K) and waves that make it one
-// (adjoint: and that need no spine pass where `s` needs none), else `s`.
+// (adjoint: and whose windows wait no further ahead than kMaxAhead where those
+// of `s` do not), else `s`.
 // simd_waves[K - 1]: waves a SIMD's registers hold.  Forward: 2000
 // chains of 151, 1573 windows at W = 3 23.2, 500 of four chains at W = 10 15.9;
 // 580 chains of 50..2000, 24.3 at W = 4, 16.8 at W = 6.  Recomputing adjoint:
@@ -462,7 +478,7 @@ Shape default_adjoint(const a2c_plan &p, Shape &rec)
     if (p.model == A2C_FULLATOM) {
         // as the forward, but four waves for large batches too
         const int32_t whole = waves_for(p.max_len, 1);
-        rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : linked_waves(p, 1)};
+        rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : linked_waves(p)};
         if (whole <= 8 && rec.W > 4 && (int64_t)kWave * rec.W * p.n_cu < R) rec.W = 4;
         return rec = prefer_one_round(p, rec, 7024, 2, {4, 3}, true);
     }
@@ -478,7 +494,7 @@ Shape default_adjoint(const a2c_plan &p, Shape &rec)
     else if (whole <= most) s.W = pack_waves(p, s.K, whole, most);
     // long chains: 48 of 1500..6000, from coordinates 10.7 at (4, 16), 6.6 at
     // (2, 8), fused step 22.1 and 14.6; 8 of 1500..4000, 5.3 and 11.6 at (1, 4)
-    else if (R <= 65536) s.W = linked_waves(p, s.K);
+    else if (R <= 65536) s.W = linked_waves(p);
     else s = {2, 8};
     // the adjoint that recomputes the frames hands nothing over: a chunk that
     // holds the longest chain, up to 4096, and beyond that the one whose

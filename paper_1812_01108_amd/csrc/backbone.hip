@@ -604,7 +604,9 @@ __device__ __forceinline__ void bb_store_torques(float *buf, const float (&gr)[3
 //                   workgroups a chain spans at once; for longer chains
 //                   (spined) a spine pass has published the aggregates and
 //                   the windows go last to first.
-template <int K, int LB, int GM, bool LINK>
+//   LEADS = true:   instead of the pass, as many workgroups more, dispatched
+//                   first, publish the aggregates.
+template <int K, int LB, int GM, bool LINK, bool LEADS = false>
 __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     const float *__restrict__ ang, const float *__restrict__ g, float *__restrict__ gang,
     float *__restrict__ xyz_out, float *__restrict__ loss_out,
@@ -622,8 +624,8 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     constexpr int RUN = kWave * K;  // residues per wave
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t =
-        LINK && spined ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const WindowOf wo = window_taken<LINK, LEADS>(spined != 0);
+    const int64_t t = wo.t;
     int64_t ts, te;
     window_range<LINK>(wstart, cap, R, t, ts, te);
     const int nact = (int)((te - ts + RUN - 1) / RUN);
@@ -639,9 +641,10 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     int64_t first = t, last = t;
     if (wave == 0) {
         if constexpr (LINK) {
-            prev_f = lb_load(status_fwd + t * kLbWords);
+            prev_f = lb_load(LEADS && !wo.lead ? status + t * kLbWords + kLbLeadWord
+                                               : status_fwd + t * kLbWords);
             prev_b = lb_load(status + t * kLbWords);
-            first = look_first[t];
+            first = wo.lead ? t : look_first[t];
             last = look_last[t];
         }
         if (GM == kGradMse && loss_out) prev_l = lb_load(status + t * kLbWords + kLbLossWord);
@@ -658,20 +661,26 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
         run_load<K>(ang + rbase, nres, full, v0);
         run_load<K>(ang + R + rbase, nres, full, v1);
         run_load<K>(ang + 2 * R + rbase, nres, full, v2);
-        run_load<3 * K>(gb, 3 * nres, full, w0);
-        run_load<3 * K>(gb + A, 3 * nres, full, w1);
-        run_load<3 * K>(gb + 2 * A, 3 * nres, full, w2);
+        if (!wo.lead) {
+            run_load<3 * K>(gb, 3 * nres, full, w0);
+            run_load<3 * K>(gb + A, 3 * nres, full, w1);
+            run_load<3 * K>(gb + 2 * A, 3 * nres, full, w2);
+        }
         run_to_lanes<K>(buf, v0, phi);
         run_to_lanes<K>(buf, v1, psi);
         run_to_lanes<K>(buf, v2, om);
         m = bb_walk<K>(phi, psi, om, hm, P, x, y, z, first_head);
-        run_to_lanes<3 * K>(buf, w0, gx);
-        run_to_lanes<3 * K>(buf, w1, gy);
-        run_to_lanes<3 * K>(buf, w2, gz);
+        if (!wo.lead) {
+            run_to_lanes<3 * K>(buf, w0, gx);
+            run_to_lanes<3 * K>(buf, w1, gy);
+            run_to_lanes<3 * K>(buf, w2, gz);
+        }
     }
     const uint64_t heads = __builtin_amdgcn_ballot_w64(first_head < K);
+    if (LEADS && !wo.lead) prev_f = lead_tag(status, t, prev_f);
     const Aff X = block_prefix_windows<LINK>(m, heads, nact, active, shf, fcarry_sh, status_fwd, t,
-                                             first, prev_f, spined != 0);
+                                             first, prev_f, LEADS ? !wo.lead : spined != 0);
+    if (LEADS && wo.lead) return;
     float px = 0.f, py = 0.f, pz = 0.f;  // the atom before the lane's first
     float loss = 0.f;
     Wrench agg = wrench_zero();
@@ -719,7 +728,7 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
         bb_store_torques<K>(buf, gr, gang, R, rbase, nres, full, nt != 0);
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) lb_loss_commit(loss, status, t, gridDim.x, prev_l, loss_out, loss_tot);
+        if (loss_out) lb_loss_commit(loss, status, t, wo.n, prev_l, loss_out, loss_tot);
     }
 }
 
@@ -990,8 +999,11 @@ hipError_t mse_kl(const a2c_plan &p, const float *ang, const float *tgt, float *
                            nullptr, nullptr, nullptr, S.d_own_status, p.R, p.bb, 0,
                            p.nt_grad ? 1 : 0);
     else {
-        if (S.spined) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
-        hipLaunchKernelGGL((bb_backward_frames_flat_kernel<K, LB, kGradMse, true>), dim3(S.n_win),
+        if (S.pass()) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
+        auto kernel = bb_backward_frames_flat_kernel<K, LB, kGradMse, true>;
+        if constexpr (K == 1)
+            if (S.leads) kernel = bb_backward_frames_flat_kernel<K, LB, kGradMse, true, true>;
+        hipLaunchKernelGGL(kernel, dim3(S.linked_groups()),
                            block, lds, s, ang, tgt, gang, xyz, loss, p.d_head_bits, S.d_wstart, S.cap(),
                            S.d_look_fwd, S.d_status_fwd, S.d_look, S.d_status, p.R, p.bb,
                            S.spined ? 1 : 0, p.nt_grad ? 1 : 0);

@@ -937,7 +937,8 @@ struct AtomForce {
 // windows go in order and a launch progresses as long as the device holds the
 // at most kMaxAhead + 1 workgroups a chain spans at once.  For longer chains
 // (spined) a spine pass has published the aggregates and the windows go last
-// to first.  Otherwise positions and axes from the forward's coordinates, last
+// to first (LEADS: as many workgroups more, dispatched first, publish them
+// instead of the pass).  Otherwise positions and axes from the forward's coordinates, last
 // window first (rev; in order where the windows hold whole chains).
 // GM = kGradMse (with RECOMPUTE): g points at a target t and the upstream
 // gradient is 2 (r - t), formed from the recomputed positions (the fused
@@ -954,7 +955,7 @@ struct AtomForce {
 // STG: atoms go through the per-wave LDS stage; otherwise global memory is
 // addressed directly (schedules whose stage does not fit the LDS).
 // LINK: as in the forward.
-template <int K, bool RECOMPUTE, int LB, int GM, bool LINK, bool STG>
+template <int K, bool RECOMPUTE, int LB, int GM, bool LINK, bool STG, bool LEADS = false>
 __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     const float *__restrict__ ang, const float *__restrict__ xyz, const float *__restrict__ g,
     float *__restrict__ gang, float *__restrict__ xyz_out, float *__restrict__ loss_out,
@@ -976,7 +977,8 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     __shared__ float loss_tot[GM == kGradMse ? kMaxWaves : 1];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t = LINK && rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const WindowOf wo = window_taken<LINK, LEADS>(rev != 0);
+    const int64_t t = wo.t;
     ChunkRange k;
     window_range<LINK>(wstart, cap, R, t, k.cs, k.ce);
     k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
@@ -988,8 +990,9 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
             prev = lb_load(status + t * kLbWords);
             last = look_last[t];
             if (RECOMPUTE) {
-                prev_f = lb_load(status_fwd + t * kLbWords);
-                first = look_fwd[t];
+                prev_f = lb_load(LEADS && !wo.lead ? status + t * kLbWords + kLbLeadWord
+                                                   : status_fwd + t * kLbWords);
+                first = wo.lead ? t : look_fwd[t];
             }
         }
         if (GM == kGradMse && loss_out) prev_l = lb_load(status + t * kLbWords + kLbLossWord);
@@ -1002,7 +1005,7 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     float *st = stage_mem + (size_t)wave * planes * stage_atoms;
     float *stx = st + 3 * stage_atoms;  // coordinates (coordinate mode)
     RunStart gr;
-    if (STG && L.active) gr = run_start(g, A, L.A0, L.natoms);
+    if (STG && L.active && !wo.lead) gr = run_start(g, A, L.A0, L.natoms);
     table_store(tab, tc);
     Aff cur = aff_identity();
     ResidueIn in[K];
@@ -1013,8 +1016,11 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
             unit = spine_unit<K>(in, L, P);
         }
         const int n_units = (int)((k.ce - k.cs + K - 1) / K);
+        if (LEADS && !wo.lead) prev_f = lead_tag(status, t, prev_f);
         cur = entering_frame<LINK>(unit, L.hm != 0u, n_units, stage_mem, unit_flags, shf,
-                                   fcarry_sh, status_fwd, t, first, prev_f, spined != 0);
+                                   fcarry_sh, status_fwd, t, first, prev_f,
+                                   LEADS ? !wo.lead : spined != 0);
+        if (LEADS && wo.lead) return;
     }
     __syncthreads();  // the stage takes the frames' place; the table is complete
     if (STG && L.active) {
@@ -1180,7 +1186,7 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
         }
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) lb_loss_commit(force.loss, status, t, gridDim.x, prev_l, loss_out, loss_tot);
+        if (loss_out) lb_loss_commit(force.loss, status, t, wo.n, prev_l, loss_out, loss_tot);
     }
 }
 
@@ -1218,17 +1224,20 @@ void fa_bwd_launch(const a2c_plan &p, const float *ang, const float *xyz, const 
                    float *gang, hipStream_t s, float *xyz_out, float *loss_out)
 {
     const Sched &S = p.bs;
-    const bool spined = RECOMPUTE && S.spined;
-    if (spined) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
+    const bool pass = RECOMPUTE && S.pass();
+    if (pass) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
     size_t lds = STG ? (size_t)S.W * (RECOMPUTE ? 3 : 6) * S.fa_stage_atoms * sizeof(float) : 0;
     if (RECOMPUTE) lds = std::max(lds, frame_bytes(S.W));
-    const bool rev = RECOMPUTE ? spined : !S.whole_chains;
-    hipLaunchKernelGGL((S.whole_chains ? fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, false, STG>
-                                       : fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, true, STG>),
-                       dim3(S.n_win), dim3(S.W * kWave), lds, s, ang, xyz, g, gang, xyz_out, loss_out,
+    const bool rev = RECOMPUTE ? pass : !S.whole_chains;
+    auto kernel = S.whole_chains ? fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, false, STG>
+                                 : fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, true, STG>;
+    if constexpr (RECOMPUTE && K == 1 && STG)
+        if (S.leads) kernel = fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, true, STG, true>;
+    hipLaunchKernelGGL(kernel, dim3(RECOMPUTE ? S.linked_groups() : S.n_win), dim3(S.W * kWave), lds,
+                       s, ang, xyz, g, gang, xyz_out, loss_out,
                        p.d_head_bits, S.d_wstart, S.cap(), p.d_res_atom_off, p.d_seq, p.d_fa,
                        S.d_status_fwd, S.d_look_fwd, S.d_look, S.d_status, p.R, p.A, p.bb,
-                       S.fa_stage_atoms, rev ? 1 : 0, spined ? 1 : 0, p.nt_grad ? 1 : 0);
+                       S.fa_stage_atoms, rev ? 1 : 0, pass ? 1 : 0, p.nt_grad ? 1 : 0);
 }
 
 // mode 0: adjoint from coordinates, 1: recompute, 2: fused squared-distance step
@@ -1328,6 +1337,10 @@ static void allow_lds_kll()
     allow_lds(fa_backward_flat_kernel<K, false, LB, kGradLoad, LINK, true>);
     allow_lds(fa_backward_flat_kernel<K, true, LB, kGradLoad, LINK, true>);
     allow_lds(fa_backward_flat_kernel<K, true, LB, kGradMse, LINK, true>);
+    if constexpr (K == 1 && LINK) {
+        allow_lds(fa_backward_flat_kernel<K, true, LB, kGradLoad, LINK, true, true>);
+        allow_lds(fa_backward_flat_kernel<K, true, LB, kGradMse, LINK, true, true>);
+    }
 }
 
 template <int K, int LB>

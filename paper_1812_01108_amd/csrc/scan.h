@@ -754,6 +754,29 @@ __device__ __forceinline__ int64_t reverse_window(int64_t b, int64_t n)
     return ((c - 1 - (b >> 3)) << 3) + x;
 }
 
+// The window a workgroup takes, of the launch's n, and whether it is a lead:
+// in a launch with leads, the first n workgroups only publish their windows'
+// spine aggregates and wait on nothing; n more then take the windows last to
+// first.
+struct WindowOf {
+    int64_t t, n;
+    bool lead;
+};
+
+template <bool LINK, bool LEADS>
+__device__ __forceinline__ WindowOf window_taken(bool rev)
+{
+    WindowOf w{blockIdx.x, gridDim.x, false};
+    if constexpr (LEADS) {
+        w.n >>= 1;
+        w.lead = w.t < w.n;
+        if (!w.lead) w.t = reverse_window(w.t - w.n, w.n);
+    } else if (LINK && rev) {
+        w.t = reverse_window(w.t, w.n);
+    }
+    return w;
+}
+
 // ------------------------------------------------------ window look-back
 // Windows (tiles) of a packed batch hand the scan state across window
 // edges through device memory.  Every tile publishes its aggregate (the
@@ -765,9 +788,10 @@ __device__ __forceinline__ int64_t reverse_window(int64_t b, int64_t n)
 // reads, so no wait depends on another wait; a tile only waits on tiles of
 // lower index, which start no later than it does.  The adjoints, which wait on
 // later windows, take them in reverse (reverse_window) where they wait on
-// nothing else, and otherwise in order, looking at most kMaxAhead ahead.  Words are written and
-// read with relaxed device-scope atomics (each word carries its own tag, so
-// no ordering between words is needed).  The tag of a launch is one more than
+// nothing else or on workgroups that started before theirs (a spine pass or
+// leads), and otherwise in order, looking at most kMaxAhead ahead.  Words are
+// written and read with relaxed device-scope atomics (each word carries its
+// own tag, so no ordering between words is needed).  The tag of a launch is one more than
 // the one a tile finds in its own words (all tiles start from 0 and every
 // launch runs every tile once, so they agree).  A wait gives up after
 // kLbSpinLimit polls and takes NaN for the missing aggregate, so every wave
@@ -848,7 +872,8 @@ __device__ __forceinline__ Aff lb_carry_in(const uint64_t *status, int64_t first
 // Every thread of the block calls it; inactive waves get the identity.
 // LINK = false (windows of whole chains): no window needs another's frame, so
 // nothing is published or read (status, first, prev and carry_sh unused).
-// published: an earlier launch has published the aggregates (the spine pass).
+// published: another workgroup publishes the aggregate, with the tag in prev
+// (the spine pass, or a lead of this launch).
 template <bool LINK = true, typename Shared>
 __device__ __forceinline__ Aff block_prefix_windows(Aff m, uint64_t heads, int nact, bool active,
                                                     Shared &sh, float (&carry_sh)[12],
@@ -1045,6 +1070,22 @@ __device__ __forceinline__ Wrench block_suffix_windows(Wrench agg, uint64_t ends
 // workgroup, started after all others, waits for all shares and adds them in
 // window order into *out.  Every thread of the block calls it (one barrier).
 constexpr int kLbLossWord = kLbWrenchWords;
+
+// In a launch with leads, a window's own workgroup cannot tell the launch's tag
+// from the aggregate's words, which the window's lead writes meanwhile; it
+// keeps the last tag in this word of its own.  Returns prev with the tag of
+// this launch (thread 0 read prev from the word).
+constexpr int kLbLeadWord = kLbLossWord + 1;
+static_assert(kLbLeadWord < kLbWords, "words of a window");
+
+__device__ __forceinline__ uint64_t lead_tag(uint64_t *__restrict__ status, int64_t t,
+                                             uint64_t prev)
+{
+    prev += 1ull << 32;
+    if (threadIdx.x == 0)
+        lb_store(status + t * kLbWords + kLbLeadWord, (uint32_t)(prev >> 32), 0.f);
+    return prev;
+}
 
 __device__ __forceinline__ void lb_loss_commit(float v, uint64_t *__restrict__ status, int64_t t,
                                                int64_t n_win, uint64_t prev,

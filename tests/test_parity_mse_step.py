@@ -185,19 +185,23 @@ def test_optional_outputs_and_empty_plan():
     assert float(l0) == 0.0 and g0.numel() == 0
 
 
-@pytest.mark.parametrize("model,K,W", [
+@pytest.mark.parametrize("model,K,W,groups", [
     # the spine pass with 1, 2, 4 and 8 residues per lane (the most of them
-    # that divides a wave's share of the window), full last waves or not
-    ("backbone", 1, 3), ("backbone", 2, 1), ("backbone", 1, 4), ("backbone", 1, 12),
-    ("backbone", 2, 4), ("backbone", 4, 2),
-    ("fullatom", 1, 3), ("fullatom", 2, 1), ("fullatom", 1, 4), ("fullatom", 2, 4)])
-def test_chain_over_more_windows_than_one_waits_on(model, K, W):
-    """A chain over ten windows, so that a spine pass goes first, between
-    shorter ones; the full-atom recomputing adjoint (the unfused path) takes it
-    too.  Three calls: the tags move on."""
+    # that divides a wave's share of the window): more windows than a launch
+    # with leads takes, or two residues per lane or more
+    ("backbone", 1, 1, 50), ("backbone", 2, 1, 1), ("backbone", 2, 2, 1), ("backbone", 4, 2, 1),
+    ("fullatom", 1, 1, 50), ("fullatom", 2, 1, 1), ("fullatom", 2, 2, 1), ("fullatom", 2, 4, 1),
+    # leads, in every class of workgroup sizes, window counts around multiples
+    # of the eight that the order of windows goes by
+    ("backbone", 1, 1, 1), ("backbone", 1, 3, 2), ("backbone", 1, 8, 1), ("backbone", 1, 12, 1),
+    ("fullatom", 1, 1, 1), ("fullatom", 1, 4, 2), ("fullatom", 1, 6, 1), ("fullatom", 1, 12, 1)])
+def test_chain_over_more_windows_than_one_waits_on(model, K, W, groups):
+    """Chains over ten windows, so that a spine pass goes first or leads do,
+    between shorter ones; the full-atom recomputing adjoint (the unfused path)
+    takes the same form.  Three calls: the tags move on."""
     a2c = _a2c()
     cap = 64 * K * W
-    lengths = [cap // 2 + 1, 9 * cap + 5, 7, cap + 3]
+    lengths = [cap // 2 + 1, 9 * cap + 5, 7, cap + 3] * groups
     off, seq, ang, t = _case(model, lengths, 351 + K + W)
     plan = (a2c.Plan("backbone", offsets=off) if model == "backbone"
             else a2c.Plan("fullatom", offsets=off, seq=seq))

@@ -1,8 +1,9 @@
 """What a launch of a recomputing adjoint waits on: windows in order wait ahead
-on at most the 7 after their own, and a batch with a chain over more than 8
-windows takes a spine pass and then the windows last to first.  Either way the
-launch progresses where the device holds 8 of its workgroups at once.  The form
-taken is read off the number of kernels a captured call holds."""
+on at most the 7 after their own; in a batch with a chain over more than 8
+windows the spine aggregates are published first, by as many workgroups of the
+same launch (leads) or by a spine pass, and the windows go last to first.  Either
+way the launch progresses where the device holds 8 of its workgroups at once.
+The form taken is read off the kernels that a captured call holds."""
 import ctypes
 
 import numpy as np
@@ -25,8 +26,16 @@ def _plan(model, lengths):
     return plan, ang
 
 
+class _KernelNode(ctypes.Structure):
+    """hipKernelNodeParams."""
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p),
+                ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
 def _kernels(run):
-    """Kernels a call enqueues (nodes of a graph captured over it)."""
+    """Workgroups of each kernel that a call enqueues, sorted (nodes of a graph
+    captured over it)."""
     import torch
     from paper_1812_01108_amd import _lib
     run()
@@ -34,11 +43,20 @@ def _kernels(run):
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         run()
+    lib = _lib.load()
+    nodes_of, node_params = lib.hipGraphGetNodes, lib.hipGraphKernelNodeGetParams
+    nodes_of.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    node_params.argtypes = [ctypes.c_void_p, ctypes.POINTER(_KernelNode)]
     n = ctypes.c_size_t()
-    count = _lib.load().hipGraphGetNodes
-    count.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
-    assert count(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
-    return n.value
+    assert nodes_of(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert nodes_of(graph.raw_cuda_graph(), nodes, ctypes.byref(n)) == 0
+    grids = []
+    for node in nodes:
+        p = _KernelNode()
+        assert node_params(node, ctypes.byref(p)) == 0
+        grids.append(p.grid[0])
+    return sorted(grids)
 
 
 def _calls(plan, ang):
@@ -54,21 +72,29 @@ def _calls(plan, ang):
 
 
 @pytest.mark.parametrize("model", ["backbone", "fullatom"])
-@pytest.mark.parametrize("K,W", [(1, 1), (2, 2)])
-@pytest.mark.parametrize("windows", [8, 9, 32])
+@pytest.mark.parametrize("K,W", [(1, 1), (1, 4), (2, 2)])
+@pytest.mark.parametrize("windows", [8, 9, 32, 514])
 def test_windows_wait_on_at_most_seven_ahead(model, K, W, windows):
     cap = 64 * K * W
-    # from residue 5 of window 0 into residue 0 of the last of `windows`
-    plan, ang = _plan(model, [5, (windows - 1) * cap - 4, 3])
+    # from residue 5 of window 0 into residue 0 of the last of at most 33 windows
+    chains = [5, (min(windows, 33) - 1) * cap - 4, 3]
+    plan, ang = _plan(model, chains + [cap] * (windows - min(windows, 33)))
     plan.set_schedule(K, W)
+    want = ([windows] if windows <= 8                          # in order
+            else [2 * windows] if K == 1 and windows <= 512    # leads
+            else [windows, windows])                           # a spine pass
     for name, call in _calls(plan, ang).items():
-        assert _kernels(call) == (1 if windows <= 8 else 2), name
+        assert _kernels(call) == want, name
 
 
-@pytest.mark.parametrize("model,lengths", [
-    ("fullatom", [2000, 300] * 30), ("fullatom", [1793, 3500, 60]), ("backbone", [3500, 1800, 40])])
-def test_default_schedules_need_no_spine_pass(model, lengths):
-    """Chains over more than 8 windows of four waves, not of eight."""
+@pytest.mark.parametrize("model,lengths,waves", [
+    # windows of four waves: a chain over more than 8, on few of them and many
+    ("fullatom", [2000, 300] * 30, 4), ("fullatom", [2000, 300] * 80, 8),
+    ("fullatom", [1793, 3500, 60], 4), ("backbone", [3500, 1800, 40], 4),
+    # every chain within 8
+    ("fullatom", [1700, 300] * 80, 4)])
+def test_default_schedules_need_no_spine_pass(model, lengths, waves):
     plan, ang = _plan(model, lengths)
+    assert plan.adjoint_schedule["waves_per_group"] == waves
     for name, call in _calls(plan, ang).items():
-        assert _kernels(call) == 1, (name, plan.adjoint_schedule)
+        assert len(_kernels(call)) == 1, name
