@@ -624,8 +624,9 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     constexpr int RUN = kWave * K;  // residues per wave
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const WindowOf wo = window_taken<LINK, LEADS>(spined != 0);
-    const int64_t t = wo.t;
+    const bool lead = LEADS && is_lead();
+    const int64_t t = LEADS ? window_with_leads()
+                      : LINK && spined ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
     int64_t ts, te;
     window_range<LINK>(wstart, cap, R, t, ts, te);
     const int nact = (int)((te - ts + RUN - 1) / RUN);
@@ -641,10 +642,10 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
     int64_t first = t, last = t;
     if (wave == 0) {
         if constexpr (LINK) {
-            prev_f = lb_load(LEADS && !wo.lead ? status + t * kLbWords + kLbLeadWord
+            prev_f = lb_load(LEADS && !lead ? status + t * kLbWords + kLbLeadWord
                                                : status_fwd + t * kLbWords);
             prev_b = lb_load(status + t * kLbWords);
-            first = wo.lead ? t : look_first[t];
+            first = lead ? t : look_first[t];
             last = look_last[t];
         }
         if (GM == kGradMse && loss_out) prev_l = lb_load(status + t * kLbWords + kLbLossWord);
@@ -661,7 +662,7 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
         run_load<K>(ang + rbase, nres, full, v0);
         run_load<K>(ang + R + rbase, nres, full, v1);
         run_load<K>(ang + 2 * R + rbase, nres, full, v2);
-        if (!wo.lead) {
+        if (!lead) {
             run_load<3 * K>(gb, 3 * nres, full, w0);
             run_load<3 * K>(gb + A, 3 * nres, full, w1);
             run_load<3 * K>(gb + 2 * A, 3 * nres, full, w2);
@@ -670,17 +671,17 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
         run_to_lanes<K>(buf, v1, psi);
         run_to_lanes<K>(buf, v2, om);
         m = bb_walk<K>(phi, psi, om, hm, P, x, y, z, first_head);
-        if (!wo.lead) {
+        if (!lead) {
             run_to_lanes<3 * K>(buf, w0, gx);
             run_to_lanes<3 * K>(buf, w1, gy);
             run_to_lanes<3 * K>(buf, w2, gz);
         }
     }
     const uint64_t heads = __builtin_amdgcn_ballot_w64(first_head < K);
-    if (LEADS && !wo.lead) prev_f = lead_tag(status, t, prev_f);
+    if (LEADS && !lead) prev_f = lead_tag(status, t, prev_f);
     const Aff X = block_prefix_windows<LINK>(m, heads, nact, active, shf, fcarry_sh, status_fwd, t,
-                                             first, prev_f, LEADS ? !wo.lead : spined != 0);
-    if (LEADS && wo.lead) return;
+                                             first, prev_f, LEADS ? !lead : spined != 0);
+    if (LEADS && lead) return;
     float px = 0.f, py = 0.f, pz = 0.f;  // the atom before the lane's first
     float loss = 0.f;
     Wrench agg = wrench_zero();
@@ -728,7 +729,9 @@ __global__ __launch_bounds__(LB, 4) void bb_backward_frames_flat_kernel(
         bb_store_torques<K>(buf, gr, gang, R, rbase, nres, full, nt != 0);
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) lb_loss_commit(loss, status, t, wo.n, prev_l, loss_out, loss_tot);
+        if (loss_out)
+            lb_loss_commit(loss, status, t, LEADS ? gridDim.x >> 1 : gridDim.x, prev_l,
+                           loss_out, loss_tot);
     }
 }
 

@@ -977,8 +977,9 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     __shared__ float loss_tot[GM == kGradMse ? kMaxWaves : 1];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const WindowOf wo = window_taken<LINK, LEADS>(rev != 0);
-    const int64_t t = wo.t;
+    const bool lead = LEADS && is_lead();
+    const int64_t t = LEADS ? window_with_leads()
+                      : LINK && rev ? reverse_window(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
     ChunkRange k;
     window_range<LINK>(wstart, cap, R, t, k.cs, k.ce);
     k.nact = (int)((k.ce - k.cs + kWave * K - 1) / (kWave * K));
@@ -990,9 +991,9 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
             prev = lb_load(status + t * kLbWords);
             last = look_last[t];
             if (RECOMPUTE) {
-                prev_f = lb_load(LEADS && !wo.lead ? status + t * kLbWords + kLbLeadWord
+                prev_f = lb_load(LEADS && !lead ? status + t * kLbWords + kLbLeadWord
                                                    : status_fwd + t * kLbWords);
-                first = wo.lead ? t : look_fwd[t];
+                first = lead ? t : look_fwd[t];
             }
         }
         if (GM == kGradMse && loss_out) prev_l = lb_load(status + t * kLbWords + kLbLossWord);
@@ -1005,7 +1006,7 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     float *st = stage_mem + (size_t)wave * planes * stage_atoms;
     float *stx = st + 3 * stage_atoms;  // coordinates (coordinate mode)
     RunStart gr;
-    if (STG && L.active && !wo.lead) gr = run_start(g, A, L.A0, L.natoms);
+    if (STG && L.active && !lead) gr = run_start(g, A, L.A0, L.natoms);
     table_store(tab, tc);
     Aff cur = aff_identity();
     ResidueIn in[K];
@@ -1016,11 +1017,11 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
             unit = spine_unit<K>(in, L, P);
         }
         const int n_units = (int)((k.ce - k.cs + K - 1) / K);
-        if (LEADS && !wo.lead) prev_f = lead_tag(status, t, prev_f);
+        if (LEADS && !lead) prev_f = lead_tag(status, t, prev_f);
         cur = entering_frame<LINK>(unit, L.hm != 0u, n_units, stage_mem, unit_flags, shf,
                                    fcarry_sh, status_fwd, t, first, prev_f,
-                                   LEADS ? !wo.lead : spined != 0);
-        if (LEADS && wo.lead) return;
+                                   LEADS ? !lead : spined != 0);
+        if (LEADS && lead) return;
     }
     __syncthreads();  // the stage takes the frames' place; the table is complete
     if (STG && L.active) {
@@ -1186,7 +1187,9 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
         }
     }
     if constexpr (GM == kGradMse) {
-        if (loss_out) lb_loss_commit(force.loss, status, t, wo.n, prev_l, loss_out, loss_tot);
+        if (loss_out)
+            lb_loss_commit(force.loss, status, t, LEADS ? gridDim.x >> 1 : gridDim.x, prev_l,
+                           loss_out, loss_tot);
     }
 }
 

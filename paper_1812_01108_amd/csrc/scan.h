@@ -754,27 +754,14 @@ __device__ __forceinline__ int64_t reverse_window(int64_t b, int64_t n)
     return ((c - 1 - (b >> 3)) << 3) + x;
 }
 
-// The window a workgroup takes, of the launch's n, and whether it is a lead:
-// in a launch with leads, the first n workgroups only publish their windows'
-// spine aggregates and wait on nothing; n more then take the windows last to
-// first.
-struct WindowOf {
-    int64_t t, n;
-    bool lead;
-};
-
-template <bool LINK, bool LEADS>
-__device__ __forceinline__ WindowOf window_taken(bool rev)
+// A launch with leads over n windows: workgroups 0 .. n - 1 only publish their
+// windows' spine aggregates and wait on nothing; n more then take the windows
+// last to first.
+__device__ __forceinline__ bool is_lead() { return blockIdx.x < gridDim.x >> 1; }
+__device__ __forceinline__ int64_t window_with_leads()
 {
-    WindowOf w{blockIdx.x, gridDim.x, false};
-    if constexpr (LEADS) {
-        w.n >>= 1;
-        w.lead = w.t < w.n;
-        if (!w.lead) w.t = reverse_window(w.t - w.n, w.n);
-    } else if (LINK && rev) {
-        w.t = reverse_window(w.t, w.n);
-    }
-    return w;
+    const int64_t n = gridDim.x >> 1, b = blockIdx.x;
+    return b < n ? b : reverse_window(b - n, n);
 }
 
 // ------------------------------------------------------ window look-back
