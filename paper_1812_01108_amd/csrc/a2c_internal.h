@@ -17,7 +17,6 @@ constexpr int kMaxChunks = 64;        // chunks of 64 W K residues per tile
 // dynamic LDS allowed to the full-atom kernels (160 KB per workgroup on
 // gfx950, less the static tables)
 constexpr int kMaxDynamicLds = 136 * 1024;
-constexpr size_t kCuLds = 160 * 1024;  // LDS of a compute unit
 // Launch-bound classes of the scan kernels: a workgroup of up to 8 waves (512
 // lanes) leaves a kernel up to 256 VGPRs, one of 16 waves 128 (the backbone
 // forward and the adjoint that recomputes its frames on windows ask for four
@@ -129,6 +128,7 @@ struct Sched {
     bool leads = false;                  // and leads publish the aggregates (else a pass)
     int32_t fa_stage_atoms = 0;          // per-wave staging (floats per plane)
     bool fa_unstaged = false;            // stage too large for the LDS: direct I/O
+    bool fa_from_coords = false;         // the adjoint given coordinates reads them
     int32_t n_own = 0;                   // own windows
     int32_t *d_own_wstart = nullptr;     // n_own + 1 boundaries
     uint64_t *d_own_status = nullptr;    // n_own x kLbWords tagged words (loss shares)
@@ -235,6 +235,14 @@ hipError_t launch_fa_mse_step(const a2c_plan &p, const float *ang, const float *
 hipError_t launch_fa_forward_scan(const a2c_plan &p, const float *ang, float *xyz, hipStream_t s);
 hipError_t launch_fa_backward_scan(const a2c_plan &p, const float *ang, const float *xyz,
                                    const float *g, float *gang, hipStream_t s);
+// Workgroups of a staged full-atom launch that a compute unit holds at once, by
+// its LDS and by its registers (both 0 where the stage does not fit), for the
+// kernel that the launch takes; stage_atoms as in Sched.
+enum class FaForm { forward, coords, recompute, mse };
+struct FaHeld {
+    int32_t by_lds, by_registers;
+};
+FaHeld fa_held(FaForm form, int32_t K, int32_t W, bool whole_chains, int64_t stage_atoms);
 void build_lrmsd_segments(a2c_plan &p);
 void build_chi_points(const FATable &T, uint8_t (&out)[A2C_NUM_RESIDUE_TYPES][8]);
 int32_t inverse_stage_atoms(const a2c_plan &p);

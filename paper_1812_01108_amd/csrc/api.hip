@@ -236,6 +236,16 @@ a2c_status build_sched(const a2c_plan *p, int32_t K, int32_t W, Sched &out, hipS
             S.fa_unstaged = true;  // atoms straight to global memory
         else
             S.fa_stage_atoms = (int32_t)most;
+        // the form from coordinates stages six planes; where they do not fit,
+        // the recomputing form (three planes) computes the same gradient, and
+        // where their LDS leaves the launch more than one round it is the
+        // faster one: (1, 4), us from coordinates and recomputing: 64 x 300 9.1
+        // and 13.2, 1000 chains of 100 10.5 and 13.8, 512 of 50..2000 24.4 and
+        // 20.0, 4096 of them 206 and 141
+        S.fa_from_coords =
+            S.fa_unstaged ||
+            (int64_t)starts.size() - 1 <=
+                (int64_t)fa_held(FaForm::coords, K, W, S.whole_chains, most).by_lds * p->n_cu;
     }
     const bool fwd = role == kRoleForward;
     bool ignored = false;
@@ -374,24 +384,21 @@ int32_t pack_waves(const a2c_plan &p, int32_t K, int32_t least, int32_t most)
 }
 
 // Whether a full-atom launch of schedule (K, W) is one round of workgroups: the
-// LDS (the waves' stages, and the tables and scan state, `fixed` bytes) and the
-// registers (simd_waves per SIMD, a workgroup's waves dealt out over the four)
-// let the device hold all of them at once.
-bool one_round(const a2c_plan &p, int32_t K, int32_t W, size_t fixed, int32_t simd_waves)
+// LDS and the registers let the device hold all of them at once.
+bool one_round(const a2c_plan &p, int32_t K, int32_t W, FaForm form)
 {
-    constexpr size_t kGranule = 1280;  // LDS is handed out in pieces of this
     const int64_t run = (int64_t)kWave * K;
-    const auto holds = [&](int64_t n_win, int64_t run_atoms) {
-        const size_t stage = (size_t)W * 3 * run_atoms * sizeof(float);
-        if (stage > (size_t)kMaxDynamicLds) return false;
-        const size_t group = (stage + fixed + kGranule - 1) / kGranule * kGranule;
-        return n_win <= std::min<int64_t>(kCuLds / group, simd_waves / ((W + 3) / 4)) * p.n_cu;
+    const auto holds = [&](int64_t n_win, bool whole, int64_t run_atoms) {
+        const FaHeld h = fa_held(form, K, W, whole, run_atoms);
+        return n_win <= (int64_t)std::min(h.by_lds, h.by_registers) * p.n_cu;
     };
     // the least there can be, before the windows are laid out
-    if (!holds((p.R + run * W - 1) / (run * W), run * p.A / std::max<int64_t>(1, p.R))) return false;
+    const int64_t least = (p.R + run * W - 1) / (run * W);
+    const int64_t mean_atoms = run * p.A / std::max<int64_t>(1, p.R);
+    if (!holds(least, true, mean_atoms) && !holds(least, false, mean_atoms)) return false;
     bool whole;
     const std::vector<int64_t> st = window_starts(&p, run * W, whole);
-    return holds((int64_t)st.size() - 1, most_run_atoms(p, st, run));
+    return holds((int64_t)st.size() - 1, whole, most_run_atoms(p, st, run));
 }
 
 // Whether some chain runs over more than kMaxAhead + 1 fixed windows of `cap`
@@ -425,20 +432,19 @@ int32_t linked_waves(const a2c_plan &p)
 // the fewest residues per lane (one, up to most_K) and waves that make it one
 // (adjoint: and whose windows wait no further ahead than kMaxAhead where those
 // of `s` do not), else `s`.
-// simd_waves[K - 1]: waves a SIMD's registers hold.  Forward: 2000
+// Forward: 2000
 // chains of 151, 1573 windows at W = 3 23.2, 500 of four chains at W = 10 15.9;
 // 580 chains of 50..2000, 24.3 at W = 4, 16.8 at W = 6.  Recomputing adjoint:
 // 550 of them, 30.8 at (1, 4), 23.7 at (2, 3).
-Shape prefer_one_round(const a2c_plan &p, Shape s, size_t fixed, int32_t most_K,
-                       const int32_t (&simd_waves)[2], bool adjoint)
+Shape prefer_one_round(const a2c_plan &p, Shape s, int32_t most_K, FaForm form)
 {
-    if (one_round(p, s.K, s.W, fixed, simd_waves[s.K - 1])) return s;
+    if (one_round(p, s.K, s.W, form)) return s;
     const auto far = [&](int32_t K, int32_t W) { return spans_far(p, (int64_t)kWave * K * W); };
-    const bool near_only = adjoint && !far(s.K, s.W);
+    const bool near_only = form != FaForm::forward && !far(s.K, s.W);
     // (two residues per lane and more than eight waves spill)
     for (int32_t K = 1; K <= most_K; ++K)
         for (int32_t W = 2; W <= kMaxWaves / K; ++W)
-            if (one_round(p, K, W, fixed, simd_waves[K - 1]) && !(near_only && far(K, W)))
+            if (one_round(p, K, W, form) && !(near_only && far(K, W)))
                 return {K, W};
     return s;
 }
@@ -455,7 +461,7 @@ Shape default_forward(const a2c_plan &p)
         const int32_t whole = waves_for(p.max_len, 1);
         const Shape s{1, whole <= 8 ? pack_waves(p, 1, whole, 8)
                                     : std::min<int32_t>(R > 400000 ? 8 : 4, whole)};
-        return prefer_one_round(p, s, 6032, 1, {6, 5}, false);
+        return prefer_one_round(p, s, 1, FaForm::forward);
     }
     // a batch of a few chunks keeps a chunk that holds its longest chain
     if (p.max_len > 1024 && p.max_len <= 4096 && R <= 4 * 4096) return {4, waves_for(p.max_len, 4)};
@@ -480,7 +486,7 @@ Shape default_adjoint(const a2c_plan &p, Shape &rec)
         const int32_t whole = waves_for(p.max_len, 1);
         rec = {1, whole <= 8 ? pack_waves(p, 1, whole, 8) : linked_waves(p)};
         if (whole <= 8 && rec.W > 4 && (int64_t)kWave * rec.W * p.n_cu < R) rec.W = 4;
-        return rec = prefer_one_round(p, rec, 7024, 2, {4, 3}, true);
+        return rec = prefer_one_round(p, rec, 2, FaForm::mse);
     }
     // from coordinates: 256 x 700 7.2 at (4, 3), 5.2 at (1, 12); 700 chains of
     // 20..1000 9.2 at (4, 4), 8.3 at (2, 8); 6000 of them 41.4 and 41.9 at

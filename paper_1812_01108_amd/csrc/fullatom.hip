@@ -1193,11 +1193,19 @@ __global__ __launch_bounds__(LB) void fa_backward_flat_kernel(
     }
 }
 
+// Dynamic LDS of a launch: the waves' stages, whose place the frames entering the
+// units take first (no frames: the adjoint from coordinates; stage_atoms 0:
+// direct I/O).
+size_t fa_lds_bytes(FaForm form, int32_t W, int64_t stage_atoms)
+{
+    const size_t plane = (size_t)W * stage_atoms * sizeof(float);
+    return form == FaForm::coords ? 6 * plane : std::max(3 * plane, frame_bytes(W));
+}
+
 template <int K, int LB, bool STG>
 hipError_t fa_fwd_kl(const a2c_plan &p, const float *ang, float *xyz, hipStream_t s)
 {
-    const size_t stage = STG ? (size_t)p.fs.W * 3 * p.fs.fa_stage_atoms * sizeof(float) : 0;
-    const size_t lds = std::max(stage, frame_bytes(p.fs.W));
+    const size_t lds = fa_lds_bytes(FaForm::forward, p.fs.W, STG ? p.fs.fa_stage_atoms : 0);
     hipLaunchKernelGGL((p.fs.whole_chains ? fa_forward_flat_kernel<K, LB, false, STG>
                                           : fa_forward_flat_kernel<K, LB, true, STG>),
                        dim3(p.fs.n_win), dim3(p.fs.W * kWave), lds, s, ang, xyz, p.d_head_bits,
@@ -1229,8 +1237,8 @@ void fa_bwd_launch(const a2c_plan &p, const float *ang, const float *xyz, const 
     const Sched &S = p.bs;
     const bool pass = RECOMPUTE && S.pass();
     if (pass) launch_spine_pass(ang, p.d_head_bits, S, p.R, p.bb, s);
-    size_t lds = STG ? (size_t)S.W * (RECOMPUTE ? 3 : 6) * S.fa_stage_atoms * sizeof(float) : 0;
-    if (RECOMPUTE) lds = std::max(lds, frame_bytes(S.W));
+    const size_t lds = fa_lds_bytes(RECOMPUTE ? FaForm::recompute : FaForm::coords, S.W,
+                                    STG ? S.fa_stage_atoms : 0);
     const bool rev = RECOMPUTE ? pass : !S.whole_chains;
     auto kernel = S.whole_chains ? fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, false, STG>
                                  : fa_backward_flat_kernel<K, RECOMPUTE, LB, GM, true, STG>;
@@ -1278,20 +1286,7 @@ template <int K>
 hipError_t fa_bwd_k(const a2c_plan &p, const float *ang, const float *xyz, const float *g,
                     float *gang, hipStream_t s)
 {
-    // the staged coordinate form needs six planes; where they do not fit,
-    // the recompute form (three planes) computes the same gradient, and where
-    // their LDS leaves the launch more than one round it is the faster one:
-    // (1, 4), us from coordinates and recomputing: 64 x 300 9.1 and 13.2, 1000
-    // chains of 100 10.5 and 13.8, 512 of 50..2000 24.4 and 20.0, 4096 of
-    // them 206 and 141
-    if (xyz && !p.bs.fa_unstaged) {
-        const size_t stage = (size_t)p.bs.W * 6 * p.bs.fa_stage_atoms * sizeof(float);
-        const size_t group = stage + sizeof(FADevTable) + sizeof(BwdShared) + 512;
-        if (stage > (size_t)kMaxDynamicLds ||
-            (int64_t)p.bs.n_win > (int64_t)(kCuLds / group) * p.n_cu)
-            xyz = nullptr;
-    }
-    return xyz ? fa_bwd_mode<K, 0>(p, ang, xyz, g, gang, s)
+    return xyz && p.bs.fa_from_coords ? fa_bwd_mode<K, 0>(p, ang, xyz, g, gang, s)
                : fa_bwd_mode<K, 1>(p, ang, xyz, g, gang, s);
 }
 
@@ -1324,6 +1319,57 @@ hipError_t launch_fa_mse_step(const a2c_plan &p, const float *ang, const float *
     case 2: return fa_mse_k<2>(p, ang, tgt, xyz, loss_out, gang, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+template <int K, int LB, bool LINK>
+static const void *staged_kernel(FaForm form)
+{
+    switch (form) {
+    case FaForm::forward: return (const void *)fa_forward_flat_kernel<K, LB, LINK, true>;
+    case FaForm::coords:
+        return (const void *)fa_backward_flat_kernel<K, false, LB, kGradLoad, LINK, true>;
+    case FaForm::recompute:
+        return (const void *)fa_backward_flat_kernel<K, true, LB, kGradLoad, LINK, true>;
+    case FaForm::mse: break;
+    }
+    return (const void *)fa_backward_flat_kernel<K, true, LB, kGradMse, LINK, true>;
+}
+
+template <int K, bool LINK>
+static const void *staged_kernel(FaForm form, int32_t W)
+{
+    const int threads = W * kWave;
+    return threads <= 256        ? staged_kernel<K, 256, LINK>(form)
+           : threads <= kLbSmall ? staged_kernel<K, kLbSmall, LINK>(form)
+                                 : staged_kernel<K, kLbLarge, LINK>(form);
+}
+
+// The kernel's own LDS and registers come from the loaded code: literals here
+// went stale when a kernel changed (the forward over whole chains takes 68
+// registers, seven waves a SIMD, the linked one 74, six).  LDS is handed out in
+// pieces of 1280 bytes; a SIMD has 512 registers a lane, given in eights, and
+// runs at most eight waves.  A workgroup counts as one wave on each SIMD, or as
+// many as the fullest holds when its waves are dealt out over the four (five
+// waves at four a SIMD: two workgroups; 4096 chains of 50..2000 recomputing 253
+// us, 149 at eight waves).
+FaHeld fa_held(FaForm form, int32_t K, int32_t W, bool whole_chains, int64_t stage_atoms)
+{
+    constexpr size_t kCuLds = 160 * 1024, kGranule = 1280;
+    constexpr int32_t kSimdRegisters = 512, kSimdWaves = 8, kSimds = 4;
+    const size_t dynamic = fa_lds_bytes(form, W, stage_atoms);
+    hipFuncAttributes a{};
+    const void *kernel = K == 1 ? whole_chains ? staged_kernel<1, false>(form, W)
+                                               : staged_kernel<1, true>(form, W)
+                         : whole_chains ? staged_kernel<2, false>(form, W)
+                                        : staged_kernel<2, true>(form, W);
+    if (dynamic > (size_t)kMaxDynamicLds) return {0, 0};
+    if (hipFuncGetAttributes(&a, kernel) != hipSuccess) {
+        (void)hipGetLastError();  // not for the next launch to report
+        return {0, 0};
+    }
+    const size_t group = (dynamic + a.sharedSizeBytes + kGranule - 1) / kGranule * kGranule;
+    const int32_t simd = std::min(kSimdWaves, kSimdRegisters / std::max(8, (a.numRegs + 7) / 8 * 8));
+    return {(int32_t)(kCuLds / group), simd / ((W + kSimds - 1) / kSimds)};
 }
 
 template <typename F>

@@ -93,3 +93,18 @@ def test_autotuner_times_default_and_present_first(tmp_path, default, present):
     assert cands[0] == default and present in cands[:2]
     assert len(set(cands)) == len(cands)
     assert {(k, w) for k in (1, 2, 4, 8) for w in (1, 2, 3, 4, 6, 8, 12, 16)} <= set(cands)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("length,waves", [(180, 3), (120, 2)])
+def test_default_forward_counts_the_kernels_own_registers(length, waves):
+    """The forward over whole chains runs seven workgroups of up to four waves a
+    CU where their LDS allows it (glycines: four atoms), one more than the
+    linked one: 6.6 chains a CU, one to a window, are one round."""
+    import torch
+    n = int(6.6 * torch.cuda.get_device_properties(0).multi_processor_count)
+    from workloads import ALPHABET
+    off = offsets_from_lengths([length] * n)
+    plan = _a2c().Plan("fullatom", offsets=off,
+                       seq=np.full(n * length, ALPHABET.index("G"), np.uint8))
+    assert plan.schedule == {"res_per_lane": 1, "waves_per_group": waves, "n_tiles": n}
