@@ -172,8 +172,7 @@ typedef struct {
  * chain.  Fails with A2C_ERR_INVALID_ARG on malformed offsets or codes >= 20,
  * and with A2C_ERR_UNSUPPORTED, before any device call, if a chain is longer
  * than 64 chunks of the widest schedule (262144 residues for A2C_BACKBONE,
- * 131072 for A2C_FULLATOM), or if the full-atom default schedule cannot stage
- * its atoms in LDS.  *out is NULL on failure.                             */
+ * 131072 for A2C_FULLATOM).  *out is NULL on failure.                      */
 a2c_status a2c_plan_create(a2c_plan **out, int32_t model, int32_t n_chains,
                            const int32_t *h_res_offsets, const uint8_t *h_seq,
                            const a2c_backbone_geometry *geom,
@@ -184,7 +183,9 @@ a2c_status a2c_plan_create(a2c_plan **out, int32_t model, int32_t n_chains,
  * coordinates (12 bytes per atom, A atoms) fit the plan's memory budget, so
  * a2c_backward should be given them (d_coords); 0 when the adjoint should
  * recompute the frames from the angles (d_coords = NULL).  Host only.  Both
- * choices give the same gradient up to float32 rounding. */
+ * choices give the same gradient up to float32 rounding.  This is the budget's
+ * answer alone: the full-atom adjoint may recompute the frames although it is
+ * given coordinates (a2c_plan_set_schedule). */
 a2c_status a2c_plan_keep_coords(const a2c_plan *plan, int32_t *keep);
 
 void a2c_plan_destroy(a2c_plan *plan);
@@ -243,10 +244,12 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  * may be replayed after the plan is destroyed.
  * UNSUPPORTED, leaving the plan's schedule as it was, if the longest chain
  * needs more than 64 chunks.  Full-atom atom I/O goes through a per-wave LDS
- * stage (three float planes; the adjoint from coordinates stages six and
- * recomputes the frames from the angles instead where those do not fit,
- * with the same result); where the waves' atoms of one chunk exceed 136 KiB
- * of LDS, the kernels read and write atoms in global memory directly. */
+ * stage (three float planes; the adjoint from coordinates stages six, and
+ * recomputes the frames from the angles instead, with the same result, where
+ * those do not fit or leave more workgroups than the device's LDS holds at
+ * once: with four waves, batches of more than some two windows per CU); where
+ * the waves' atoms of one chunk exceed 136 KiB of LDS, the kernels read and
+ * write atoms in global memory directly. */
 a2c_status a2c_plan_set_schedule(a2c_plan *plan, int32_t res_per_lane,
                                  int32_t waves_per_group, void *stream);
 a2c_status a2c_plan_get_schedule(const a2c_plan *plan, int32_t *res_per_lane,
@@ -315,6 +318,8 @@ a2c_status a2c_forward(a2c_plan *plan, int32_t variant, const float *d_angles,
  *              NULL: A2C_SCAN then recomputes the frames from the angles
  *              inside the backward kernel (nothing is stored between the two
  *              passes).  A2C_PLAIN requires the workspace its forward filled.
+ *              Full-atom plans may recompute them all the same
+ *              (a2c_plan_set_schedule).
  * The result is exact up to float32 rounding: for angle alpha_i of node i,
  *   dL/dalpha_i = u_i . sum_{k in subtree(i)} (r_k - r_i) x dL/dr_k,
  * u_i the unit bond vector the node rotates about, which equals the sums of

@@ -145,7 +145,9 @@ class Plan:
     @property
     def keep_coords(self) -> bool:
         """The plan's store-vs-recompute choice: keep the forward's
-        coordinates for the adjoint (True) or recompute the frames (False)."""
+        coordinates for the adjoint (True) or recompute the frames (False).
+        The memory budget's answer alone: large full-atom batches recompute
+        the frames either way, where that is faster."""
         return self._keep_coords
 
     def atom_offsets(self):
@@ -409,7 +411,8 @@ class Angles2Coords(torch.autograd.Function):
 
     mode "auto" (default): the plan's store-vs-recompute choice
     (Plan.keep_coords: the coordinates fit its memory budget or not);
-    mode "coords": the backward reads the forward's coordinates (saved);
+    mode "coords": the backward is given the forward's coordinates (saved),
+    which the full-atom adjoint reads where one round of workgroups can;
     mode "recompute": the backward recomputes every frame from the angles and
     nothing but the angles is kept between the passes;
     mode "plain": the paper's GPU design (stores M_i per atom in a workspace).

@@ -108,3 +108,28 @@ def test_default_forward_counts_the_kernels_own_registers(length, waves):
     plan = _a2c().Plan("fullatom", offsets=off,
                        seq=np.full(n * length, ALPHABET.index("G"), np.uint8))
     assert plan.schedule == {"res_per_lane": 1, "waves_per_group": waves, "n_tiles": n}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("past", [-1, 1])
+def test_full_atom_adjoint_reads_coordinates_up_to_one_round(past):
+    """At four waves, two workgroups of six staged planes a CU: up to two
+    windows a CU the adjoint reads the coordinates it is given, beyond it
+    recomputes the frames.  Linked windows, against the oracle."""
+    import torch
+    import oracle
+    from tests.gpu_util import GRAD_TOL_REL, grad_rel_err
+    from workloads import BACKBONE_GEOMETRY
+    windows = 2 * torch.cuda.get_device_properties(0).multi_processor_count + past
+    lengths = [700] * (windows * 256 // 700) + [windows * 256 % 700]
+    off = offsets_from_lengths(lengths)
+    rng = np.random.Generator(np.random.PCG64(911))
+    seq, ang = random_sequence(rng, int(off[-1])), make_angles(rng, int(off[-1]), "mixture", 7)
+    plan = _a2c().Plan("fullatom", offsets=off, seq=seq)
+    plan.set_schedule(1, 4)
+    a, g = to_dev(ang), upstream_grad(7, plan.n_atoms)
+    grad = plan.backward(a, to_dev(g), coords=plan.forward(a))
+    ref = oracle.fullatom_backward(off, seq, ang, BACKBONE_GEOMETRY, g)
+    assert grad_rel_err(grad.cpu().numpy(), ref, off) <= GRAD_TOL_REL
+    off_by = plan.backward(a, to_dev(g), coords=plan.forward(a) + 1.0)
+    assert torch.equal(grad, off_by) == (past > 0)
