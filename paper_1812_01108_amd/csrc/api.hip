@@ -156,8 +156,6 @@ a2c_status upload_starts(const std::vector<int64_t> &starts, int32_t *&d_wstart,
     return upload((void **)&d_wstart, v.data(), v.size() * sizeof(int32_t), s);
 }
 
-// Pack the tiles of schedule (K, W) and upload its tile table into out
-// (whose own table, if any, the caller frees).
 // Greedy packing of whole chains, in order, into tiles: chains of at most one
 // chunk (`cap` residues) share tiles of at most `cap` residues; a longer chain
 // gets a tile of its own, which the kernels walk chunk by chunk.  Zero-length

@@ -579,11 +579,13 @@ __device__ __forceinline__ void bb_store_torques(float *buf, const float (&gr)[3
 // scan give every atom's position, then the adjoint's reverse scan runs on
 // them, all in registers: 12 + 36 bytes in and 12 out per residue (+ 36 where
 // the fused step writes the positions).
-// Bound by VALU issue (some 2300 instructions per wave of 256 residues at
-// K = 4) with the memory close behind; hence the forward's straight-line walk
+// Bound by VALU issue (1900 instructions per wave of 256 residues at K = 4: 44
+// us of issue on 6000 chains of 20..1000 residues) with the memory close behind
+// (189 MB there, 37 us at a copy's rate); hence the forward's straight-line walk
 // and constant-offset LDS transposes, against per-residue predicates and
-// per-element index divisions before.  On 6000 chains of 20..1000 residues
-// the adjoint went from 65.4 to 55.5 us at (4, 4) (51.7 at (4, 8)).  The
+// per-element index divisions before.  On those chains the adjoint went from
+// 65.4 to 55.5 us at (4, 4) (51.7 at (4, 8), 59 with its inputs out of cache);
+// at K = 4 two values spill under the bound of four waves per SIMD.  The
 // fused step went from 247 to 77.9 us there: its loss shares now travel in
 // tagged words, where every workgroup's fence before its atomic count flushed
 // the L2.  On 48 chains of 1500..6000 residues, one workgroup walking each

@@ -769,9 +769,9 @@ __device__ __forceinline__ void fa_emit_residue(const FADevTable &tab, int type,
 // copied out with coalesced stores (STG; otherwise, for schedules whose stage
 // does not fit the LDS, straight to global memory).  The stage takes the
 // frames' place once every lane holds its own.
-// Bound by VALU issue and waits in turn: 1137 instructions per wave of 64
-// residues at K = 1 (62 us of issue for 2.16 M residues in some 114 us, where
-// the 288 MB would take 56), 16 waves per CU (the LDS stages).  The spine scan
+// Bound by VALU issue and waits in turn: 1082 instructions per wave of 64
+// residues at K = 1 (60 us of issue for 2.16 M residues in some 110 us, where
+// the 301 MB it moves would take 59), 16 waves per CU (the LDS stages).  The spine scan
 // on a quarter of the waves, one loop over the last frame's atoms and 12-byte
 // stage accesses took 2000 chains of 50..2000 residues from 59.7 to 51.5 us at
 // (1, 4), 500 chains of 151 from 11.9 to 10.7 us at (1, 6).
@@ -944,7 +944,8 @@ struct AtomForce {
 // gradient is 2 (r - t), formed from the recomputed positions (the fused
 // training step); xyz_out (may be NULL) receives the positions, loss_out
 // (may be NULL) the batch's sum of |r - t|^2 (lb_loss_commit).
-// Bound as the forward, with 1759 instructions per wave at K = 1.  Without the
+// Bound as the forward, with 1699 instructions per wave at (1, 8) (94 us of
+// issue for 2.16 M residues recomputing, 366 MB, in some 150 us).  Without the
 // spine pass before it (6.5 us on 512 chains of 50..2000 residues), with the
 // spine scan on a quarter of the waves, the extra atoms in one loop and the
 // first rows of the gradients loaded ahead of the scan, the recomputing form

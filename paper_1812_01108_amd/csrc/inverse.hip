@@ -135,8 +135,8 @@ constexpr int kInvThreads = 256;  // residues per workgroup
 // residues [max(r0 - 1, 0), min(r0 + 257, R)), at most 258 residues of at most
 // kAtoms atoms each; rows of 256 atoms past the range are skipped as a whole.
 // Bound by the memory: 1.68 M full-atom residues, 223 MB with the atoms no
-// torsion needs (they share cache lines with those that do), in 44.3 us, 5.0
-// TB/s, the rate of a device copy; 52.6 us before, with 630 VALU instructions
+// torsion needs (they share cache lines with those that do; 235 MB counted), in
+// 44.3 us, 5.0 TB/s, the rate of a device copy; 52.6 us before, with 630 VALU instructions
 // per wave (549 now: shared bonds and normals) and seven useless rows of loads
 // per thread.  128 residues per workgroup 47.9 us, 64 52.2, 512 46.6.
 // NT: large plans write the angles with non-temporal stores (46.3 -> 44.3 us);
