@@ -354,11 +354,10 @@ a2c_status a2c_coords_to_angles(a2c_plan *plan, const float *d_coords, float *d_
  *   L = sum over atoms a of |r_a - t_a|^2
  * (r the map of d_angles, t = d_target [3][A]): one kernel over the windows
  * (after a spine-only pass where a2c_plan_set_schedule says so) recomputes the
- * frames, forms the loss gradient 2 (r - t) in
- * registers and runs the adjoint above, so neither the coordinates nor
- * their gradient make a round trip through memory.  Same result as
- * a2c_forward, then dL/dr = 2 (r - t), then a2c_backward, up to float32
- * rounding.
+ * frames, forms the loss gradient 2 (r - t) in registers and runs the adjoint
+ * above, so neither the coordinates nor their gradient make a round trip
+ * through memory.  Same result as a2c_forward, then dL/dr = 2 (r - t), then
+ * a2c_backward, up to float32 rounding.
  *   d_coords      [3][A] receives r, or NULL (not written);
  *   d_loss        float[1] receives L, or NULL (not computed).  Each window
  *                 adds its atoms in a fixed order into a share kept in the
