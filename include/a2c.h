@@ -227,8 +227,9 @@ a2c_status a2c_plan_workspace_bytes(const a2c_plan *plan, int32_t variant,
  *     or by as many workgroups more at the head of the launch, which wait on
  *     nothing, and the windows are taken last to first too); a launch
  *     therefore progresses whenever the device holds 8 of its workgroups at
- *     once.  Consequently two such calls on one plan must not run at the same
- *     time (on different streams).
+ *     once (on fewer, a wait gives up after a bounded time and takes NaN, so
+ *     that every launch ends).  Consequently two such calls on one plan must
+ *     not run at the same time (on different streams).
  *   - The backbone adjoint that recomputes the frames (a2c_backward without
  *     d_coords) hands nothing between workgroups.  Where every chain fits in
  *     one chunk, it and the backbone fused step run on windows of whole
