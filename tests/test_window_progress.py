@@ -98,3 +98,46 @@ def test_default_schedules_need_no_spine_pass(model, lengths, waves):
     assert plan.adjoint_schedule["waves_per_group"] == waves
     for name, call in _calls(plan, ang).items():
         assert len(_kernels(call)) == 1, name
+
+
+@pytest.mark.parametrize("model,K,W", [("backbone", 1, 2), ("fullatom", 1, 4), ("fullatom", 2, 2)])
+def test_replays_between_other_calls_on_the_same_words(model, K, W):
+    """A captured call with leads (K = 1) or a spine pass, replayed between eager
+    calls of every form, which move the tags of the same words on."""
+    import torch
+    cap = 64 * K * W
+    plan, ang = _plan(model, [9, 10 * cap + 3, 70, cap])
+    plan.set_schedule(K, W)
+    target = torch.randn((3, plan.n_atoms), device=ang.device)
+    coords, loss = plan.forward(ang), torch.empty(1, device=ang.device)
+    grads = [torch.empty_like(ang) for _ in range(3)]
+
+    def call(which):
+        if which == 0:
+            plan.mse_step(ang, target, grad_angles=grads[0], loss_out=loss)
+        else:
+            plan.backward(ang, target, coords=coords if which == 2 else None,
+                          grad_angles=grads[which])
+        torch.cuda.synchronize()
+        return [grads[which].clone()] + ([loss.clone()] if which == 0 else [])
+
+    want = [call(k) for k in range(3)]
+    graphs = []
+    for k in range(3):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            if k == 0:
+                plan.mse_step(ang, target, grad_angles=grads[0], loss_out=loss)
+            else:
+                plan.backward(ang, target, coords=coords if k == 2 else None, grad_angles=grads[k])
+        graphs.append(graph)
+    for replayed, eager in [(0, 1), (1, 2), (2, 0), (0, 0), (1, 1), (0, 2), (0, 1)]:
+        for g in grads:
+            g.fill_(float("nan"))
+        graphs[replayed].replay()
+        torch.cuda.synchronize()
+        assert torch.equal(grads[replayed], want[replayed][0])
+        if replayed == 0:
+            assert torch.equal(loss, want[0][1])
+        for a, b in zip(call(eager), want[eager]):
+            assert torch.equal(a, b)
